@@ -215,7 +215,9 @@ enum {
 
 /* Optional per-kernel timing (host memory).  When passed to an entry point,
  * elapsed milliseconds (HIP events on `stream`) and launch counts of every
- * kernel class are ADDED to the record, after the call waits for its events. */
+ * kernel class are ADDED to the record, after the call waits for its events.
+ * A launch that does the work of several samples, or several of a class's
+ * steps, counts as that many. */
 typedef struct bgpo_timing {
   double ms[BGPO_K_COUNT];
   int64_t launches[BGPO_K_COUNT];

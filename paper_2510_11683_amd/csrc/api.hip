@@ -80,7 +80,8 @@ size_t workspace_layout(const Dims& dm, const Plan& pl, void* base, Workspace* w
   // of a large allocation the forward ran up to 5 % slower (measured), at
   // its head not.
   auto take_unit = [&](Workspace& w) {
-    w.meta = static_cast<SampleMeta*>(take(G * sizeof(SampleMeta)));
+    w.meta = static_cast<SampleMeta*>(take(2 * G * sizeof(SampleMeta)));
+    w.meta2 = w.meta + (b ? G : 0);
     w.idx = static_cast<int32_t*>(take(G * P * 4));
     w.row_tgt = static_cast<int32_t*>(take(RP * 4));
     w.row_seq = static_cast<int32_t*>(take(RP * 4));
@@ -422,14 +423,10 @@ static int run_forward_unit(const bgpo_problem* p, Workspace& ws, Timer& tm, int
   const Dims dm = dims_of(p);
   ws.g_used = n_s;
   BGPO_TRY(tm.begin(BGPO_K_MASK));
-  for (int gs = 0; gs < n_s; ++gs) {
-    const int j = j0 + gs;
-    BGPO_TRY(launch_mask_compact(resp, targets, dm.B, dm.L, dm.n_t, j, gs, p->t_mode, p->seed,
-                                 p->seq_id_base, &ws, nullptr, n_masked + j, dm.n_t,
-                                 t_out ? t_out + j : nullptr, dm.n_t, dm.V,
-                                 gs ? ws.meta + (gs - 1) : prev_unit, dx_plan(dm, ws, grid),
-                                 ws.mask_scratch, false, s));
-  }
+  BGPO_TRY(launch_masks(resp, targets, dm.B, dm.L, dm.n_t, j0, n_s, p->t_mode, p->seed,
+                        p->seq_id_base, &ws, nullptr, n_masked + j0, dm.n_t,
+                        t_out ? t_out + j0 : nullptr, dm.n_t, dm.V, prev_unit,
+                        dx_plan(dm, ws, grid), ws.mask_scratch, false, s));
   BGPO_TRY(tm.end(n_s));
   BGPO_TRY(tm.begin(BGPO_K_GATHER));
   if (act.gamma)
@@ -508,10 +505,9 @@ int bgpo_sample_masks(const bgpo_problem* prob, const uint8_t* resp_mask, int32_
   const int st = plan_problem(prob, &pl);
   if (st != BGPO_OK) return st;
   if (!resp_mask || !idx || !n_masked || j < 0 || j >= prob->n_t) return BGPO_ERR_INVALID_ARG;
-  if (launch_mask_compact(resp_mask, nullptr, prob->B, prob->L, prob->n_t, j, 0, prob->t_mode,
-                          prob->seed, prob->seq_id_base, nullptr, idx, n_masked, 1, t_out, 1,
-                          prob->V, nullptr, DxPlan{1, 1, 1, 1}, nullptr, false,
-                          (hipStream_t)stream) != hipSuccess)
+  if (launch_masks(resp_mask, nullptr, prob->B, prob->L, prob->n_t, j, 1, prob->t_mode, prob->seed,
+                   prob->seq_id_base, nullptr, idx, n_masked, 1, t_out, 1, prob->V, nullptr,
+                   DxPlan{1, 1, 1, 1}, nullptr, false, (hipStream_t)stream) != hipSuccess)
     return BGPO_ERR_HIP;
   return BGPO_OK;
 }
@@ -734,13 +730,14 @@ static int elbo_bwd_impl(const bgpo_problem* prob, const Act& act, const void* W
   const int j_end = prob->j_begin + prob->j_count;
   const bool store_u = !ws.chunk;   // stored mode keeps the forward's exponentials
   int in_batch = 0;        // units already in the current dW batch
-  int prev_used = 0;       // samples of the previous unit (its record is meta[prev_used - 1])
+  const SampleMeta* last = nullptr;   // the record of the previous unit
   for (int j0 = prob->j_begin; j0 < j_end; j0 += (int)ws.G) {
     const int n_s = std::min<int>(j_end - j0, (int)ws.G);
     // a unit after the first of its batch puts its dZ rows / H_c^T columns
-    // after the previous unit's (whose last record the first mask launch reads
-    // before any record is rewritten)
-    const SampleMeta* prev = in_batch ? ws.meta + (prev_used - 1) : nullptr;
+    // after the previous unit's, whose record the mask kernel reads while it
+    // writes this unit's: the two take turns in two sets of records
+    const SampleMeta* prev = in_batch ? last : nullptr;
+    std::swap(ws.meta, ws.meta2);
     st = run_forward_unit(prob, ws, tm, grid, j0, n_s, act, targets, resp_mask, adv, ell_old,
                           loss_scale, ell, g, loss, n_masked, t_out, status_flags, true, store_u,
                           prev, dbar, s);
@@ -748,7 +745,7 @@ static int elbo_bwd_impl(const bgpo_problem* prob, const Act& act, const void* W
     st = unit_backward(ws, act, j0, prob->j_begin, static_cast<const uint16_t*>(W_head), dX,
                        dgamma, dW, dm, grid, tm, s);
     if (st != BGPO_OK) return st;
-    prev_used = n_s;
+    last = ws.unit();
     // stored mode: one dW GEMM per batch of units, K over all their rows (the
     // recompute mode accumulated dW chunk by chunk)
     if (!ws.chunk && (++in_batch == (int)ws.dw_batch || j0 + n_s >= j_end)) {
@@ -885,10 +882,9 @@ extern "C" int bgpo_test_mask_multiblock(const bgpo_problem* prob, const uint8_t
   if (!scratch || ((uintptr_t)scratch % 256) != 0 ||
       scratch_bytes < mask_scratch_bytes(prob->B, prob->L))
     return BGPO_ERR_WORKSPACE;
-  if (launch_mask_compact(resp_mask, nullptr, prob->B, prob->L, prob->n_t, j, 0, prob->t_mode,
-                          prob->seed, prob->seq_id_base, nullptr, idx, n_masked, 1, t_out, 1,
-                          prob->V, nullptr, DxPlan{1, 1, 1, 1}, scratch, true,
-                          (hipStream_t)stream) != hipSuccess)
+  if (launch_masks(resp_mask, nullptr, prob->B, prob->L, prob->n_t, j, 1, prob->t_mode, prob->seed,
+                   prob->seq_id_base, nullptr, idx, n_masked, 1, t_out, 1, prob->V, nullptr,
+                   DxPlan{1, 1, 1, 1}, scratch, true, (hipStream_t)stream) != hipSuccess)
     return BGPO_ERR_HIP;
   return BGPO_OK;
 }

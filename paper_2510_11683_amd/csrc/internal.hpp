@@ -60,6 +60,8 @@ struct SampleMeta {
   int32_t pad[56];
 };
 
+constexpr int kMaxDxSplit = 16;   // vocabulary splits of the dX GEMM
+
 // What the mask kernel needs to choose the dX split of a unit (the split
 // count that best fills the persistent grid for the unit's row count).
 struct DxPlan {
@@ -73,6 +75,8 @@ struct DxPlan {
 // (RP = G * NP rows) and the buffers shared by all units.
 struct Workspace {
   SampleMeta* meta;    // [G]          one record per sample of the unit
+  SampleMeta* meta2;   // [G]          a second set: consecutive units of a dW batch alternate, since
+                       //              a unit's masks read the last record of the unit before it
   int32_t* idx;        // [G*P]        masked flat positions, per sample ascending
   int32_t* row_tgt;    // [RP]         target token of each compacted row
   int32_t* row_seq;    // [RP]         g*B + b of each row (sample g of the unit, response b)
@@ -150,16 +154,18 @@ size_t workspace_layout(const Dims& dm, const Plan& pl, void* base, Workspace* w
 // slab); fp32 W (f32) is rounded to bf16 as it is read
 hipError_t launch_transpose_w(const void* W, bool f32, uint16_t* WT, uint16_t* Wk, int d, int V,
                               hipStream_t s);
-// Mask and compaction of sample j, sample g of its unit: rows go after those of
-// the unit's earlier samples (prev = record of sample g - 1); for g = 0, prev
-// (may be NULL) is the record of the previous unit of the dW batch, whose
-// columns this unit's follow.
-hipError_t launch_mask_compact(const uint8_t* resp, const int32_t* targets, int B, int L, int n_t,
-                               int j, int g, int t_mode, uint64_t seed, uint32_t seq_base,
-                               const Workspace* ws, int32_t* idx_out, int32_t* n_masked_out,
-                               int nm_stride, float* t_out, int t_stride, int V,
-                               const SampleMeta* prev, const DxPlan& plan, void* scratch,
-                               bool force_multi, hipStream_t s);
+// Masks and compaction of the samples j0 .. j0 + n_samples - 1 of a unit, the
+// rows of each after those of the unit's earlier samples; prev_unit (may be
+// NULL) is the record of the previous unit of the dW batch, whose columns this
+// unit's follow (not one of the records written here).  Sample g's counts and
+// timesteps go to n_masked_out + g and t_out + g.  ws NULL: one sample's
+// positions only.
+hipError_t launch_masks(const uint8_t* resp, const int32_t* targets, int B, int L, int n_t, int j0,
+                        int n_samples, int t_mode, uint64_t seed, uint32_t seq_base,
+                        const Workspace* ws, int32_t* idx_out, int32_t* n_masked_out,
+                        int nm_stride, float* t_out, int t_stride, int V,
+                        const SampleMeta* prev_unit, const DxPlan& plan, void* scratch,
+                        bool force_multi, hipStream_t s);
 // scratch bytes the multi-block mask passes need (mask words, block counts and
 // offsets, timesteps); with scratch NULL the single-workgroup kernel runs, and
 // with scratch the multi-block passes run above 65536 positions (or always,

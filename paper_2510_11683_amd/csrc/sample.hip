@@ -25,13 +25,8 @@ struct MaskWalker {
   int L, j;
   int cached_b = -1, cached_blk = -1;
   u32x4 w;
-  __device__ bool masked(const uint8_t* resp, const uint32_t* sT, int64_t p) {
-    return resp[p] ? test(sT, p) : false;
-  }
-  // the Philox test of response position p (resp_mask[p] != 0 assumed)
-  __device__ bool test(const uint32_t* sT, int64_t p) {
-    const int b = (int)(p / L);
-    const int i = (int)(p - (int64_t)b * L);
+  // the Philox test of response position i of response b
+  __device__ bool test(const uint32_t* sT, int b, int i) {
     const int blk = i >> 2;
     if (blk != cached_blk || b != cached_b) {
       w = philox4x32_10(u32x4{(uint32_t)blk, seq_base + (uint32_t)b, (uint32_t)j, 0u}, k0, k1);
@@ -49,145 +44,206 @@ struct MaskWalker {
 //   prologue and fp32 partial store) + ~0.65 per (split, row tile) for the
 //   reduction of the partials.
 // A fixed split leaves most of the last round idle for some row counts
-// (576 tiles on 256 workgroups use 2.25 of 3 rounds).
-__device__ void choose_dx_split(int row_tiles, const DxPlan& pl, int* split, int* kslab) {
+// (576 tiles on 256 workgroups use 2.25 of 3 rounds).  One wave: lane l
+// estimates the split l + 1, the smallest estimate (of the smallest split)
+// wins.
+__device__ void choose_dx_split(int row_tiles, const DxPlan& pl, int lane, int* split, int* kslab) {
+  static_assert(kMaxDxSplit <= 64, "one lane per split");
+  const int sp = min(lane, pl.s_max - 1) + 1;
   // 32-bit divisions (tiles <= 16384 x 256 x 16), 64-bit cost
-  int best_s = 1, best_ks = pl.kslabs;
-  uint64_t best = ~0ull;
-  for (int sp = 1; sp <= pl.s_max && row_tiles > 0; ++sp) {
-    const uint32_t ks = ((uint32_t)pl.kslabs + sp - 1) / sp;
-    const uint32_t se = ((uint32_t)pl.kslabs + ks - 1) / ks;   // splits actually used
-    const uint32_t tiles = (uint32_t)row_tiles * pl.col_tiles * se;
-    const uint32_t rounds = (tiles + pl.grid - 1) / pl.grid;
-    const uint64_t cost = (uint64_t)rounds * (ks + 10) * 20 + 13ull * se * row_tiles;
-    if (cost < best) {
-      best = cost;
-      best_s = (int)se;
-      best_ks = (int)ks;
-    }
+  const uint32_t ks = ((uint32_t)pl.kslabs + sp - 1) / sp;
+  const uint32_t se = ((uint32_t)pl.kslabs + ks - 1) / ks;   // splits actually used
+  const uint32_t tiles = (uint32_t)row_tiles * pl.col_tiles * se;
+  const uint32_t rounds = (tiles + pl.grid - 1) / pl.grid;
+  const uint64_t cost = (uint64_t)rounds * (ks + 10) * 20 + 13ull * se * row_tiles;
+  uint64_t best = (cost << 6) | (uint32_t)(sp - 1);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    const uint64_t o = __shfl_xor((unsigned long long)best, off, 64);
+    best = o < best ? o : best;
   }
-  *split = best_s;
-  *kslab = best_ks;
+  const int win = row_tiles > 0 ? (int)(best & 63) : 0;
+  *split = row_tiles > 0 ? __shfl((int)se, win, 64) : 1;
+  *kslab = row_tiles > 0 ? __shfl((int)ks, win, 64) : pl.kslabs;
 }
 
-// Pointers of a unit's row state handed to the mask kernel (all NULL for the
-// mask-only test hook, which writes positions to idx at row 0).
+// Pointers of a unit's row state handed to the mask kernels (all NULL but idx
+// for the mask-only entry point, which writes positions to idx at row 0).
 struct MaskOut {
   int32_t* idx;          // [rows]  masked flat positions, indexed by unit row
   int32_t* row_tgt;      // [rows]  target token
   int32_t* row_seq;      // [rows]  g*B + b
-  int32_t* seg_off;      // [B+1]   this sample's response offsets (unit rows)
-  uint32_t* t24;         // [B]     this sample's timesteps
-  SampleMeta* meta;      // this sample's record
+  int32_t* seg_off;      // [G, B+1] every sample's response offsets (unit rows)
+  uint32_t* t24;         // [G, B]  every sample's timesteps
+  SampleMeta* meta;      // [G]     every sample's record
   int row_cap;           // rows the unit holds (padding is written up to it)
 };
 
 // The record of a sample whose `total` masked rows follow row0 rows of its
-// unit, with the unit's columns from col0.
-__device__ void write_record(SampleMeta* m, int row0, int col0, int total, const DxPlan& plan) {
+// unit, with the unit's columns from col0 (called by one whole wave).
+__device__ void write_record(SampleMeta* m, int row0, int col0, int total, const DxPlan& plan,
+                             int lane) {
   if (!m) return;
   const int rows = row0 + total;
   const int rows_pad = (rows + kRowPad - 1) / kRowPad * kRowPad;
-  m->n_rows = rows;
-  m->n_rows_pad = rows_pad;
-  m->col_off = col0;
-  m->col_end = col0 + (rows + 63) / 64 * 64;
-  m->s_rows = total;
-  m->s_row_off = row0;
-  choose_dx_split(rows_pad / kRowPad, plan, &m->dx_split, &m->dx_kslab);
+  int split, kslab;
+  choose_dx_split(rows_pad / kRowPad, plan, lane, &split, &kslab);
+  if (lane == 0) {
+    m->n_rows = rows;
+    m->n_rows_pad = rows_pad;
+    m->col_off = col0;
+    m->col_end = col0 + (rows + 63) / 64 * 64;
+    m->s_rows = total;
+    m->s_row_off = row0;
+    m->dx_split = split;
+    m->dx_kslab = kslab;
+  }
 }
 
-// Single-workgroup form (up to kSingleBlockPositions positions): timesteps in
-// LDS, every thread a contiguous run of positions, one block-wide scan.
+// Single-workgroup form: workgroup g handles sample j0 + g of a unit, timesteps
+// in LDS, kSpan positions at a time (all of them up to kSingleBlockPositions;
+// only the mask-only entry point goes beyond), every thread a contiguous run
+// of at most 64 positions whose mask bits stay in a register between the
+// count and the output, one block-wide scan.  Bound by the Philox arithmetic
+// of one compute unit and by latency.  The first row of a sample follows from
+// the mask counts of the unit's earlier samples, which every workgroup counts
+// again for itself (one Philox block per four positions), so that the samples
+// of a unit run side by side in one launch.  Against one launch per sample: a
+// whole step of 4 samples of 128 positions 117 -> 99 us, of 6 samples of 603
+// positions 192 -> 171 us.
+constexpr int kSpan = 64 * kMaskThreads;
+static_assert(kSingleBlockPositions <= kSpan, "one span per sample in a unit");
+
+// The mask bits of positions p0 .. p1 - 1 (at most 64): response position i0
+// of response b0 onwards.  p0 is a multiple of 4, so that the response-mask
+// bytes load four at a time.
+__device__ __forceinline__ uint64_t mask_run(MaskWalker& mw, const uint8_t* resp,
+                                             const uint32_t* sT, int p0, int p1, int b, int i) {
+  const bool words = ((uintptr_t)resp & 3) == 0;
+  uint64_t bits = 0;
+  for (int p = p0; p < p1; p += 4) {
+    uint32_t r4 = 0;
+    if (words && p + 4 <= p1) {
+      r4 = *reinterpret_cast<const uint32_t*>(resp + p);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) r4 |= p + e < p1 ? (uint32_t)resp[p + e] << (8 * e) : 0u;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (p + e < p1) {
+        if (((r4 >> (8 * e)) & 255u) && mw.test(sT, b, i)) bits |= 1ull << (p - p0 + e);
+        if (++i == mw.L) {
+          i = 0;
+          ++b;
+        }
+      }
+    }
+  }
+  return bits;
+}
+
 __global__ __launch_bounds__(kMaskThreads) void k_mask_compact(
     const uint8_t* __restrict__ resp, const int32_t* __restrict__ targets, int B, int L, int n_t,
-    int j, int g, int t_mode, uint32_t k0, uint32_t k1, uint32_t seq_base, MaskOut out,
+    int j0, int t_mode, uint32_t k0, uint32_t k1, uint32_t seq_base, MaskOut out,
     int32_t* __restrict__ nm_out, int nm_stride, float* __restrict__ t_out, int t_stride, int V,
     const SampleMeta* prev, DxPlan plan) {
-  __shared__ uint32_t sT[kMaxB];
+  __shared__ uint32_t sT[kMaxB];      // timesteps of kMaxB / B samples at a time
   __shared__ int32_t sSeg[kMaxB + 1];
-  __shared__ int32_t sWave[kMaskThreads / 64];
+  __shared__ int32_t sWave[kMaskThreads / 64], sEarlier[kMaskThreads / 64];
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
+  const int g = blockIdx.x;
+  const int P = B * L;
 
-  // where this sample's rows start: after the unit's earlier samples (g > 0),
-  // or at row 0 of a new unit whose columns follow the previous unit's
-  const int row0 = (g > 0 && prev) ? prev->n_rows : 0;
-  const int col0 = prev ? (g > 0 ? prev->col_off : prev->col_end) : 0;
-
-  for (int b = tid; b < B; b += kMaskThreads)
-    sT[b] = timestep_t24(k0, k1, seq_base + (uint32_t)b, j, n_t, t_mode);
-  __syncthreads();
-
-  const int64_t P = (int64_t)B * L;
-  const int64_t chunk = (P + kMaskThreads - 1) / kMaskThreads;
-  const int64_t p0 = min(P, (int64_t)tid * chunk), p1 = min(P, p0 + chunk);
-
-  MaskWalker mw{k0, k1, seq_base, L, j};
-  int cnt = 0;
-  for (int64_t p = p0; p < p1; ++p) cnt += mw.masked(resp, sT, p) ? 1 : 0;
-
-  // block-wide exclusive scan of the per-thread counts
-  int incl = cnt;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int v = __shfl_up(incl, off, 64);
-    if (lane >= off) incl += v;
+  // counts of the unit's earlier samples, then this sample's timesteps at
+  // sT + t_base
+  int earlier = 0, t_base = 0;
+  const int per = kMaxB / B;
+  for (int q0 = 0; q0 <= g; q0 += per) {
+    const int nq = min(per, g + 1 - q0);
+    if (q0) __syncthreads();          // the previous samples' timesteps are done with
+    for (int e = tid; e < nq * B; e += kMaskThreads)
+      sT[e] = timestep_t24(k0, k1, seq_base + (uint32_t)(e % B), j0 + q0 + e / B, n_t, t_mode);
+    __syncthreads();
+    for (int q = 0; q < nq; ++q) {
+      t_base = q * B;
+      if (q0 + q == g) break;
+      MaskWalker mw{k0, k1, seq_base, L, j0 + q0 + q};
+      const int chunk = ((P + kMaskThreads - 1) / kMaskThreads + 3) & ~3;
+      const int p0 = min(P, tid * chunk), p1 = min(P, p0 + chunk);
+      earlier += __popcll(mask_run(mw, resp, sT + t_base, p0, p1, p0 / L, p0 % L));
+    }
   }
-  if (lane == 63) sWave[wave] = incl;
-  __syncthreads();
-  if (wave == 0) {
-    int wv = lane < kMaskThreads / 64 ? sWave[lane] : 0;
-    int wincl = wv;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) earlier += __shfl_xor(earlier, off, 64);
+  if (lane == 0) sEarlier[wave] = earlier;
+  // the unit's columns follow the previous unit's of the dW batch
+  const int col0 = prev ? prev->col_end : 0;
+
+  MaskWalker mw{k0, k1, seq_base, L, j0 + g};
+  int row0 = 0, total = 0;
+  for (int s0 = 0; s0 < P; s0 += kSpan) {
+    const int n = min(kSpan, P - s0);
+    const int chunk = ((n + kMaskThreads - 1) / kMaskThreads + 3) & ~3;
+    const int p0 = s0 + min(n, tid * chunk), p1 = min(s0 + n, p0 + chunk);
+    const int b0 = p0 / L;
+    const uint64_t bits = mask_run(mw, resp, sT + t_base, p0, p1, b0, p0 - b0 * L);
+    const int cnt = __popcll(bits);
+    // block-wide exclusive scan of the per-thread counts
+    int incl = cnt;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
-      const int v = __shfl_up(wincl, off, 64);
-      if (lane >= off) wincl += v;
+      const int v = __shfl_up(incl, off, 64);
+      if (lane >= off) incl += v;
     }
-    if (lane < kMaskThreads / 64) sWave[lane] = wincl - wv;  // exclusive
-  }
-  __syncthreads();
-  int base = sWave[wave] + incl - cnt;
-
-  MaskWalker mw2{k0, k1, seq_base, L, j};
-  for (int64_t p = p0; p < p1; ++p) {
-    const int b = (int)(p / L);
-    if (p == (int64_t)b * L) sSeg[b] = base;
-    if (mw2.masked(resp, sT, p)) {
-      const int r = row0 + base;
-      if (out.idx) out.idx[r] = (int32_t)p;
+    if (s0) __syncthreads();          // the previous span's wave sums are done with
+    if (lane == 63) sWave[wave] = incl;
+    __syncthreads();
+    int base = total + incl - cnt;    // masked positions of this sample before the run
+#pragma unroll
+    for (int q = 0; q < kMaskThreads / 64; ++q) {
+      const int v = sWave[q];
+      base += q < wave ? v : 0;
+      total += v;
+      row0 += s0 ? 0 : sEarlier[q];
+    }
+    // offsets of the responses that start in this thread's run
+    for (int b = (p0 + L - 1) / L; b < B && b * L < p1; ++b)
+      sSeg[b] = base + __popcll(bits & ((1ull << (b * L - p0)) - 1));
+    int b = b0, r = row0 + base;
+    for (uint64_t m = bits; m; m &= m - 1, ++r) {
+      const int p = p0 + __builtin_ctzll(m);
+      out.idx[r] = p;
       if (out.row_tgt) {
         // ids outside [0, V) are clamped so that no kernel reads outside W
         const int y = targets[p];
         out.row_tgt[r] = y < 0 ? 0 : (y >= V ? V - 1 : y);
+        while (p >= (b + 1) * L) ++b;
+        out.row_seq[r] = g * B + b;
       }
-      if (out.row_seq) out.row_seq[r] = g * B + b;
-      ++base;
     }
   }
-  if (tid == kMaskThreads - 1) sSeg[B] = base;  // the last thread ends at P
+  if (tid == 0) sSeg[B] = total;
   __syncthreads();
 
-  const int total = sSeg[B];
   const int rows = row0 + total;
-  const int rows_pad = (rows + kRowPad - 1) / kRowPad * kRowPad;
   for (int b = tid; b < B; b += kMaskThreads) {
-    const int nm = sSeg[b + 1] - sSeg[b];
-    if (nm_out) nm_out[(int64_t)b * nm_stride] = nm;
-    if (t_out) t_out[(int64_t)b * t_stride] = (float)sT[b] * (1.0f / 16777216.0f);
-    if (out.seg_off) out.seg_off[b] = row0 + sSeg[b];
-    if (out.t24) out.t24[b] = sT[b];
+    const uint32_t T = sT[t_base + b];
+    if (nm_out) nm_out[(int64_t)b * nm_stride + g] = sSeg[b + 1] - sSeg[b];
+    if (t_out) t_out[(int64_t)b * t_stride + g] = (float)T * (1.0f / 16777216.0f);
+    if (out.seg_off) out.seg_off[g * (B + 1) + b] = row0 + sSeg[b];
+    if (out.t24) out.t24[g * B + b] = T;
   }
-  if (tid == 0) {
-    if (out.seg_off) out.seg_off[B] = rows;
-    write_record(out.meta, row0, col0, total, plan);
-  }
-  // padding rows up to the next row tile (a later sample of the unit
-  // overwrites them with its own rows)
-  const int pad_end = min(rows_pad, out.row_cap);
-  for (int r = rows + tid; r < pad_end; r += kMaskThreads) {
-    if (out.row_tgt) out.row_tgt[r] = 0;
-    if (out.row_seq) out.row_seq[r] = 0;
+  if (tid == 0 && out.seg_off) out.seg_off[g * (B + 1) + B] = rows;
+  if (wave == 0) write_record(out.meta ? out.meta + g : nullptr, row0, col0, total, plan, lane);
+  // the last sample pads the unit's rows up to the next row tile
+  if (g == (int)gridDim.x - 1 && out.row_tgt) {
+    const int pad_end = min((rows + kRowPad - 1) / kRowPad * kRowPad, out.row_cap);
+    for (int r = rows + tid; r < pad_end; r += kMaskThreads) {
+      out.row_tgt[r] = 0;
+      out.row_seq[r] = 0;
+    }
   }
 }
 
@@ -254,9 +310,12 @@ __global__ __launch_bounds__(kMbThreads) void k_mask_bits(
       for (int e = 0; e < 32; ++e) r[e] = p0 + e < P ? resp[p0 + e] : 0;
     }
     MaskWalker mw{k0, k1, seq_base, L, j};
+    int b = (int)(p0 / L), i = (int)(p0 - (int64_t)b * L);
 #pragma unroll
-    for (int e = 0; e < 32; ++e)
-      if (r[e] && mw.test(t24, p0 + e)) word |= 1u << e;
+    for (int e = 0; e < 32; ++e) {
+      if (r[e] && mw.test(t24, b, i)) word |= 1u << e;
+      if (++i == L) { i = 0; ++b; }
+    }
     bits[w] = word;
   }
   int total;
@@ -305,10 +364,8 @@ __global__ __launch_bounds__(1024) void k_mask_scan(
   }
   const int rows = row0 + total;
   const int rows_pad = (rows + kRowPad - 1) / kRowPad * kRowPad;
-  if (tid == 0) {
-    if (out.seg_off) out.seg_off[B] = rows;
-    write_record(out.meta, row0, col0, total, plan);
-  }
+  if (tid == 0 && out.seg_off) out.seg_off[B] = rows;
+  if (tid < 64) write_record(out.meta, row0, col0, total, plan, tid);
   const int pad_end = min(rows_pad, out.row_cap);
   for (int r = rows + tid; r < pad_end; r += 1024) {
     if (out.row_tgt) out.row_tgt[r] = 0;
@@ -346,28 +403,28 @@ size_t mask_scratch_bytes(int B, int L) {
   return (size_t)(words * 8 + nblk * 8 + (int64_t)B * 4 + 4 * 256);
 }
 
-hipError_t launch_mask_compact(const uint8_t* resp, const int32_t* targets, int B, int L, int n_t,
-                               int j, int g, int t_mode, uint64_t seed, uint32_t seq_base,
-                               const Workspace* ws, int32_t* idx_out, int32_t* n_masked_out,
-                               int nm_stride, float* t_out, int t_stride, int V,
-                               const SampleMeta* prev, const DxPlan& plan, void* scratch,
-                               bool force_multi, hipStream_t s) {
+hipError_t launch_masks(const uint8_t* resp, const int32_t* targets, int B, int L, int n_t, int j0,
+                        int n_samples, int t_mode, uint64_t seed, uint32_t seq_base,
+                        const Workspace* ws, int32_t* idx_out, int32_t* n_masked_out,
+                        int nm_stride, float* t_out, int t_stride, int V,
+                        const SampleMeta* prev_unit, const DxPlan& plan, void* scratch,
+                        bool force_multi, hipStream_t s) {
   MaskOut out{idx_out, nullptr, nullptr, nullptr, nullptr, nullptr, 0};
   if (ws) {
     out.idx = ws->idx;
     out.row_tgt = ws->row_tgt;
     out.row_seq = ws->row_seq;
-    out.seg_off = ws->seg_off + (int64_t)g * (B + 1);
-    out.t24 = ws->t24 + (int64_t)g * B;
-    out.meta = ws->meta + g;
+    out.seg_off = ws->seg_off;
+    out.t24 = ws->t24;
+    out.meta = ws->meta;
     out.row_cap = (int)ws->RP;
   }
   const uint32_t k0 = (uint32_t)(seed & 0xFFFFFFFFu), k1 = (uint32_t)(seed >> 32);
   const int64_t P = (int64_t)B * L;
   if ((P <= kSingleBlockPositions && !force_multi) || !scratch) {
-    k_mask_compact<<<1, kMaskThreads, 0, s>>>(resp, targets, B, L, n_t, j, g, t_mode, k0, k1,
-                                              seq_base, out, n_masked_out, nm_stride, t_out,
-                                              t_stride, V, prev, plan);
+    k_mask_compact<<<n_samples, kMaskThreads, 0, s>>>(resp, targets, B, L, n_t, j0, t_mode, k0, k1,
+                                                      seq_base, out, n_masked_out, nm_stride,
+                                                      t_out, t_stride, V, prev_unit, plan);
     return hipGetLastError();
   }
   // scratch: mask words, block counts and offsets, and (without a unit) the
@@ -379,22 +436,35 @@ hipError_t launch_mask_compact(const uint8_t* resp, const int32_t* targets, int 
   int32_t* wprefix = reinterpret_cast<int32_t*>(sc + wbytes);
   int32_t* blk_count = reinterpret_cast<int32_t*>(sc + 2 * wbytes);
   int32_t* blk_off = blk_count + nblk;
-  uint32_t* t24 = out.t24 ? out.t24
-                          : reinterpret_cast<uint32_t*>(sc + 2 * wbytes +
-                                                        (nblk * 8 + 255) / 256 * 256);
-  k_timesteps<<<(unsigned)((B + 255) / 256), 256, 0, s>>>(B, n_t, j, t_mode, k0, k1, seq_base, t24,
-                                                          t_out, t_stride);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  k_mask_bits<<<(unsigned)nblk, kMbThreads, 0, s>>>(resp, t24, L, P, j, k0, k1, seq_base, bits,
-                                                    wprefix, blk_count);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  k_mask_scan<<<1, 1024, 0, s>>>(bits, wprefix, blk_count, blk_off, (int)nblk, B, L, g, out,
-                                 n_masked_out, nm_stride, prev, plan);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  k_mask_scatter<<<(unsigned)nblk, kMbThreads, 0, s>>>(bits, wprefix, blk_off, targets, B, L, P,
-                                                       g, V, out, prev);
-  return hipGetLastError();
+  uint32_t* t24_0 = out.t24 ? out.t24
+                            : reinterpret_cast<uint32_t*>(sc + 2 * wbytes +
+                                                          (nblk * 8 + 255) / 256 * 256);
+  for (int g = 0; g < n_samples; ++g) {
+    const int j = j0 + g;
+    uint32_t* t24 = out.t24 ? t24_0 + (int64_t)g * B : t24_0;
+    MaskOut og = out;   // this sample's share of the per-sample arrays
+    if (ws) {
+      og.seg_off += (int64_t)g * (B + 1);
+      og.meta += g;
+    }
+    const SampleMeta* prev = g ? ws->meta + (g - 1) : prev_unit;
+    k_timesteps<<<(unsigned)((B + 255) / 256), 256, 0, s>>>(B, n_t, j, t_mode, k0, k1, seq_base,
+                                                            t24, t_out ? t_out + g : nullptr,
+                                                            t_stride);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    k_mask_bits<<<(unsigned)nblk, kMbThreads, 0, s>>>(resp, t24, L, P, j, k0, k1, seq_base, bits,
+                                                      wprefix, blk_count);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    k_mask_scan<<<1, 1024, 0, s>>>(bits, wprefix, blk_count, blk_off, (int)nblk, B, L, g, og,
+                                   n_masked_out ? n_masked_out + g : nullptr, nm_stride, prev,
+                                   plan);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    k_mask_scatter<<<(unsigned)nblk, kMbThreads, 0, s>>>(bits, wprefix, blk_off, targets, B, L, P,
+                                                         g, V, og, prev);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // ---------------------------------------------------------------------------
