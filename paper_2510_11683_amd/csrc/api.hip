@@ -83,6 +83,7 @@ size_t workspace_layout(const Dims& dm, const Plan& pl, void* base, Workspace* w
     w.meta = static_cast<SampleMeta*>(take(2 * G * sizeof(SampleMeta)));
     w.meta2 = w.meta + (b ? G : 0);
     w.idx = static_cast<int32_t*>(take(G * P * 4));
+    w.inv = static_cast<int32_t*>(take(G * P * 4));
     w.row_tgt = static_cast<int32_t*>(take(RP * 4));
     w.row_seq = static_cast<int32_t*>(take(RP * 4));
     w.seg_off = static_cast<int32_t*>(take(G * (dm.B + 1) * 4));
@@ -106,7 +107,7 @@ size_t workspace_layout(const Dims& dm, const Plan& pl, void* base, Workspace* w
   const size_t unit_bytes = off;   // the same for every unit (all pieces 256-byte aligned)
   off = unit_bytes * n_units;
   w.dbar = static_cast<double*>(take(dm.B * 8));
-  w.gpart = static_cast<float*>(take((NP / 256) * dm.d * 4));
+  w.gpart = static_cast<float*>(take(RP / kGammaRows * dm.d * 4));
   w.HcT = static_cast<uint16_t*>(take(KT * dm.d * 2));
   w.WT = static_cast<uint16_t*>(take((size_t)dm.V * dm.d * 2));
   // the slab-major bf16 W of the dX GEMM (without it the GEMM reads the
@@ -567,15 +568,12 @@ static int unit_backward(const Workspace& ws, const Act& act, int j0, int j_begi
     }
   }
   BGPO_TRY(tm.begin(BGPO_K_DX_REDUCE));
-  for (int gs = 0; gs < ws.g_used; ++gs) {
-    const int j = j0 + gs;
-    float* dXj = dX + (int64_t)(j - j_begin) * act.stride;
-    if (act.gamma)
-      BGPO_TRY(launch_dx_reduce_rmsnorm(ws, gs, act.at(j), act.f32, act.gamma, dXj, dgamma, dm.d,
-                                        s));
-    else
-      BGPO_TRY(launch_dx_reduce(ws, gs, dXj, dm.d, s));
-  }
+  float* dXj = dX + (int64_t)(j0 - j_begin) * act.stride;
+  if (act.gamma)
+    BGPO_TRY(launch_dx_reduce_rmsnorm(ws, dm.B, act.at(j0), act.f32, act.gamma, dXj, act.stride,
+                                      dgamma, dm.d, s));
+  else
+    BGPO_TRY(launch_dx_reduce(ws, dm.B, dXj, act.stride, dm.d, s));
   BGPO_TRY(tm.end(ws.g_used * (act.gamma ? 3 : 1)));   // the norm backward is 3 kernels
   return BGPO_OK;
 }

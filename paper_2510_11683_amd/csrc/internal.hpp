@@ -60,6 +60,9 @@ struct SampleMeta {
   int32_t pad[56];
 };
 
+// Rows per partial sum of dgamma.
+constexpr int kGammaRows = 128;
+
 constexpr int kMaxDxSplit = 16;   // vocabulary splits of the dX GEMM
 
 // What the mask kernel needs to choose the dX split of a unit (the split
@@ -78,6 +81,7 @@ struct Workspace {
   SampleMeta* meta2;   // [G]          a second set: consecutive units of a dW batch alternate, since
                        //              a unit's masks read the last record of the unit before it
   int32_t* idx;        // [G*P]        masked flat positions, per sample ascending
+  int32_t* inv;        // [G*P]        unit row of each sample's positions (negative: not masked)
   int32_t* row_tgt;    // [RP]         target token of each compacted row
   int32_t* row_seq;    // [RP]         g*B + b of each row (sample g of the unit, response b)
   int32_t* seg_off;    // [G*(B+1)]    first row of each (sample, response), unit row space
@@ -101,7 +105,7 @@ struct Workspace {
   double* dbar;        // [B]          mean log-ratio over all samples (exact objective)
   float* inv_rms;      // [RP]         final-RMSNorm 1/rms of each compacted row
   void* mask_scratch;  // mask_scratch_bytes(B, L): the multi-block mask passes
-  float* gpart;        // [NP/256, d]  dgamma partial sums over 256-row chunks of a sample
+  float* gpart;        // [RP/kGammaRows, d] dgamma partial sums over chunks of a unit's rows
   uint16_t* dZ;        // stored mode: [KT rows, V] the forward's bf16 exponentials against
                        // the row's reference, i.e. s (softmax - onehot) up to the row factor
                        // (target entries rewritten), the units of a dW batch one after the
@@ -195,12 +199,14 @@ hipError_t launch_grad_scale(const Workspace& ws, int d, int V, hipStream_t s);
 // (W: the caller's bf16 W_head, read row-major when ws.Wk is NULL)
 hipError_t launch_gemm_dx(const Workspace& ws, const uint16_t* W, int d, int V, int grid,
                           hipStream_t s);
-// dX of sample g of the unit (its rows only; samples of a unit run one after
-// the other, so positions shared between samples are summed in sample order)
-hipError_t launch_dx_reduce(const Workspace& ws, int g, float* dX, int d, hipStream_t s);
-hipError_t launch_dx_reduce_rmsnorm(const Workspace& ws, int g, const void* x, bool f32,
-                                    const float* gamma, float* dx, float* dgamma, int d,
-                                    hipStream_t s);
+// dX of the unit's samples, added in sample order where they share a position
+// (stride: elements between the samples' dX and head inputs, 0 = shared; dX
+// and x those of the unit's first sample)
+hipError_t launch_dx_reduce(const Workspace& ws, int B, float* dX, int64_t stride, int d,
+                            hipStream_t s);
+hipError_t launch_dx_reduce_rmsnorm(const Workspace& ws, int B, const void* x, bool f32,
+                                    const float* gamma, float* dx, int64_t stride, float* dgamma,
+                                    int d, hipStream_t s);
 hipError_t launch_gemm_dw(const Workspace& ws, float* dW, int d, int V, int grid, hipStream_t s);
 // recompute mode, vocabulary chunk [v0, v0 + width): the chunk's logits from
 // W^T and H_c, turned into dZ = s (softmax - onehot) (bf16);

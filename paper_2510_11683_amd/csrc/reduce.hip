@@ -379,153 +379,251 @@ hipError_t launch_grad_scale(const Workspace& ws, int d, int V, hipStream_t s) {
   return hipGetLastError();
 }
 
-// dX[idx[r], :] += f_r sum_s part[s][r][:] over the rows r of one sample of
-// the unit (sm: its record; um: the unit's, which holds the split count; f_r
-// the stored backward's row factor, 1 without one), float4 per thread; rows
-// are unique within a sample, so there are no write conflicts.
-__global__ __launch_bounds__(256) void k_dx_reduce(const float* __restrict__ part,
-                                                   const int32_t* __restrict__ idx,
-                                                   const SampleMeta* __restrict__ sm,
+// The rows of a unit that add into one dX row, in sample order.  Shared head
+// input (SHARED): target t is position t, whose row in sample g is
+// inv[g P + t] (negative: not masked there); the samples' rows are added one
+// after the other, as if each sample were reduced alone.  Per-sample head
+// inputs: target t is unit row t, alone, at its sample's own dX; with a stride
+// below B L d the samples' dX overlap, and they run one after the other
+// (`only`: the sample of this launch, else -1).
+struct DxTarget {
+  const int32_t* inv;       // [G, P]
+  const int32_t* idx;       // [RP]  position of a unit row
+  const int32_t* row_seq;   // [RP]  g*B + b of a unit row
+  int n_samples, B, only;
+  int64_t P, stride, d;
+  // element offset of the target's dX row (and head input row)
+  template <bool SHARED>
+  __device__ int64_t offset(int t) const {
+    return SHARED ? (int64_t)t * d : (int64_t)(row_seq[t] / B) * stride + (int64_t)idx[t] * d;
+  }
+  template <bool SHARED>
+  __device__ bool none(int t, const SampleMeta* um) const {
+    return !SHARED && (t >= um->n_rows || (only >= 0 && row_seq[t] / B != only));
+  }
+  template <bool SHARED>
+  __device__ int row(int g, int t) const {
+    return SHARED ? inv[(int64_t)g * P + t] : t;
+  }
+};
+
+// sum_s part[s][r][c .. c + 3], splits in order
+__device__ __forceinline__ float4 split_sum(const float* __restrict__ part, int n_split,
+                                            int64_t split_stride) {
+  float4 acc = *reinterpret_cast<const float4*>(part);
+#pragma unroll 4
+  for (int s = 1; s < n_split; ++s) {
+    const float4 v = *reinterpret_cast<const float4*>(part + s * split_stride);
+    acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+  }
+  return acc;
+}
+
+// dX[t, :] += f_r sum_s part[s][r][:] over the rows r of target t (f_r the
+// stored backward's row factor, 1 without one), float4 per thread.  One launch
+// per unit: bound by HBM, the partials are read once and a dX row is read and
+// written once per unit instead of once per sample (B8 L512 d4096, a unit of 8
+// samples with 15.2k rows in 4 splits: 191 us in one launch per sample -> 132).
+template <bool SHARED>
+__global__ __launch_bounds__(256) void k_dx_reduce(const float* __restrict__ part, DxTarget tg,
                                                    const SampleMeta* __restrict__ um,
                                                    const float* __restrict__ rowf,
                                                    float* __restrict__ dX, int d,
                                                    int64_t split_stride) {
-  if ((int)blockIdx.x >= sm->s_rows) return;
-  const int r = sm->s_row_off + blockIdx.x;
-  const int n_split = um->dx_split;
+  const int t = blockIdx.x;
+  if (tg.none<SHARED>(t, um)) return;
   const int c = (blockIdx.y * 256 + threadIdx.x) * 4;
   if (c >= d) return;
-  float4 acc = *reinterpret_cast<const float4*>(part + (int64_t)r * d + c);
-  for (int s = 1; s < n_split; ++s) {
-    const float4 v = *reinterpret_cast<const float4*>(part + s * split_stride + (int64_t)r * d + c);
-    acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+  const int n_split = um->dx_split;
+  float4* dst = reinterpret_cast<float4*>(dX + tg.offset<SHARED>(t) + c);
+  float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+  bool any = false;
+  const int n = SHARED ? tg.n_samples : 1;
+  for (int g = 0; g < n; ++g) {
+    const int r = tg.row<SHARED>(g, t);
+    if (r < 0) continue;
+    float4 acc = split_sum(part + (int64_t)r * d + c, n_split, split_stride);
+    if (rowf) {
+      const float f = rowf[r];
+      acc.x *= f; acc.y *= f; acc.z *= f; acc.w *= f;
+    }
+    if (!any) o = *dst;
+    any = true;
+    o.x += acc.x; o.y += acc.y; o.z += acc.z; o.w += acc.w;
   }
-  if (rowf) {
-    const float f = rowf[r];
-    acc.x *= f; acc.y *= f; acc.z *= f; acc.w *= f;
-  }
-  float4* dst = reinterpret_cast<float4*>(dX + (int64_t)idx[r] * d + c);
-  float4 o = *dst;
-  o.x += acc.x; o.y += acc.y; o.z += acc.z; o.w += acc.w;
-  *dst = o;
+  if (any) *dst = o;
 }
 
-hipError_t launch_dx_reduce(const Workspace& ws, int g, float* dX, int d, hipStream_t s) {
-  dim3 grid((unsigned)ws.NP, (unsigned)((d / 4 + 255) / 256));
-  k_dx_reduce<<<grid, 256, 0, s>>>(ws.dx_part, ws.idx, ws.meta + g, ws.unit(),
-                                   ws.chunk ? nullptr : ws.row_f, dX, d, ws.RP * d);
+static DxTarget dx_target(const Workspace& ws, int B, int d, int64_t stride) {
+  return DxTarget{ws.inv, ws.idx, ws.row_seq, ws.g_used, B, -1, ws.P, stride, d};
+}
+
+// launches `run` once for the unit, or once per sample where the samples' dX
+// overlap
+template <typename F>
+static void for_disjoint(DxTarget tg, F run) {
+  if (tg.stride == 0 || tg.stride >= tg.P * tg.d) {
+    run(tg);
+  } else {
+    for (tg.only = 0; tg.only < tg.n_samples; ++tg.only) run(tg);
+  }
+}
+
+hipError_t launch_dx_reduce(const Workspace& ws, int B, float* dX, int64_t stride, int d,
+                            hipStream_t s) {
+  const float* rowf = ws.chunk ? nullptr : ws.row_f;
+  const unsigned cols = (unsigned)((d / 4 + 255) / 256);
+  for_disjoint(dx_target(ws, B, d, stride), [&](const DxTarget& tg) {
+    if (stride == 0)
+      k_dx_reduce<true><<<dim3((unsigned)ws.P, cols), 256, 0, s>>>(ws.dx_part, tg, ws.unit(), rowf,
+                                                                   dX, d, ws.RP * d);
+    else
+      k_dx_reduce<false><<<dim3((unsigned)(ws.g_used * ws.NP), cols), 256, 0, s>>>(
+          ws.dx_part, tg, ws.unit(), rowf, dX, d, ws.RP * d);
+  });
   return hipGetLastError();
 }
 
 // Split reduction followed by the backward of the final RMSNorm
-// h = gamma x r, r = (mean x^2 + eps)^(-1/2), for one row of one sample of the
-// unit per workgroup (x: that sample's activations):
+// h = gamma x r, r = (mean x^2 + eps)^(-1/2), one target (see DxTarget) per
+// workgroup:
 //   dh       = f_row sum_s part[s][row]               (d loss / d h; f_row the
 //                                                     stored backward's row
 //                                                     factor, 1 without one)
 //   dx_k    += r gamma_k dh_k - (r^3 / d) x_k sum_i gamma_i dh_i x_i
 //   c_k      = dh_k x_k r  -> part[0][row][k], summed over rows into dgamma
-// Every thread revisits only the elements it wrote, so part[0] needs no
+// Every thread revisits only the elements it wrote, so part[0] and dx need no
 // cross-thread ordering; the row dot product goes through LDS.
-template <typename T>
+template <typename T, bool SHARED>
 __global__ __launch_bounds__(256) void k_dx_reduce_rmsnorm(
-    float* __restrict__ part, const int32_t* __restrict__ idx, const SampleMeta* __restrict__ sm,
-    const SampleMeta* __restrict__ um, const float* __restrict__ rowf, const T* __restrict__ x,
-    const float* __restrict__ gamma, const float* __restrict__ inv_rms, float* __restrict__ dx,
-    int d, int64_t split_stride) {
-  __shared__ float red[4];
-  if ((int)blockIdx.x >= sm->s_rows) return;
-  const int r = sm->s_row_off + blockIdx.x;
+    float* __restrict__ part, DxTarget tg, const SampleMeta* __restrict__ um,
+    const float* __restrict__ rowf, const T* __restrict__ x, const float* __restrict__ gamma,
+    const float* __restrict__ inv_rms, float* __restrict__ dx, int d, int64_t split_stride) {
+  __shared__ float red[2][4];
+  const int t = blockIdx.x;
+  if (tg.none<SHARED>(t, um)) return;
   const int n_split = um->dx_split;
   const int tid = threadIdx.x;
-  const float f = rowf ? rowf[r] : 1.f;   // the stored backward's row factor
-  float* p0 = part + (int64_t)r * d;
-  const T* xr = x + (int64_t)idx[r] * d;
-  float dot = 0.f;
-  for (int c = tid * 4; c < d; c += 1024) {
-    float4 acc = *reinterpret_cast<const float4*>(p0 + c);
-    for (int sp = 1; sp < n_split; ++sp) {
-      const float4 v = *reinterpret_cast<const float4*>(p0 + sp * split_stride + c);
+  const int64_t off = tg.offset<SHARED>(t);
+  const T* xr = x + off;
+  float* dxr = dx + off;
+  const int n = SHARED ? tg.n_samples : 1;
+  int set = 0;
+  for (int g = 0; g < n; ++g) {
+    const int r = tg.row<SHARED>(g, t);
+    if (r < 0) continue;                    // the same for the whole workgroup
+    const float f = rowf ? rowf[r] : 1.f;   // the stored backward's row factor
+    float* p0 = part + (int64_t)r * d;
+    float dot = 0.f;
+    for (int c = tid * 4; c < d; c += 1024) {
+      float4 acc = split_sum(p0 + c, n_split, split_stride);
+      acc.x *= f; acc.y *= f; acc.z *= f; acc.w *= f;
+      *reinterpret_cast<float4*>(p0 + c) = acc;
+      const uint2 xv = load_bf16x4(xr + c);
+      const float4 gm = *reinterpret_cast<const float4*>(gamma + c);
+      dot = fmaf(gm.x * acc.x, __uint_as_float(xv.x << 16), dot);
+      dot = fmaf(gm.y * acc.y, __uint_as_float(xv.x & 0xFFFF0000u), dot);
+      dot = fmaf(gm.z * acc.z, __uint_as_float(xv.y << 16), dot);
+      dot = fmaf(gm.w * acc.w, __uint_as_float(xv.y & 0xFFFF0000u), dot);
+    }
+#pragma unroll
+    for (int off2 = 32; off2 > 0; off2 >>= 1) dot += __shfl_xor(dot, off2, 64);
+    set ^= 1;   // two sets: a set is rewritten one barrier after its last read
+    if ((tid & 63) == 0) red[set][tid >> 6] = dot;
+    __syncthreads();
+    dot = red[set][0] + red[set][1] + red[set][2] + red[set][3];
+    const float ir = inv_rms[r];
+    const float cx = ir * ir * ir * dot / (float)d;
+    for (int c = tid * 4; c < d; c += 1024) {
+      const float4 dh = *reinterpret_cast<const float4*>(p0 + c);
+      const uint2 xv = load_bf16x4(xr + c);
+      const float4 gm = *reinterpret_cast<const float4*>(gamma + c);
+      const float x0 = __uint_as_float(xv.x << 16), x1 = __uint_as_float(xv.x & 0xFFFF0000u);
+      const float x2 = __uint_as_float(xv.y << 16), x3 = __uint_as_float(xv.y & 0xFFFF0000u);
+      float4 o = *reinterpret_cast<float4*>(dxr + c);
+      o.x += ir * gm.x * dh.x - cx * x0;
+      o.y += ir * gm.y * dh.y - cx * x1;
+      o.z += ir * gm.z * dh.z - cx * x2;
+      o.w += ir * gm.w * dh.w - cx * x3;
+      *reinterpret_cast<float4*>(dxr + c) = o;
+      *reinterpret_cast<float4*>(p0 + c) =
+          make_float4(dh.x * x0 * ir, dh.y * x1 * ir, dh.z * x2 * ir, dh.w * x3 * ir);
+    }
+  }
+}
+
+// dgamma[k] += sum over the unit's rows of part[0][row][k], in a fixed order:
+// partial sums over chunks of kGammaRows rows (four groups of rows per
+// workgroup, 256 columns), then the chunks in order.  Bound by HBM in the
+// first pass (2.4k rows of 4096: 82 us with one column per thread and chunks
+// of 256 rows -> 13 us for the two).
+__global__ __launch_bounds__(256) void k_dgamma_partial(const float* __restrict__ part,
+                                                        const SampleMeta* __restrict__ um,
+                                                        float* __restrict__ gpart, int d) {
+  __shared__ float4 red[3][64];
+  const int n_rows = um->n_rows;
+  const int r0 = blockIdx.y * kGammaRows;
+  if (r0 >= n_rows) return;
+  const int q = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int k = blockIdx.x * 256 + lane * 4;
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (k < d) {
+    const int ra = r0 + q * (kGammaRows / 4), rb = min(n_rows, ra + kGammaRows / 4);
+#pragma unroll 8
+    for (int r = ra; r < rb; ++r) {
+      const float4 v = *reinterpret_cast<const float4*>(part + (int64_t)r * d + k);
       acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
     }
-    acc.x *= f; acc.y *= f; acc.z *= f; acc.w *= f;
-    *reinterpret_cast<float4*>(p0 + c) = acc;
-    const uint2 xv = load_bf16x4(xr + c);
-    const float4 g = *reinterpret_cast<const float4*>(gamma + c);
-    dot = fmaf(g.x * acc.x, __uint_as_float(xv.x << 16), dot);
-    dot = fmaf(g.y * acc.y, __uint_as_float(xv.x & 0xFFFF0000u), dot);
-    dot = fmaf(g.z * acc.z, __uint_as_float(xv.y << 16), dot);
-    dot = fmaf(g.w * acc.w, __uint_as_float(xv.y & 0xFFFF0000u), dot);
   }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) dot += __shfl_xor(dot, off, 64);
-  if ((tid & 63) == 0) red[tid >> 6] = dot;
+  if (q) red[q - 1][lane] = acc;
   __syncthreads();
-  dot = red[0] + red[1] + red[2] + red[3];
-  const float ir = inv_rms[r];
-  const float cx = ir * ir * ir * dot / (float)d;
-  float* dxr = dx + (int64_t)idx[r] * d;
-  for (int c = tid * 4; c < d; c += 1024) {
-    const float4 dh = *reinterpret_cast<const float4*>(p0 + c);
-    const uint2 xv = load_bf16x4(xr + c);
-    const float4 g = *reinterpret_cast<const float4*>(gamma + c);
-    const float x0 = __uint_as_float(xv.x << 16), x1 = __uint_as_float(xv.x & 0xFFFF0000u);
-    const float x2 = __uint_as_float(xv.y << 16), x3 = __uint_as_float(xv.y & 0xFFFF0000u);
-    float4 o = *reinterpret_cast<float4*>(dxr + c);
-    o.x += ir * g.x * dh.x - cx * x0;
-    o.y += ir * g.y * dh.y - cx * x1;
-    o.z += ir * g.z * dh.z - cx * x2;
-    o.w += ir * g.w * dh.w - cx * x3;
-    *reinterpret_cast<float4*>(dxr + c) = o;
-    *reinterpret_cast<float4*>(p0 + c) = make_float4(dh.x * x0 * ir, dh.y * x1 * ir, dh.z * x2 * ir, dh.w * x3 * ir);
+  if (q || k >= d) return;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const float4 v = red[i][lane];
+    acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
   }
+  *reinterpret_cast<float4*>(gpart + (int64_t)blockIdx.y * d + k) = acc;
 }
 
-// dgamma[k] += sum over one sample's rows of part[0][row][k], in a fixed
-// order: partial sums over 256-row chunks of the sample, then the chunks in
-// order.
-__global__ __launch_bounds__(256) void k_dgamma_partial(const float* __restrict__ part,
-                                                        const SampleMeta* __restrict__ sm,
-                                                        float* __restrict__ gpart, int d) {
-  const int k = blockIdx.x * 256 + threadIdx.x;
-  const int r0 = blockIdx.y * 256;
+__global__ __launch_bounds__(64) void k_dgamma_final(const float* __restrict__ gpart,
+                                                     const SampleMeta* __restrict__ um,
+                                                     float* __restrict__ dgamma, int d) {
+  const int k = blockIdx.x * 64 + threadIdx.x;
   if (k >= d) return;
-  const int r1 = min(sm->s_rows, r0 + 256);
-  const float* base = part + (int64_t)sm->s_row_off * d;
+  const int chunks = (um->n_rows + kGammaRows - 1) / kGammaRows;
   float acc = 0.f;
-  for (int r = r0; r < r1; ++r) acc += base[(int64_t)r * d + k];
-  gpart[(int64_t)blockIdx.y * d + k] = acc;
-}
-
-__global__ __launch_bounds__(256) void k_dgamma_final(const float* __restrict__ gpart,
-                                                      const SampleMeta* __restrict__ sm,
-                                                      float* __restrict__ dgamma, int d) {
-  const int k = blockIdx.x * 256 + threadIdx.x;
-  if (k >= d) return;
-  const int chunks = (sm->s_rows + 255) / 256;
-  float acc = 0.f;
+#pragma unroll 16
   for (int c = 0; c < chunks; ++c) acc += gpart[(int64_t)c * d + k];
   dgamma[k] += acc;
 }
 
-hipError_t launch_dx_reduce_rmsnorm(const Workspace& ws, int g, const void* x, bool f32,
-                                    const float* gamma, float* dx, float* dgamma, int d,
-                                    hipStream_t s) {
-  const SampleMeta* sm = ws.meta + g;
+template <typename T, bool SHARED>
+static void dx_reduce_rmsnorm(const Workspace& ws, int B, const void* x, const float* gamma,
+                              float* dx, int64_t stride, int d, hipStream_t s) {
+  for_disjoint(dx_target(ws, B, d, stride), [&](const DxTarget& tg) {
+    k_dx_reduce_rmsnorm<T, SHARED><<<(unsigned)(SHARED ? ws.P : ws.g_used * ws.NP), 256, 0, s>>>(
+        ws.dx_part, tg, ws.unit(), ws.chunk ? nullptr : ws.row_f, static_cast<const T*>(x), gamma,
+        ws.inv_rms, dx, d, ws.RP * d);
+  });
+}
+
+hipError_t launch_dx_reduce_rmsnorm(const Workspace& ws, int B, const void* x, bool f32,
+                                    const float* gamma, float* dx, int64_t stride, float* dgamma,
+                                    int d, hipStream_t s) {
   if (f32)
-    k_dx_reduce_rmsnorm<float><<<(unsigned)ws.NP, 256, 0, s>>>(
-        ws.dx_part, ws.idx, sm, ws.unit(), ws.chunk ? nullptr : ws.row_f,
-        static_cast<const float*>(x), gamma, ws.inv_rms, dx, d, ws.RP * d);
+    (stride ? dx_reduce_rmsnorm<float, false>
+            : dx_reduce_rmsnorm<float, true>)(ws, B, x, gamma, dx, stride, d, s);
   else
-    k_dx_reduce_rmsnorm<uint16_t><<<(unsigned)ws.NP, 256, 0, s>>>(
-        ws.dx_part, ws.idx, sm, ws.unit(), ws.chunk ? nullptr : ws.row_f,
-        static_cast<const uint16_t*>(x), gamma, ws.inv_rms, dx, d, ws.RP * d);
+    (stride ? dx_reduce_rmsnorm<uint16_t, false>
+            : dx_reduce_rmsnorm<uint16_t, true>)(ws, B, x, gamma, dx, stride, d, s);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  dim3 g1((unsigned)((d + 255) / 256), (unsigned)(ws.NP / 256));
-  k_dgamma_partial<<<g1, 256, 0, s>>>(ws.dx_part, sm, ws.gpart, d);
+  const dim3 g1((unsigned)((d + 255) / 256),
+                (unsigned)((ws.g_used * ws.NP + kGammaRows - 1) / kGammaRows));
+  k_dgamma_partial<<<g1, 256, 0, s>>>(ws.dx_part, ws.unit(), ws.gpart, d);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  k_dgamma_final<<<(unsigned)((d + 255) / 256), 256, 0, s>>>(ws.gpart, sm, dgamma, d);
+  k_dgamma_final<<<(unsigned)((d + 63) / 64), 64, 0, s>>>(ws.gpart, ws.unit(), dgamma, d);
   return hipGetLastError();
 }
 

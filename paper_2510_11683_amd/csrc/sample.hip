@@ -71,6 +71,7 @@ __device__ void choose_dx_split(int row_tiles, const DxPlan& pl, int lane, int* 
 // for the mask-only entry point, which writes positions to idx at row 0).
 struct MaskOut {
   int32_t* idx;          // [rows]  masked flat positions, indexed by unit row
+  int32_t* inv;          // [G, P]  every position's unit row (negative: not masked)
   int32_t* row_tgt;      // [rows]  target token
   int32_t* row_seq;      // [rows]  g*B + b
   int32_t* seg_off;      // [G, B+1] every sample's response offsets (unit rows)
@@ -211,6 +212,11 @@ __global__ __launch_bounds__(kMaskThreads) void k_mask_compact(
     // offsets of the responses that start in this thread's run
     for (int b = (p0 + L - 1) / L; b < B && b * L < p1; ++b)
       sSeg[b] = base + __popcll(bits & ((1ull << (b * L - p0)) - 1));
+    if (out.inv) {
+      int32_t* const inv = out.inv + (int64_t)g * P;
+      int r = row0 + base;
+      for (int p = p0; p < p1; ++p) inv[p] = (bits >> (p - p0)) & 1 ? r++ : -1;
+    }
     int b = b0, r = row0 + base;
     for (uint64_t m = bits; m; m &= m - 1, ++r) {
       const int p = p0 + __builtin_ctzll(m);
@@ -382,6 +388,11 @@ __global__ __launch_bounds__(kMbThreads) void k_mask_scatter(
   const uint32_t word = bits[w];
   const int row0 = (g > 0 && prev) ? prev->n_rows : 0;
   int r = row0 + blk_off[blockIdx.x] + wprefix[w];
+  if (out.inv) {
+    int32_t* const inv = out.inv + (int64_t)g * P + w * 32;
+    int q = r;
+    for (int e = 0; e < 32 && w * 32 + e < P; ++e) inv[e] = (word >> e) & 1 ? q++ : -1;
+  }
   uint32_t m = word;
   while (m) {
     const int e = __builtin_ctz(m);
@@ -409,9 +420,10 @@ hipError_t launch_masks(const uint8_t* resp, const int32_t* targets, int B, int 
                         int nm_stride, float* t_out, int t_stride, int V,
                         const SampleMeta* prev_unit, const DxPlan& plan, void* scratch,
                         bool force_multi, hipStream_t s) {
-  MaskOut out{idx_out, nullptr, nullptr, nullptr, nullptr, nullptr, 0};
+  MaskOut out{idx_out, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0};
   if (ws) {
     out.idx = ws->idx;
+    out.inv = ws->inv;
     out.row_tgt = ws->row_tgt;
     out.row_seq = ws->row_seq;
     out.seg_off = ws->seg_off;

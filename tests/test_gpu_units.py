@@ -65,3 +65,47 @@ def test_masks_of_a_misaligned_response_mask(offset):
     want = elbo.sample_masks(p, resp, 2)[3]
     np.testing.assert_array_equal(idx[:want.size].cpu().numpy(), want)
     assert int(nm.sum()) == want.size
+
+
+@pytest.mark.parametrize("norm", [False, True])
+@pytest.mark.parametrize("stride_rows", [7, 21, 30])
+def test_overlapping_sample_strides(stride_rows, norm):
+    """Sample strides below B*L*d (21 rows), where consecutive samples' head
+    inputs and dX share rows, and above: one call over a range gives the sum
+    of one call per sample at that sample's offset (reassociation of fp32
+    sums only: 1e-5)."""
+    b = lib()
+    B, L, d, V, n_t = 3, 7, 1088, 192, 10
+    stride = stride_rows * d
+    rng = np.random.default_rng(5)
+    rows = (n_t - 1) * stride_rows + B * L
+    x = torch.from_numpy(rng.standard_normal((rows, d), dtype=np.float32)).to(torch.bfloat16).cuda()
+    W = torch.from_numpy(0.05 * rng.standard_normal((d, V), dtype=np.float32)).to(torch.bfloat16).cuda()
+    gamma = torch.from_numpy((1 + 0.1 * rng.standard_normal(d)).astype(np.float32)).cuda()
+    y = torch.from_numpy(rng.integers(0, V, (B, L)).astype(np.int32)).cuda()
+    resp = torch.ones(B, L, dtype=torch.uint8, device="cuda")
+    adv = torch.from_numpy(rng.standard_normal(B).astype(np.float32)).cuda()
+
+    def run(ranges):
+        dX = torch.zeros(rows, d, device="cuda")
+        dW, dg = torch.zeros(d, V, device="cuda"), torch.zeros(d, device="cuda")
+        ell = torch.zeros(B, n_t, dtype=torch.float64, device="cuda")
+        g, loss = torch.zeros_like(ell), torch.zeros(1, dtype=torch.float64, device="cuda")
+        nm = torch.zeros(B, n_t, dtype=torch.int32, device="cuda")
+        for j0, n in ranges:
+            p = b.Problem(B, L, d, V, n_t, j_begin=j0, j_count=n, seed=41, sample_stride=stride)
+            ws = b.alloc_workspace(p)
+            xj, dj = x[j0 * stride_rows:].data_ptr(), dX[j0 * stride_rows:].data_ptr()
+            tail = [W, y, resp, adv]
+            out = [ell, g, loss, nm]
+            a = [t.data_ptr() for t in tail] + [None, 0.125, dj] + ([dg.data_ptr()] if norm else []) + \
+                [dW.data_ptr()] + [t.data_ptr() for t in out] + [None, None, ws.data_ptr(), ws.numel(), None, None]
+            f = b._lib.bgpo_elbo_bwd_accumulate_rmsnorm if norm else b._lib.bgpo_elbo_bwd_accumulate
+            head = [xj] + ([gamma.data_ptr()] if norm else [])
+            torch.cuda.synchronize()
+            assert f(p.c(), *head, *a) == 0
+            torch.cuda.synchronize()
+        return [t.cpu().numpy() for t in (dX, dW, dg, ell)]
+
+    for one, many in zip(run([(0, n_t)]), run([(j, 1) for j in range(n_t)])):
+        assert rel_maxnorm(one, many) <= 1e-5
