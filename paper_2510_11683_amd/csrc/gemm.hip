@@ -493,6 +493,8 @@ __global__ __launch_bounds__(256, 1) void k_gemm4w(GemmParams p) {
       // drain the ring (outstanding re-loads) before the epilogue may reuse LDS
       __builtin_amdgcn_s_waitcnt(0);
       __builtin_amdgcn_s_barrier();
+    } else if (preload) {
+      wait_vmcnt<0>();   // an empty K slice stores the values it loaded
     }
     asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7");   // the last MFMAs' results land
 

@@ -109,3 +109,22 @@ def test_overlapping_sample_strides(stride_rows, norm):
 
     for one, many in zip(run([(0, n_t)]), run([(j, 1) for j in range(n_t)])):
         assert rel_maxnorm(one, many) <= 1e-5
+
+
+@pytest.mark.parametrize("d", [128, 256, 576])
+def test_empty_splits_of_the_last_vocabulary_chunk(d):
+    """Recompute backward whose last vocabulary chunk (64 ids, one slab) leaves
+    splits of the dX GEMM empty: their partials keep the earlier chunks' sums.
+    Against the oracle, and l bit-identical to the stored backward."""
+    w = workloads.Workload("empty", B=4, L=150, d=d, V=2048 + 64, n_t=3, adv="normal", group=4,
+                           data_seed=2300 + d, philox_seed=0xB6B50000 + d)
+    x = workloads.generate(w)
+    ref = elbo.elbo_collapsed(elbo.Problem(4, 150, d, w.V, 3, seed=w.philox_seed), x["hidden"], x["W"],
+                              x["targets"], x["resp_mask"], x["adv"])
+    r, q = Runner(w, x, vocab_chunk=1024), Runner(w, x)
+    r.bwd()
+    q.bwd()
+    o = r.out()
+    assert np.array_equal(o["ell"], q.out()["ell"])
+    assert rel_maxnorm(o["dX"], ref.dX) <= 2e-2
+    assert rel_maxnorm(o["dW"], ref.dW) <= 2e-2
