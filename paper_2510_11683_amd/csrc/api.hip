@@ -389,12 +389,6 @@ static Dims dims_of(const bgpo_problem* p) { return Dims{p->B, p->L, p->d, p->V,
     if ((expr) != hipSuccess) return BGPO_ERR_HIP; \
   } while (0)
 
-// the dX GEMM's K: the whole vocabulary, or one chunk of it in the recompute mode
-static DxPlan dx_plan(const Dims& dm, const Workspace& ws, int grid) {
-  const int k = ws.chunk ? (int)std::min<int64_t>(ws.chunk, dm.V) : dm.V;
-  return DxPlan{k / 64, (dm.d + 255) / 256, grid, (int)ws.n_split};
-}
-
 // The head input of the samples of a call: sample j reads x + (j - j_begin) *
 // stride elements (stride 0: one tensor shared by all samples; bf16 or, with
 // f32, fp32 elements), normalised by the final RMSNorm when gamma is given.
@@ -427,7 +421,7 @@ static int run_forward_unit(const bgpo_problem* p, Workspace& ws, Timer& tm, int
   BGPO_TRY(launch_masks(resp, targets, dm.B, dm.L, dm.n_t, j0, n_s, p->t_mode, p->seed,
                         p->seq_id_base, &ws, nullptr, n_masked + j0, dm.n_t,
                         t_out ? t_out + j0 : nullptr, dm.n_t, dm.V, prev_unit,
-                        dx_plan(dm, ws, grid), ws.mask_scratch, false, s));
+                        dx_plan(ws, dm.d, dm.V, grid), ws.mask_scratch, false, s));
   BGPO_TRY(tm.end(n_s));
   BGPO_TRY(tm.begin(BGPO_K_GATHER));
   if (act.gamma)
@@ -508,7 +502,7 @@ int bgpo_sample_masks(const bgpo_problem* prob, const uint8_t* resp_mask, int32_
   if (!resp_mask || !idx || !n_masked || j < 0 || j >= prob->n_t) return BGPO_ERR_INVALID_ARG;
   if (launch_masks(resp_mask, nullptr, prob->B, prob->L, prob->n_t, j, 1, prob->t_mode, prob->seed,
                    prob->seq_id_base, nullptr, idx, n_masked, 1, t_out, 1, prob->V, nullptr,
-                   DxPlan{1, 1, 1, 1}, nullptr, false, (hipStream_t)stream) != hipSuccess)
+                   DxPlan{1, 1, 1, 1, 256, 13}, nullptr, false, (hipStream_t)stream) != hipSuccess)
     return BGPO_ERR_HIP;
   return BGPO_OK;
 }
@@ -882,7 +876,7 @@ extern "C" int bgpo_test_mask_multiblock(const bgpo_problem* prob, const uint8_t
     return BGPO_ERR_WORKSPACE;
   if (launch_masks(resp_mask, nullptr, prob->B, prob->L, prob->n_t, j, 1, prob->t_mode, prob->seed,
                    prob->seq_id_base, nullptr, idx, n_masked, 1, t_out, 1, prob->V, nullptr,
-                   DxPlan{1, 1, 1, 1}, scratch, true, (hipStream_t)stream) != hipSuccess)
+                   DxPlan{1, 1, 1, 1, 256, 13}, scratch, true, (hipStream_t)stream) != hipSuccess)
     return BGPO_ERR_HIP;
   return BGPO_OK;
 }

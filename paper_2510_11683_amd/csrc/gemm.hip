@@ -40,6 +40,8 @@
 
 #include <string.h>
 
+#include <algorithm>
+
 namespace bgpo {
 
 enum EpiKind { EPI_FWD = 0, EPI_FWDU = 1, EPI_F32_STORE = 2, EPI_F32_ACCUM = 3, EPI_DZ = 4 };
@@ -135,23 +137,24 @@ __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
-// A per-row value for each of a lane's 8 accumulator rows, row
-// nw + 16 j + (lane % 16) for j = 0 .. 7: the wave's 128 rows in two
-// coalesced loads (lane l takes rows nw + l and nw + 64 + l, f of the loaded
-// value, or `fill` at rows not below n_valid), then lane shuffles.  With one
+// A per-row value for each of a lane's TN accumulator rows, row
+// nw + 16 j + (lane % 16) for j = 0 .. TN - 1: the wave's 128 (or 32) rows in
+// two (one) coalesced loads (lane l takes rows nw + l and nw + 64 + l, f of the
+// loaded value, or `fill` at rows not below n_valid), then lane shuffles.  With one
 // load per row the compiler issued and waited for the eight loads one after
 // the other, and where a row's value was first used inside a conditional
 // block it waited again there for every outstanding store.  (Clamped
 // unconditional loads, to have both in flight under one wait, changed the
 // register allocation: spill reloads then waited inside the column loop.)
-template <typename T, typename F>
+template <int TN, typename T, typename F>
 __device__ __forceinline__ void rows_of_lane(const T* src, int nw, int n_valid, int lane, T fill,
-                                             F f, T (&out)[8]) {
-  const int na = nw + lane, nb = nw + 64 + lane;
+                                             F f, T (&out)[TN]) {
+  static_assert(TN == 8 || TN == 2, "128 or 32 rows per wave");
+  const int na = nw + (TN == 8 ? lane : lane & 31), nb = nw + 64 + lane;
   const T a = na < n_valid ? f(src[na]) : fill;
-  const T b = nb < n_valid ? f(src[nb]) : fill;
+  const T b = TN == 8 && nb < n_valid ? f(src[nb]) : fill;
 #pragma unroll
-  for (int j = 0; j < 8; ++j) out[j] = __shfl(j < 4 ? a : b, 16 * (j & 3) + (lane & 15), 64);
+  for (int j = 0; j < TN; ++j) out[j] = __shfl(j < 4 ? a : b, 16 * (j & 3) + (lane & 15), 64);
 }
 
 // One 16-byte bf16 store per lane for two vertically adjacent 16x16 blocks
@@ -225,10 +228,10 @@ __device__ __forceinline__ void epi_f32_16t(const f32x4 (&acc)[TM][TN], float* o
   }
 }
 
-template <int EPI, int AL, int BM, int BN, int BK, int STAGES>
+template <int EPI, int AL, int BM, int BN, int BK, int STAGES, int WN>
 __global__ __launch_bounds__(256, 1) void k_gemm4w(GemmParams p) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass needs only the signature
-  constexpr int WM = 128, WN = 128;
+  constexpr int WM = 128;
   using C = Cfg<BM, BN, BK, WM, WN>;
   constexpr int NT = C::NT, KCH = C::KCH;
   constexpr int TM = WM / 16, TN = WN / 16;
@@ -237,7 +240,9 @@ __global__ __launch_bounds__(256, 1) void k_gemm4w(GemmParams p) {
   // A is row-major (W^T, W) or M-slab-major (dZ, with transposing fragment
   // reads); B is always K-slab-major
   constexpr bool kMSlabA = AL == A_MSLAB, kKSlabA = AL == A_KSLAB;
-  static_assert(!kMSlabA || BM / 64 == C::NWAVES, "one 64-row M slab of A per wave");
+  // waves that share the load of one 64-wide M slab of A
+  constexpr int WPS = C::NWAVES / (BM / 64);
+  static_assert(!kMSlabA || WPS * (BM / 64) == C::NWAVES, "whole waves per M slab of A");
   __shared__ uint4 smem[STAGES * (BM + BN) * KCH];
   uint4* As = smem;                           // [STAGES][BM][KCH]
   uint4* Bs = smem + STAGES * BM * KCH;       // [STAGES][BN][KCH]
@@ -248,7 +253,10 @@ __global__ __launch_bounds__(256, 1) void k_gemm4w(GemmParams p) {
 
   int M = p.M, N = p.N, K = p.K, n_valid = p.N;
   if (p.dyn_m) { M = p.meta->n_rows_pad; n_valid = p.meta->n_rows; }
-  if (p.dyn_n) { N = p.meta->n_rows_pad; n_valid = p.meta->n_rows; }
+  if (p.dyn_n) {
+    n_valid = p.meta->n_rows;
+    N = BN < kRowPad ? (n_valid + BN - 1) / BN * BN : p.meta->n_rows_pad;
+  }
   if (p.dyn_k) K = p.meta->col_end;    // batched dW: all samples' columns (multiple of 64)
   // first row of the unit in dZ (EPI_FWDU), read once into a scalar register
   const int zt_col = EPI == EPI_FWDU ? __builtin_amdgcn_readfirstlane(p.meta->col_off) : 0;
@@ -348,17 +356,17 @@ __global__ __launch_bounds__(256, 1) void k_gemm4w(GemmParams p) {
         __builtin_amdgcn_make_buffer_rsrc((void*)a_tile, (short)0, 0x7FFFFFFF, 0x00020000);
     constexpr int RPI = 64 / KCH;                        // rows per load instruction
     constexpr int A_INS = BM / RPI / C::NWAVES, B_INS = BN / RPI / C::NWAVES;
-    static_assert(A_INS + B_INS == BK / 4, "one slab load per 256 / BK MFMAs");
     uint32_t a_voff[A_INS], b_voff[B_INS];
-    // A_MSLAB: wave w loads M slab w of the tile (the matrix's last slab for
-    // slabs past M), K rows 8 q .. 8 q + 7 of it per instruction q, into
-    // LDS [M slab][K row][8 chunks of 8 M ids], chunk-swizzled by K row
+    // A_MSLAB: wave w loads its share (all of it, or half) of M slab w / WPS of
+    // the tile (the matrix's last slab for slabs past M), 8 K rows per
+    // instruction, into LDS [M slab][K row][8 chunks of 8 M ids],
+    // chunk-swizzled by K row
     const int64_t a_wslab =
-        kMSlabA ? (int64_t)(min(m0 / 64 + wave, (M + 63) / 64 - 1) - m0 / 64) * a_slab : 0;
+        kMSlabA ? (int64_t)(min(m0 / 64 + wave / WPS, (M + 63) / 64 - 1) - m0 / 64) * a_slab : 0;
 #pragma unroll
     for (int q = 0; q < A_INS; ++q) {
       if constexpr (kMSlabA) {
-        const int k = 8 * q + lane / KCH;
+        const int k = (wave % WPS) * (64 / WPS) + 8 * q + lane / KCH;
         a_voff[q] = (uint32_t)(k * 128 + ((lane % KCH) ^ mslab_swz(k)) * 16);
       } else {
         const int g = wave * A_INS + q, row = g * RPI + lane / KCH;
@@ -456,7 +464,10 @@ __global__ __launch_bounds__(256, 1) void k_gemm4w(GemmParams p) {
       // of its first 48 MFMAs, so that the reads are complete when the wave
       // reaches the barrier's wait (measured 1 % faster than reads spread to
       // the last MFMA); the other sub-step reads after every fourth.
+      // (128-wide tiles: 16 MFMAs per sub-step, ten reads after its first ten,
+      // a load after every second.)
       constexpr int LEVERY = TM * TN / NINS;   // MFMAs per slab load
+      constexpr bool kWide = TM * TN == 64;
       auto step = [&](int h, int nst, int nks, bool loads, int lq, int lst, bool pre) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
@@ -465,7 +476,9 @@ __global__ __launch_bounds__(256, 1) void k_gemm4w(GemmParams p) {
             const int m = i * TN + j;
             BGPO_MFMA16(acc[i][j], fa[h][i], fb[h][j]);
             if (loads && m % LEVERY == 1) issue_one(lq, lst, m / LEVERY);
-            if (pre) {
+            if (!kWide) {
+              if (m < TM + TN) rd(fa[1 - h], fb[1 - h], nst, nks, m);
+            } else if (pre) {
               if (m % 3 == 0 && m / 3 < TM + TN) rd(fa[1 - h], fb[1 - h], nst, nks, m / 3);
             } else if ((m & 3) == 3) {
               rd(fa[1 - h], fb[1 - h], nst, nks, m >> 2);
@@ -534,12 +547,11 @@ __global__ __launch_bounds__(256, 1) void k_gemm4w(GemmParams p) {
       // per-lane offsets)
       float* const pm = p.part_m + (int64_t)vt * p.ldp;
       float* const ps = p.part_s + (int64_t)vt * p.ldp;
-      // the references of the lane's 8 rows, loaded before the column blocks
+      // the references of the lane's rows, loaded before the column blocks
       // so that one wait covers them (padding rows: R2 = 0)
-      static_assert(TN == 8, "8 rows per lane");
       float r2v[TN];
       if constexpr (kStore)
-        rows_of_lane(p.ztgt, nw, n_valid, lane, 0.f, [](float z) { return exp_reference(z); }, r2v);
+        rows_of_lane<TN>(p.ztgt, nw, n_valid, lane, 0.f, [](float z) { return exp_reference(z); }, r2v);
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
         float mx = -INFINITY;
@@ -597,15 +609,15 @@ __global__ __launch_bounds__(256, 1) void k_gemm4w(GemmParams p) {
       // zeros.  Stored like the forward's exponentials: 16 bytes per lane and
       // pair of blocks straight into the chunk's slab-major dZ, which the dX GEMM reads
       // as its B operand and the dW GEMM as its M-slab-major A operand.
-      // the lane's 8 rows' log2-sum-exp2, scale and target (as a tile row
+      // the lane's rows' log2-sum-exp2, scale and target (as a tile row
       // index, may be outside), loaded before the column blocks so that one
       // wait covers them
       float l2v[TN], srv[TN];
       int ymv[TN];
       const int ysh = p.v0 + m0;
-      rows_of_lane(p.lse2, nw, n_valid, lane, 0.f, [](float v) { return v; }, l2v);
-      rows_of_lane(p.rscale, nw, n_valid, lane, 0.f, [](float v) { return v; }, srv);
-      rows_of_lane(p.rtgt, nw, n_valid, lane, -1, [ysh](int y) { return y - ysh; }, ymv);
+      rows_of_lane<TN>(p.lse2, nw, n_valid, lane, 0.f, [](float v) { return v; }, l2v);
+      rows_of_lane<TN>(p.rscale, nw, n_valid, lane, 0.f, [](float v) { return v; }, srv);
+      rows_of_lane<TN>(p.rtgt, nw, n_valid, lane, -1, [ysh](int y) { return y - ysh; }, ymv);
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
         const int nl = nw - n0 + 16 * j + (lane & 15);
@@ -649,8 +661,45 @@ __global__ __launch_bounds__(256, 1) void k_gemm4w(GemmParams p) {
 // Tile configuration of the production kernels (k_gemm4w): 256x256 block
 // tile, K slab 64 in a 2-stage LDS ring, four waves of 128x128, 256-byte LDS
 // swizzle.
-#define BGPO_TILE4 256, 256, 64, 2
+#define BGPO_TILE4 256, 256, 64, 2, 128
+// The same kernel on 128x128 block tiles, four waves of 128x32 (the wave's M
+// extent stays one log-sum-exp slice, summed in the same order, so l does not
+// depend on the tile), in a 4-stage ring (three slabs in flight: one tile per
+// compute unit does not hide a slab's latency by itself).  For problems whose
+// 256x256 tiles leave most of the 256 compute units idle; per FLOP it moves
+// twice the bytes from L2.
+#define BGPO_TILE4S 128, 128, 64, 4, 32
 constexpr int kGemmThreads4 = 256;
+
+// Launches kernel <EPI, AL> on the tile `small` selects.
+template <int EPI, int AL>
+static hipError_t launch_tiled(bool small, int grid, const GemmParams& p, hipStream_t s) {
+  if (small)
+    k_gemm4w<EPI, AL, BGPO_TILE4S><<<grid, kGemmThreads4, 0, s>>>(p);
+  else
+    k_gemm4w<EPI, AL, BGPO_TILE4><<<grid, kGemmThreads4, 0, s>>>(p);
+  return hipGetLastError();
+}
+
+// Rounds of the grid that M x N output tiles of edge e take.
+static int64_t rounds(int64_t M, int64_t N, int64_t e, int grid) {
+  return ((M + e - 1) / e * ((N + e - 1) / e) + grid - 1) / grid;
+}
+
+// Whether M x N outputs (one tile per workgroup and round) run faster on
+// 128-wide tiles.  A round of them takes 0.30-0.33 of a round of 256-wide
+// tiles where both take several (2048 rows of V 32000 d 2048: 16 rounds in
+// 283 us against 4 in 222; of V 16384 d 4096: 8 in 347 against 2 in 289) and
+// 0.4 where it is one (512 rows of V 8192 d 1024: 16 us against 36), so the
+// line lies at 3/8: 3 rounds for 1 stay with the 256-wide tiles, 2 for 1 or 4
+// for 2 do not (32 rows of V 126464 d 4096: 4 in 274 us against 2 in 348; dW of
+// V 4288 d 576, 1 for 1: 26 us against 57).
+static bool small_tiles(int64_t M, int64_t N, int grid) {
+  return 3 * rounds(M, N, 128, grid) < 8 * rounds(M, N, 256, grid);
+}
+
+// Rows of a unit before its masks are known: half of its positions (E[t] = 1/2).
+static int64_t rows_estimate(const Workspace& ws) { return (ws.g_used * ws.P + 1) / 2; }
 // band heights of the tile walk (bands of M tiles walking along N),
 // measured at the LLaDA head shape: dW and dX fastest with bands of 8, the
 // forward GEMM with bands of 4 (2 or 8: 2 % slower, 16: 7 %)
@@ -676,14 +725,37 @@ hipError_t launch_gemm_fwd(const Workspace& ws, int d, int V, int grid, bool sto
   p.k_split = d;
   p.part_m = ws.part_m; p.part_s = ws.part_s; p.ldp = ws.RP;
   p.group_m = kGroupMFwd;
-  if (store_u) {
-    p.dZ = ws.dZ; p.ldz = ws.ldz;
-    p.ztgt = ws.ztgt;
-    k_gemm4w<EPI_FWDU, A_ROW, BGPO_TILE4><<<grid, kGemmThreads4, 0, s>>>(p);
-  } else {
-    k_gemm4w<EPI_FWD, A_ROW, BGPO_TILE4><<<grid, kGemmThreads4, 0, s>>>(p);
-  }
-  return hipGetLastError();
+  const bool small = small_tiles(V, rows_estimate(ws), grid);
+  if (!store_u) return launch_tiled<EPI_FWD, A_ROW>(small, grid, p, s);
+  p.dZ = ws.dZ; p.ldz = ws.ldz;
+  p.ztgt = ws.ztgt;
+  return launch_tiled<EPI_FWDU, A_ROW>(small, grid, p, s);
+}
+
+// K of the dX GEMM: the vocabulary, or one chunk of it.
+static int64_t dx_k(const Workspace& ws, int V) {
+  return ws.chunk ? std::min<int64_t>(ws.chunk, V) : V;
+}
+
+// The dX GEMM's K is split so that its tiles fill the grid either way; the
+// 128-wide tiles win where their smaller tile ends (about 2 slabs' time per
+// round against 10) or their smaller row padding outweigh a slab rate of 0.75
+// (a 128-wide slab is a quarter of the work in a third of the time): with w
+// slabs per workgroup, w128 / 3 + 2 < w256 + 10.  Measured: w256 16 w128 64 (1024 rows
+// d 1024 V 16384) 48 us against 59; 15.6 and 31 (128 rows, d 2048 V 32000)
+// 39 against 75; 123 and 247 (32 rows, d 4096 V 126464) 188 against 261; 31
+// and 125 (512 rows, d 2048 V 32000) 119 against 96.
+static bool dx_small_tiles(const Workspace& ws, int d, int V, int grid) {
+  const int64_t rows = rows_estimate(ws), k = dx_k(ws, V) / 64;
+  const int64_t w256 = (d + 255) / 256 * ((rows + 255) / 256) * k;
+  const int64_t w128 = (d + 127) / 128 * ((rows + 127) / 128) * k;
+  return w128 < 3 * w256 + 24 * (int64_t)grid;
+}
+
+DxPlan dx_plan(const Workspace& ws, int d, int V, int grid) {
+  const bool small = dx_small_tiles(ws, d, V, grid);
+  const int e = small ? 128 : 256;
+  return DxPlan{(int)(dx_k(ws, V) / 64), (d + e - 1) / e, grid, (int)ws.n_split, e, small ? 26 : 13};
 }
 
 hipError_t launch_gemm_dx(const Workspace& ws, const uint16_t* W, int d, int V, int grid,
@@ -701,11 +773,9 @@ hipError_t launch_gemm_dx(const Workspace& ws, const uint16_t* W, int d, int V, 
   p.dyn_split = 1;
   p.group_m = kGroupMdX;
   p.out = ws.dx_part; p.ldo = d; p.split_stride = ws.RP * d;
-  if (ws.Wk)
-    k_gemm4w<EPI_F32_STORE, A_KSLAB, BGPO_TILE4><<<grid, kGemmThreads4, 0, s>>>(p);
-  else
-    k_gemm4w<EPI_F32_STORE, A_ROW, BGPO_TILE4><<<grid, kGemmThreads4, 0, s>>>(p);
-  return hipGetLastError();
+  const bool small = dx_small_tiles(ws, d, V, grid);
+  if (ws.Wk) return launch_tiled<EPI_F32_STORE, A_KSLAB>(small, grid, p, s);
+  return launch_tiled<EPI_F32_STORE, A_ROW>(small, grid, p, s);
 }
 
 hipError_t launch_gemm_dw(const Workspace& ws, float* dW, int d, int V, int grid, hipStream_t s) {
@@ -717,8 +787,7 @@ hipError_t launch_gemm_dw(const Workspace& ws, float* dW, int d, int V, int grid
   p.M = V; p.N = d; p.dyn_k = 1; p.meta = ws.unit();
   p.group_m = kGroupMdW;
   p.out = dW; p.ldo = V;
-  k_gemm4w<EPI_F32_ACCUM, A_MSLAB, BGPO_TILE4><<<grid, kGemmThreads4, 0, s>>>(p);
-  return hipGetLastError();
+  return launch_tiled<EPI_F32_ACCUM, A_MSLAB>(small_tiles(V, d, grid), grid, p, s);
 }
 
 hipError_t launch_gemm_recompute(const Workspace& ws, int d, int v0, int width, int grid,
@@ -732,8 +801,7 @@ hipError_t launch_gemm_recompute(const Workspace& ws, int d, int v0, int width, 
   p.group_m = kGroupMFwd;
   p.lse2 = ws.lse2; p.rscale = ws.row_scale; p.rtgt = ws.row_tgt; p.v0 = v0;
   p.dZ = ws.dZ; p.ldz = ws.RP;
-  k_gemm4w<EPI_DZ, A_ROW, BGPO_TILE4><<<grid, kGemmThreads4, 0, s>>>(p);
-  return hipGetLastError();
+  return launch_tiled<EPI_DZ, A_ROW>(small_tiles(width, rows_estimate(ws), grid), grid, p, s);
 }
 
 hipError_t launch_gemm_dx_chunk(const Workspace& ws, const uint16_t* W, int d, int V, int v0,
@@ -751,15 +819,11 @@ hipError_t launch_gemm_dx_chunk(const Workspace& ws, const uint16_t* W, int d, i
   p.dyn_split = 1;
   p.group_m = kGroupMdX;
   p.out = ws.dx_part; p.ldo = d; p.split_stride = ws.RP * d;
-  if (ws.Wk && first)
-    k_gemm4w<EPI_F32_STORE, A_KSLAB, BGPO_TILE4><<<grid, kGemmThreads4, 0, s>>>(p);
-  else if (ws.Wk)
-    k_gemm4w<EPI_F32_ACCUM, A_KSLAB, BGPO_TILE4><<<grid, kGemmThreads4, 0, s>>>(p);
-  else if (first)
-    k_gemm4w<EPI_F32_STORE, A_ROW, BGPO_TILE4><<<grid, kGemmThreads4, 0, s>>>(p);
-  else
-    k_gemm4w<EPI_F32_ACCUM, A_ROW, BGPO_TILE4><<<grid, kGemmThreads4, 0, s>>>(p);
-  return hipGetLastError();
+  const bool small = dx_small_tiles(ws, d, V, grid);
+  if (ws.Wk && first) return launch_tiled<EPI_F32_STORE, A_KSLAB>(small, grid, p, s);
+  if (ws.Wk) return launch_tiled<EPI_F32_ACCUM, A_KSLAB>(small, grid, p, s);
+  if (first) return launch_tiled<EPI_F32_STORE, A_ROW>(small, grid, p, s);
+  return launch_tiled<EPI_F32_ACCUM, A_ROW>(small, grid, p, s);
 }
 
 hipError_t launch_gemm_dw_chunk(const Workspace& ws, float* dW, int d, int V, int v0, int width,
@@ -772,8 +836,7 @@ hipError_t launch_gemm_dw_chunk(const Workspace& ws, float* dW, int d, int V, in
   p.M = width; p.N = d; p.dyn_k = 1; p.meta = ws.unit();
   p.group_m = kGroupMdW;
   p.out = dW + v0; p.ldo = V;
-  k_gemm4w<EPI_F32_ACCUM, A_MSLAB, BGPO_TILE4><<<grid, kGemmThreads4, 0, s>>>(p);
-  return hipGetLastError();
+  return launch_tiled<EPI_F32_ACCUM, A_MSLAB>(small_tiles(width, d, grid), grid, p, s);
 }
 
 int gemm_grid(int device) {

@@ -69,9 +69,11 @@ constexpr int kMaxDxSplit = 16;   // vocabulary splits of the dX GEMM
 // count that best fills the persistent grid for the unit's row count).
 struct DxPlan {
   int kslabs;      // V / 64
-  int col_tiles;   // d / 256
+  int col_tiles;   // d / tile
   int grid;        // workgroups of the persistent GEMM grid
   int s_max;       // splits the partial buffer holds
+  int tile;        // edge of the GEMM's output tiles
+  int red;         // cost of reducing one (split, row tile), in twentieths of a tile's slab
 };
 
 // Views into the caller's workspace: the state of one unit of G samples
@@ -219,6 +221,9 @@ hipError_t launch_gemm_dx_chunk(const Workspace& ws, const uint16_t* W, int d, i
                                 int width, bool first, int grid, hipStream_t s);
 hipError_t launch_gemm_dw_chunk(const Workspace& ws, float* dW, int d, int V, int v0, int width,
                                 int grid, hipStream_t s);
+
+// the split choice of a unit of g_used samples (set before): tile, K, grid
+DxPlan dx_plan(const Workspace& ws, int d, int V, int grid);
 
 int gemm_grid(int device);  // persistent grid size of the GEMM kernels on `device`
 

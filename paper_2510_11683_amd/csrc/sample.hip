@@ -37,12 +37,12 @@ struct MaskWalker {
   }
 };
 
-// Vocabulary split of the dX GEMM for a unit with row_tiles 256-row tiles:
+// Vocabulary split of the dX GEMM for a unit with row_tiles row tiles:
 // the split count s minimising an estimate of the GEMM's time on the
-// persistent grid, in units of one 256x256x64 slab on one workgroup:
+// persistent grid, in units of one tile's 64-deep slab on one workgroup:
 //   ceil(tiles / grid) rounds x (slabs per split + ~10 for the tile's
-//   prologue and fp32 partial store) + ~0.65 per (split, row tile) for the
-//   reduction of the partials.
+//   prologue and fp32 partial store) + pl.red / 20 per (split, row tile) for
+//   the reduction of the partials (0.65 slabs of a 256-wide tile).
 // A fixed split leaves most of the last round idle for some row counts
 // (576 tiles on 256 workgroups use 2.25 of 3 rounds).  One wave: lane l
 // estimates the split l + 1, the smallest estimate (of the smallest split)
@@ -55,7 +55,7 @@ __device__ void choose_dx_split(int row_tiles, const DxPlan& pl, int lane, int* 
   const uint32_t se = ((uint32_t)pl.kslabs + ks - 1) / ks;   // splits actually used
   const uint32_t tiles = (uint32_t)row_tiles * pl.col_tiles * se;
   const uint32_t rounds = (tiles + pl.grid - 1) / pl.grid;
-  const uint64_t cost = (uint64_t)rounds * (ks + 10) * 20 + 13ull * se * row_tiles;
+  const uint64_t cost = (uint64_t)rounds * (ks + 10) * 20 + (uint64_t)pl.red * se * row_tiles;
   uint64_t best = (cost << 6) | (uint32_t)(sp - 1);
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
@@ -88,7 +88,7 @@ __device__ void write_record(SampleMeta* m, int row0, int col0, int total, const
   const int rows = row0 + total;
   const int rows_pad = (rows + kRowPad - 1) / kRowPad * kRowPad;
   int split, kslab;
-  choose_dx_split(rows_pad / kRowPad, plan, lane, &split, &kslab);
+  choose_dx_split((rows + plan.tile - 1) / plan.tile, plan, lane, &split, &kslab);
   if (lane == 0) {
     m->n_rows = rows;
     m->n_rows_pad = rows_pad;

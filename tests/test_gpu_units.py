@@ -111,6 +111,35 @@ def test_overlapping_sample_strides(stride_rows, norm):
         assert rel_maxnorm(one, many) <= 1e-5
 
 
+@pytest.mark.parametrize("d,V", [
+    (64, 64),        # one tile of either size, most of it past the edges
+    (128, 128),      # one whole 128-wide tile
+    (192, 320),      # ragged in both
+    (1024, 8256),    # several 128-wide tiles per workgroup in dW, one in the forward
+    (2048, 32064),   # 256-wide tiles in the forward and dW
+])
+@pytest.mark.parametrize("L", [2, 127, 300])
+def test_tile_sizes_match_oracle(d, V, L):
+    """The GEMMs on 128-wide and 256-wide tiles, chosen by the sizes, with the
+    unit's rows below, around and above a tile; off-policy."""
+    w = workloads.Workload("tiles", B=2, L=L, d=d, V=V, n_t=2, lengths=(max(1, L - 5), L), adv="normal",
+                           targets="uniform", data_seed=2200 + d, philox_seed=0xB6B40000 + L)
+    x = workloads.generate(w)
+    p = elbo.Problem(2, L, d, V, 2, seed=w.philox_seed)
+    args = (x["hidden"], x["W"], x["targets"], x["resp_mask"], x["adv"])
+    old = elbo.elbo_collapsed(p, *args, backward=False).ell + np.random.default_rng(L).normal(0, 0.5, (2, 2))
+    ref = elbo.elbo_collapsed(p, *args, ell_old=old)
+    r = Runner(w, x)
+    r.bwd(ell_old=old)
+    o = r.out()
+    np.testing.assert_array_equal(o["nm"], ref.n_masked)
+    np.testing.assert_allclose(o["ell"], ref.ell, rtol=1e-3, atol=0)
+    assert rel_maxnorm(o["dX"], ref.dX) <= 2e-2
+    assert rel_maxnorm(o["dW"], ref.dW) <= 2e-2
+    r.fwd()
+    assert np.array_equal(r.out()["ell"], o["ell"])
+
+
 @pytest.mark.parametrize("d", [128, 256, 576])
 def test_empty_splits_of_the_last_vocabulary_chunk(d):
     """Recompute backward whose last vocabulary chunk (64 ids, one slab) leaves
