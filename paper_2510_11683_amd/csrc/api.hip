@@ -95,6 +95,7 @@ size_t workspace_layout(const Dims& dm, const Plan& pl, void* base, Workspace* w
     w.row_scale = static_cast<float*>(take(RP * 4));
     w.row_f = static_cast<float*>(take(RP * 4));
     w.row_bad = static_cast<uint8_t*>(take(RP));
+    w.bad_count = static_cast<int32_t*>(take(RP / 64 * 4));
     w.inv_rms = static_cast<float*>(take(RP * 4));
     w.mask_scratch = take(mask_scratch_bytes(dm.B, dm.L));
     w.part_m = static_cast<float*>(take(nvt * RP * 4));
@@ -412,7 +413,7 @@ struct Act {
 static int run_forward_unit(const bgpo_problem* p, Workspace& ws, Timer& tm, int grid, int j0,
                             int n_s, const Act& act, const int32_t* targets, const uint8_t* resp,
                             const float* adv, const double* ell_old, double loss_scale,
-                            double* ell, double* g, double* loss, int32_t* n_masked, float* t_out,
+                            double* ell, double* g, int32_t* n_masked, float* t_out,
                             int32_t* flags, bool backward, bool store_u,
                             const SampleMeta* prev_unit, const double* dbar, hipStream_t s) {
   const Dims dm = dims_of(p);
@@ -425,21 +426,18 @@ static int run_forward_unit(const bgpo_problem* p, Workspace& ws, Timer& tm, int
   BGPO_TRY(tm.end(n_s));
   BGPO_TRY(tm.begin(BGPO_K_GATHER));
   if (act.gamma)
-    BGPO_TRY(launch_row_rms(act.at(j0), act.f32, act.stride, dm.B, ws, dm.d, act.eps, s));
+    BGPO_TRY(launch_row_rms(act.at(j0), act.f32, act.stride, dm.B, ws, act.gamma, dm.d, act.eps,
+                            s));
   BGPO_TRY(launch_gather(act.at(j0), act.f32, act.stride, dm.B, act.gamma, ws, dm.d, s));
   BGPO_TRY(tm.end(act.gamma ? 2 : 1));
-  // the target logits first: the stored forward's exponent reference
-  BGPO_TRY(tm.begin(BGPO_K_ELL));
-  BGPO_TRY(launch_target_logit(ws, dm.d, s));
-  BGPO_TRY(tm.end());
   BGPO_TRY(tm.begin(BGPO_K_FWD));
   BGPO_TRY(launch_gemm_fwd(ws, dm.d, dm.V, grid, store_u, s));
   BGPO_TRY(tm.end());
   BGPO_TRY(tm.begin(BGPO_K_ELL));
-  BGPO_TRY(launch_combine_rows(ws, dm.V, s));
-  BGPO_TRY(launch_seq_terms(ws, dm.B, dm.n_t, j0, adv, ell_old, loss_scale, ell, g, loss, flags,
+  BGPO_TRY(launch_combine_rows(ws, dm.V, store_u, s));
+  BGPO_TRY(launch_seq_terms(ws, dm.B, dm.n_t, j0, adv, ell_old, loss_scale, ell, g, flags,
                             backward, p->bound, dbar, s));
-  BGPO_TRY(tm.end(2));
+  BGPO_TRY(tm.end(3));   // (the target logits, formed with the gather, are a step of this class)
   return BGPO_OK;
 }
 
@@ -538,12 +536,14 @@ namespace bgpo {
 // sample order (with the norm backward).  W: the caller's W_head (bf16
 // inputs), read by the dX GEMM when the plan keeps no slab-major copy.
 static int unit_backward(const Workspace& ws, const Act& act, int j0, int j_begin,
-                         const uint16_t* W, float* dX, float* dgamma, float* dW,
-                         const Dims& dm, int grid, Timer& tm, hipStream_t s) {
+                         const uint16_t* W, double loss_scale, const double* g, double* loss,
+                         float* dX, float* dgamma, float* dW, const Dims& dm, int grid, Timer& tm,
+                         hipStream_t s) {
+  // (one launch; in the stored mode it does the three steps of its class)
+  BGPO_TRY(tm.begin(ws.chunk ? BGPO_K_ELL : BGPO_K_SOFTMAX_GRAD));
+  BGPO_TRY(launch_row_terms(ws, dm.B, dm.n_t, j0, loss_scale, g, loss, dm.d, dm.V, s));
+  BGPO_TRY(tm.end(ws.chunk ? 0 : 3));
   if (!ws.chunk) {
-    BGPO_TRY(tm.begin(BGPO_K_SOFTMAX_GRAD));
-    BGPO_TRY(launch_grad_scale(ws, dm.d, dm.V, s));
-    BGPO_TRY(tm.end(3));
     BGPO_TRY(tm.begin(BGPO_K_DX));
     BGPO_TRY(launch_gemm_dx(ws, W, dm.d, dm.V, grid, s));
     BGPO_TRY(tm.end());
@@ -595,7 +595,7 @@ static int bwd_retained(const bgpo_problem* prob, const Plan& pl, const Act& act
   for (int u = 0; u < n_units; ++u) {
     const int j0 = u * G, n_s = std::min(G, dm.n_t - j0);
     const int st = run_forward_unit(prob, U[u], tm, grid, j0, n_s, act, targets, resp_mask,
-                                    nullptr, nullptr, 0.0, ell, nullptr, nullptr, n_masked, t_out,
+                                    nullptr, nullptr, 0.0, ell, nullptr, n_masked, t_out,
                                     status_flags, false, true, u ? U[u - 1].unit() : nullptr,
                                     nullptr, s);
     if (st != BGPO_OK) return st;
@@ -610,10 +610,11 @@ static int bwd_retained(const bgpo_problem* prob, const Plan& pl, const Act& act
   for (int u = 0; u < n_units; ++u) {
     const int j0 = u * G;
     BGPO_TRY(tm.begin(BGPO_K_ELL));
-    BGPO_TRY(launch_seq_terms(U[u], dm.B, dm.n_t, j0, adv, ell_old, loss_scale, ell, g, loss,
+    BGPO_TRY(launch_seq_terms(U[u], dm.B, dm.n_t, j0, adv, ell_old, loss_scale, ell, g,
                               status_flags, true, prob->bound, dbar, s));
     BGPO_TRY(tm.end());
-    const int st = unit_backward(U[u], act, j0, 0, static_cast<const uint16_t*>(W_head), dX,
+    const int st = unit_backward(U[u], act, j0, 0, static_cast<const uint16_t*>(W_head),
+                                 loss_scale, g, loss, dX,
                                  dgamma, dW, dm, grid, tm, s);
     if (st != BGPO_OK) return st;
   }
@@ -653,7 +654,7 @@ static int elbo_fwd_impl(const bgpo_problem* prob, const Act& act, const void* W
   for (int j0 = prob->j_begin; j0 < j_end; j0 += (int)ws.G) {
     const int n_s = std::min<int>(j_end - j0, (int)ws.G);
     st = run_forward_unit(prob, ws, tm, grid, j0, n_s, act, targets, resp_mask, nullptr, nullptr,
-                          0.0, ell, nullptr, nullptr, n_masked, t_out, nullptr, false, false,
+                          0.0, ell, nullptr, n_masked, t_out, nullptr, false, false,
                           nullptr, nullptr, s);
     if (st != BGPO_OK) return st;
   }
@@ -710,7 +711,7 @@ static int elbo_bwd_impl(const bgpo_problem* prob, const Act& act, const void* W
     for (int j0 = 0; j0 < prob->n_t; j0 += (int)ws.G) {
       const int n_s = std::min<int>(prob->n_t - j0, (int)ws.G);
       st = run_forward_unit(prob, ws, tm, grid, j0, n_s, act, targets, resp_mask, nullptr, nullptr,
-                            0.0, ell, nullptr, nullptr, n_masked, t_out, status_flags, false,
+                            0.0, ell, nullptr, n_masked, t_out, status_flags, false,
                             false, nullptr, nullptr, s);
       if (st != BGPO_OK) return st;
     }
@@ -731,10 +732,11 @@ static int elbo_bwd_impl(const bgpo_problem* prob, const Act& act, const void* W
     const SampleMeta* prev = in_batch ? last : nullptr;
     std::swap(ws.meta, ws.meta2);
     st = run_forward_unit(prob, ws, tm, grid, j0, n_s, act, targets, resp_mask, adv, ell_old,
-                          loss_scale, ell, g, loss, n_masked, t_out, status_flags, true, store_u,
+                          loss_scale, ell, g, n_masked, t_out, status_flags, true, store_u,
                           prev, dbar, s);
     if (st != BGPO_OK) return st;
-    st = unit_backward(ws, act, j0, prob->j_begin, static_cast<const uint16_t*>(W_head), dX,
+    st = unit_backward(ws, act, j0, prob->j_begin, static_cast<const uint16_t*>(W_head),
+                       loss_scale, g, loss, dX,
                        dgamma, dW, dm, grid, tm, s);
     if (st != BGPO_OK) return st;
     last = ws.unit();

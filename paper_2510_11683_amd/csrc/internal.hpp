@@ -105,6 +105,7 @@ struct Workspace {
   float* row_f;        // [RP]         stored backward: dZ row factor s 2^(R2 - lse2) (0 for padding)
   uint8_t* row_bad;    // [RP]         stored backward: row recomputed against R2 = lse2
   double* dbar;        // [B]          mean log-ratio over all samples (exact objective)
+  int32_t* bad_count;  // [RP/64]      marked rows among each 64
   float* inv_rms;      // [RP]         final-RMSNorm 1/rms of each compacted row
   void* mask_scratch;  // mask_scratch_bytes(B, L): the multi-block mask passes
   float* gpart;        // [RP/kGammaRows, d] dgamma partial sums over chunks of a unit's rows
@@ -178,26 +179,29 @@ hipError_t launch_masks(const uint8_t* resp, const int32_t* targets, int B, int 
 // with force_multi)
 size_t mask_scratch_bytes(int B, int L);
 // x / hidden of row r is x + (row_seq[r] / B) * stride (the row's sample in the unit)
-// (f32: x / hidden are fp32, rounded to bf16 as they are read)
+// (f32: x / hidden are fp32, rounded to bf16 as they are read).  The target
+// logits (the stored forward's exponent reference) are formed by row_rms with
+// the norm, by gather without.
 hipError_t launch_row_rms(const void* x, bool f32, int64_t stride, int B, const Workspace& ws,
-                          int d, float eps, hipStream_t s);
+                          const float* gamma, int d, float eps, hipStream_t s);
 hipError_t launch_gather(const void* hidden, bool f32, int64_t stride, int B, const float* gamma,
                          const Workspace& ws, int d, hipStream_t s);
 hipError_t launch_gemm_fwd(const Workspace& ws, int d, int V, int grid, bool store_u,
                            hipStream_t s);
-hipError_t launch_target_logit(const Workspace& ws, int d, hipStream_t s);
-hipError_t launch_combine_rows(const Workspace& ws, int V, hipStream_t s);
+// mark: also mark the rows outside the exponent range (stored backward)
+hipError_t launch_combine_rows(const Workspace& ws, int V, bool mark, hipStream_t s);
 // per-response terms of the unit's samples j0 .. j0 + g_used - 1
 hipError_t launch_seq_terms(const Workspace& ws, int B, int n_t, int j0, const float* adv,
                             const double* ell_old, double loss_scale, double* ell, double* g,
-                            double* loss, int32_t* flags, bool backward, int bound,
-                            const double* dbar, hipStream_t s);
+                            int32_t* flags, bool backward, int bound, const double* dbar,
+                            hipStream_t s);
 hipError_t launch_mean_ratio(const double* ell, const double* ell_old, int B, int n_t,
                              double* dbar, hipStream_t s);
-// stored backward, after the unit's scales: row factors, the target entries of
-// dZ, H_c^T scaled by the row factors, and the rows outside the exponent range
-// recomputed
-hipError_t launch_grad_scale(const Workspace& ws, int d, int V, hipStream_t s);
+// after the unit's scales: the loss, and the rows' scales (recompute mode) or
+// row factors, target entries of dZ, H_c^T scaled by the row factors and the
+// rows outside the exponent range recomputed (stored mode)
+hipError_t launch_row_terms(const Workspace& ws, int B, int n_t, int j0, double loss_scale,
+                            const double* g, double* loss, int d, int V, hipStream_t s);
 // (W: the caller's bf16 W_head, read row-major when ws.Wk is NULL)
 hipError_t launch_gemm_dx(const Workspace& ws, const uint16_t* W, int d, int V, int grid,
                           hipStream_t s);

@@ -1,5 +1,4 @@
 // Row and response reductions of the ELBO head:
-//   target logit      z[row, y_row] = Hc[row] . W[:, y_row]
 //   log-sum-exp       combine the per-vocabulary-tile (max, sum) partials
 //   per-response      l = (1/t) sum log p (Eq. per_step_loss), d, g (Eq. g),
 //                     loss (Algorithm 1, L_j = -g_j/G) and the gradient scale
@@ -14,40 +13,6 @@
 
 namespace bgpo {
 
-// One wave per row: 64 lanes split the d-long dot product (Hc slab-major with
-// RP rows per slab: each group of 8 lanes reads one 128-byte slab row).
-__global__ __launch_bounds__(256) void k_target_logit(const uint16_t* __restrict__ Hc,
-                                                      const uint16_t* __restrict__ WT,
-                                                      const int32_t* __restrict__ row_tgt,
-                                                      const SampleMeta* __restrict__ meta,
-                                                      float* __restrict__ ztgt, int d,
-                                                      int64_t RP) {
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (row >= meta->n_rows) return;
-  const uint16_t* w = WT + (int64_t)row_tgt[row] * d;
-  float acc = 0.f;
-  for (int k = lane * 8; k < d; k += 64 * 8) {
-    const uint4 hv = *reinterpret_cast<const uint4*>(Hc + slab_index(RP, row, k));
-    const uint4 wv = *reinterpret_cast<const uint4*>(w + k);
-    const uint32_t ha[4] = {hv.x, hv.y, hv.z, hv.w}, wa[4] = {wv.x, wv.y, wv.z, wv.w};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      acc = fmaf(__uint_as_float(ha[e] << 16), __uint_as_float(wa[e] << 16), acc);
-      acc = fmaf(__uint_as_float(ha[e] & 0xFFFF0000u), __uint_as_float(wa[e] & 0xFFFF0000u), acc);
-    }
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-  if (lane == 0) ztgt[row] = acc;
-}
-
-hipError_t launch_target_logit(const Workspace& ws, int d, hipStream_t s) {
-  k_target_logit<<<(unsigned)(ws.RP / 4), 256, 0, s>>>(ws.Hc, ws.WT, ws.row_tgt, ws.unit(), ws.ztgt,
-                                                       d, ws.RP);
-  return hipGetLastError();
-}
-
 // log-sum-exp of every row from its per-slice (max, sum) partials, and the
 // target's log p.  64 rows per workgroup, one per lane, so each load of a
 // slice's partials is 64 consecutive floats; the 16 waves take every 16th
@@ -55,10 +20,17 @@ hipError_t launch_target_logit(const Workspace& ws, int d, hipStream_t s) {
 // fixed order.
 constexpr int kCombineWaves = 16;
 
+// Whether a row's exponentials against R2 = exp_reference(z_y) may have left
+// the exponent range (true for NaN).
+__device__ __forceinline__ bool out_of_range(float lse2, float ztgt) {
+  return !(lse2 - exp_reference(ztgt) <= kExpRange);
+}
+
 __global__ __launch_bounds__(64 * kCombineWaves) void k_combine_rows(
     const float* __restrict__ part_m, const float* __restrict__ part_s,
     const float* __restrict__ ztgt, const SampleMeta* __restrict__ meta,
-    float* __restrict__ lse2, float* __restrict__ lp, int nvt, int64_t ldp) {
+    float* __restrict__ lse2, float* __restrict__ lp, uint8_t* __restrict__ row_bad,
+    int32_t* __restrict__ bad_count, int nvt, int64_t ldp) {
   __shared__ float sm[kCombineWaves][64], ss[kCombineWaves][64];
   const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
   const int row = blockIdx.x * 64 + lane;
@@ -95,22 +67,24 @@ __global__ __launch_bounds__(64 * kCombineWaves) void k_combine_rows(
 #pragma unroll
     for (int k = 0; k < kCombineWaves; ++k)
       if (ss[k][lane] > 0.f) S += ss[k][lane] * exp2f(sm[k][lane] - M);
-    const float l2 = M + log2f(S);
+    const float l2 = M + log2f(S), zt = ztgt[row];
     lse2[row] = l2;
-    lp[row] = ztgt[row] - l2 * kLn2;
+    lp[row] = zt - l2 * kLn2;
+    if (row_bad) {
+      const bool bad = out_of_range(l2, zt);
+      row_bad[row] = bad;
+      const int n = __popcll(__ballot(bad));   // (row 64 blockIdx.x is valid)
+      if (lane == 0) bad_count[blockIdx.x] = n;
+    }
   }
 }
 
-hipError_t launch_combine_rows(const Workspace& ws, int V, hipStream_t s) {
-  k_combine_rows<<<(unsigned)(ws.RP / 64), 64 * kCombineWaves, 0, s>>>(
-      ws.part_m, ws.part_s, ws.ztgt, ws.unit(), ws.lse2, ws.lp, (int)ws.nvt, ws.RP);
+hipError_t launch_combine_rows(const Workspace& ws, int V, bool mark, hipStream_t s) {
+  k_combine_rows<<<(unsigned)(ws.g_used * ws.NP / 64), 64 * kCombineWaves, 0, s>>>(
+      ws.part_m, ws.part_s, ws.ztgt, ws.unit(), ws.lse2, ws.lp, mark ? ws.row_bad : nullptr,
+      ws.bad_count, (int)ws.nvt, ws.RP);
   return hipGetLastError();
 }
-
-// Per-response terms of the samples of a unit.  One workgroup; each wave
-// takes (sample, response) segments wave, wave + 16, ...; the loss is then
-// summed by one thread over the segments in sample-then-response order.
-constexpr int kSeqThreads = 1024;
 
 // The objective's per-sample term g and its derivative dg/dl for
 // d = l - l_old:
@@ -135,74 +109,52 @@ __device__ __forceinline__ void bound_term(double dj, double A, int n_t, int bou
   }
 }
 
-// Sample g of the unit is sample j0 + g; its response b has rows
+// Per-response terms of the samples of a unit, one wave per (sample, response)
+// segment.  Sample g of the unit is sample j0 + g; its response b has rows
 // [seg_off[g (B+1) + b], seg_off[g (B+1) + b + 1]) and timestep t24[g B + b].
-// The gradient scale of (g, b) goes to seq_scale[g B + b] and from there to
-// every row of that response (row_seq[r] = g B + b).
-__global__ __launch_bounds__(kSeqThreads) void k_seq_terms(
+// The gradient scale of (g, b) goes to seq_scale[g B + b]; the loss and the
+// rows' scales follow from g and seq_scale in the next kernel, when every
+// segment is done.
+__global__ __launch_bounds__(256) void k_seq_terms(
     const float* __restrict__ lp, const int32_t* __restrict__ seg_off,
-    const uint32_t* __restrict__ t24, const int32_t* __restrict__ row_seq,
-    const SampleMeta* __restrict__ meta, int B, int n_t, int j0, int n_samples,
+    const uint32_t* __restrict__ t24, int B, int n_t, int j0, int n_samples,
     const float* __restrict__ adv, const double* __restrict__ ell_old, double loss_scale,
-    double* __restrict__ ell, double* __restrict__ g, double* __restrict__ loss,
-    int32_t* __restrict__ flags, float* __restrict__ seq_scale, float* __restrict__ row_scale,
-    int backward, int bound, const double* __restrict__ dbar) {
-  __shared__ int s_bad;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (tid == 0) s_bad = 0;
-  __syncthreads();
-  const int n_seg = n_samples * B;
-  for (int sg = wave; sg < n_seg; sg += kSeqThreads / 64) {
-    const int gs = sg / B, b = sg - gs * B, j = j0 + gs;
-    const int r0 = seg_off[gs * (B + 1) + b], r1 = seg_off[gs * (B + 1) + b + 1];
-    double acc = 0.0;
-    for (int r = r0 + lane; r < r1; r += 64) acc += (double)lp[r];
+    double* __restrict__ ell, double* __restrict__ g, int32_t* __restrict__ flags,
+    float* __restrict__ seq_scale, int backward, int bound, const double* __restrict__ dbar) {
+  const int lane = threadIdx.x & 63, sg = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (sg >= n_samples * B) return;
+  const int gs = sg / B, b = sg - gs * B, j = j0 + gs;
+  const int r0 = seg_off[gs * (B + 1) + b], r1 = seg_off[gs * (B + 1) + b + 1];
+  double acc = 0.0;
+#pragma unroll 4
+  for (int r = r0 + lane; r < r1; r += 64) acc += (double)lp[r];
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-    if (lane == 0) {
-      const double t = (double)t24[gs * B + b] * (1.0 / 16777216.0);
-      const double l = acc / t;                                        // Eq. per_step_loss
-      const int64_t o = (int64_t)b * n_t + j;
-      ell[o] = l;
-      if (backward) {
-        const double dj = ell_old ? l - ell_old[o] : 0.0;
-        double gj, dg;
-        bound_term(dj, (double)adv[b], n_t, bound, dbar ? dbar[b] : 0.0, &gj, &dg);
-        g[o] = gj;
-        const double sc = loss_scale * dg / t;
-        seq_scale[gs * B + b] = (float)sc;
-        if (!isfinite(l) || !isfinite(gj) || !isfinite(sc) || !isfinite((float)sc)) s_bad = 1;
-      } else if (!isfinite(l)) {
-        s_bad = 1;
-      }
-    }
-  }
-  // g and seq_scale of every segment are written (global memory) before here
-  __threadfence_block();
-  __syncthreads();
-  if (tid == 0) {
-    if (backward) {
-      double loss_acc = 0.0;
-      for (int gs = 0; gs < n_samples; ++gs)
-        for (int b = 0; b < B; ++b) loss_acc += -loss_scale * g[(int64_t)b * n_t + j0 + gs];
-      loss[0] += loss_acc;
-    }
-    if (s_bad && flags) atomicOr(flags, kFlagNonfinite);
-  }
+  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+  if (lane) return;
+  const double t = (double)t24[sg] * (1.0 / 16777216.0);
+  const double l = acc / t;                                        // Eq. per_step_loss
+  const int64_t o = (int64_t)b * n_t + j;
+  ell[o] = l;
+  bool bad = !isfinite(l);
   if (backward) {
-    const int N = meta->n_rows, NPr = meta->n_rows_pad;
-    for (int r = tid; r < NPr; r += kSeqThreads) row_scale[r] = r < N ? seq_scale[row_seq[r]] : 0.f;
+    const double dj = ell_old ? l - ell_old[o] : 0.0;
+    double gj, dg;
+    bound_term(dj, (double)adv[b], n_t, bound, dbar ? dbar[b] : 0.0, &gj, &dg);
+    g[o] = gj;
+    const double sc = loss_scale * dg / t;
+    seq_scale[sg] = (float)sc;
+    bad = bad || !isfinite(gj) || !isfinite(sc) || !isfinite((float)sc);
   }
+  if (bad && flags) atomicOr(flags, kFlagNonfinite);
 }
 
 hipError_t launch_seq_terms(const Workspace& ws, int B, int n_t, int j0, const float* adv,
                             const double* ell_old, double loss_scale, double* ell, double* g,
-                            double* loss, int32_t* flags, bool backward, int bound,
-                            const double* dbar, hipStream_t s) {
-  k_seq_terms<<<1, kSeqThreads, 0, s>>>(ws.lp, ws.seg_off, ws.t24, ws.row_seq, ws.unit(), B, n_t,
-                                        j0, ws.g_used, adv, ell_old, loss_scale, ell, g, loss,
-                                        flags, ws.seq_scale, ws.row_scale, backward ? 1 : 0, bound,
-                                        dbar);
+                            int32_t* flags, bool backward, int bound, const double* dbar,
+                            hipStream_t s) {
+  k_seq_terms<<<(unsigned)((ws.g_used * B + 3) / 4), 256, 0, s>>>(
+      ws.lp, ws.seg_off, ws.t24, B, n_t, j0, ws.g_used, adv, ell_old, loss_scale, ell, g, flags,
+      ws.seq_scale, backward ? 1 : 0, bound, dbar);
   return hipGetLastError();
 }
 
@@ -225,61 +177,111 @@ hipError_t launch_mean_ratio(const double* ell, const double* ell_old, int B, in
   return hipGetLastError();
 }
 
-// Stored backward, once the unit's scales s are known.  The forward kept
+// Once the unit's scales s are known: the loss, and per row what the backward
+// needs.  Recompute mode: the row's scale (0 for padding), which the chunk's
+// GEMM epilogue applies.  Stored mode: the forward kept
 // u = 2^(z log2e - R2) (bf16) in dZ (the unit's rows from its col_off, ldz
 // rows per slab), with R2 = exp_reference(z_y)
 // per row; since p = u 2^(R2 - lse2),
 //     dZ = s (p - onehot) = f (u - onehot 2^(lse2 - R2)),  f = s 2^(R2 - lse2)
 // (differentiating Eq. per_step_loss, d l / d z = (onehot - p) / t; s carries
-// -loss_scale dg/dl and the 1/t).  k_grad_rows sets f per row (0 for padding)
-// and replaces the target entry by (p_y - 1) 2^(lse2 - R2),
-// p_y from the fp32 target logit; f scales the dX rows in the reduction and
-// H_c^T's columns (k_scale_hct) for the dW GEMM.  A row with
+// -loss_scale dg/dl and the 1/t).  f (0 for padding) scales the dX rows in the
+// reduction and H_c^T's columns for the dW GEMM, and the target entry becomes
+// (p_y - 1) 2^(lse2 - R2), p_y from the fp32 target logit.  A row with
 // lse2 - R2 > kExpRange (its target log2-probability below
-// -(kExpRef + kExpRange)) is marked: its exponentials may have left the range
-// of bf16 and of the fp32 accumulators, so k_fixup_rows recomputes the row
-// against R2 = lse2 (f = s), from fp32 dot products.
-__global__ __launch_bounds__(256) void k_grad_rows(
-    const float* __restrict__ lse2, const float* __restrict__ row_scale,
-    const float* __restrict__ ztgt, const int32_t* __restrict__ row_tgt,
-    const SampleMeta* __restrict__ meta, uint16_t* __restrict__ dZ, float* __restrict__ row_f,
-    uint8_t* __restrict__ row_bad, int64_t ldz) {
-  const int r = blockIdx.x * 256 + threadIdx.x;
-  if (r >= meta->n_rows_pad) return;
-  float f = 0.f;
-  if (r < meta->n_rows) {
-    const float l2 = lse2[r], z2 = ztgt[r] * kLog2e;
-    const float r2 = exp_reference(ztgt[r]);
-    const bool bad = !(l2 - r2 <= kExpRange);   // (NaN too)
-    const float r2e = bad ? l2 : r2;
-    f = row_scale[r] * __builtin_amdgcn_exp2f(r2e - l2);
-    const float val = (__builtin_amdgcn_exp2f(z2 - l2) - 1.f) * __builtin_amdgcn_exp2f(l2 - r2e);
-    const uint16_t b = (uint16_t)(pack_bf16x2(val, 0.f) & 0xFFFFu);
-    const int y = row_tgt[r];
-    dZ[slab_index(ldz, (int64_t)meta->col_off + r, y)] = b;
-    row_bad[r] = bad;
+// -(kExpRef + kExpRange)) was marked with the log-sum-exp: its exponentials may
+// have left the range of bf16 and of the fp32 accumulators, so it is
+// recomputed against R2 = lse2 (f = s), from fp32 dot products.
+//
+// One launch whose workgroups take one of these roles each; none reads what
+// another writes (every role forms f or the marks from lse2 and the target
+// logit for itself), so they run side by side.  Bound by latency and, in the
+// H_c^T role, by HBM.  With the target logits in the gather's launch and one
+// wave per segment in k_seq_terms, against five launches: a step of B2 L64 d128
+// V1024 n_t 4 62.5 -> 55.6 us, of B3 L201 d576 V4288 n_t 6 113.5 -> 106.9 us.
+struct RowTerms {
+  const float *lse2, *ztgt, *seq_scale;
+  const int32_t *row_tgt, *row_seq, *bad_count;
+  const uint8_t* row_bad;
+  const SampleMeta* meta;
+  uint16_t *dZ, *HcT;
+  const uint16_t *Hc, *WT;
+  float *row_f, *row_scale;
+  int64_t ldz, RP;
+  int d, V;
+  // the loss: g of samples j0 .. j0 + n_samples - 1
+  const double* g;
+  double* loss;
+  double loss_scale;
+  int B, n_t, j0, n_samples;
+  int n_rows_wg, n_hct_wg;    // workgroups of the row and H_c^T roles
+
+  __device__ float scale(int r) const { return seq_scale[row_seq[r]]; }
+  // f of row r < n_rows
+  __device__ float factor(int r) const {
+    const float l2 = lse2[r], zt = ztgt[r];
+    return scale(r) *
+           __builtin_amdgcn_exp2f((out_of_range(l2, zt) ? l2 : exp_reference(zt)) - l2);
   }
-  row_f[r] = f;
+};
+
+// loss += the unit's terms, summed in sample-then-response order (one wave:
+// 64 terms per load, added one after the other)
+__device__ void add_loss(const RowTerms& p) {
+  const int lane = threadIdx.x;
+  const int n = p.n_samples * p.B;
+  double acc = 0.0;
+  for (int i0 = 0; i0 < n; i0 += 64) {
+    const int i = i0 + lane;
+    double v = 0.0;
+    if (i < n) v = -p.loss_scale * p.g[(int64_t)(i % p.B) * p.n_t + p.j0 + i / p.B];
+    const int m = min(64, n - i0);
+    for (int q = 0; q < m; ++q) acc += __shfl(v, q, 64);
+  }
+  if (lane == 0) p.loss[0] += acc;
 }
 
-// H_c^T[c][col_off + r] *= f_r (bf16, nearest even) over the unit's columns
-// up to col_end (its rows rounded up to 64), not its 256-row padding: the next
-// unit of the dW batch starts at col_end, and with every sample retained its
-// columns already hold its rows when this runs.  One workgroup per 64 x 64
-// tile, which is 8 KB of the slab-major H_c^T.
-__global__ __launch_bounds__(256) void k_scale_hct(const float* __restrict__ row_f,
-                                                   const SampleMeta* __restrict__ meta,
-                                                   uint16_t* __restrict__ HcT, int d) {
-  const int r0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
-  if (r0 >= meta->col_end - meta->col_off) return;
+// the row role: f and the target entry (stored), or the scale (recompute)
+template <bool STORED>
+__device__ void row_role(const RowTerms& p, int r) {
+  if (r >= p.meta->n_rows_pad) return;
+  const bool live = r < p.meta->n_rows;
+  if constexpr (!STORED) {
+    p.row_scale[r] = live ? p.scale(r) : 0.f;
+  } else {
+    p.row_f[r] = live ? p.factor(r) : 0.f;
+    const float l2 = live ? p.lse2[r] : 0.f, zt = live ? p.ztgt[r] : 0.f;
+    if (live && !out_of_range(l2, zt)) {   // (a marked row's target entry is recomputed too)
+      const float val = (__builtin_amdgcn_exp2f(zt * kLog2e - l2) - 1.f) *
+                        __builtin_amdgcn_exp2f(l2 - exp_reference(zt));
+      const uint16_t b = (uint16_t)(pack_bf16x2(val, 0.f) & 0xFFFFu);
+      p.dZ[slab_index(p.ldz, (int64_t)p.meta->col_off + r, p.row_tgt[r])] = b;
+    }
+  }
+}
+
+// the H_c^T role: H_c^T[c][col_off + r] *= f_r (bf16, nearest even) over the
+// unit's columns up to col_end (its rows rounded up to 64), not its 256-row
+// padding: the next unit of the dW batch starts at col_end, and with every
+// sample retained its columns already hold its rows when this runs.  One
+// workgroup per 64 rows and up to kHctCols hidden units; a 64 x 64 tile is
+// 8 KB of the slab-major H_c^T.
+constexpr int kHctCols = 512;
+
+__device__ void hct_role(const RowTerms& p, int wg, float (&s_f)[64]) {
+  const int cgroups = (p.d + kHctCols - 1) / kHctCols;
+  const int r0 = wg / cgroups * 64, c0 = wg % cgroups * kHctCols;
+  if (r0 >= p.meta->col_end - p.meta->col_off) return;
   const int tid = threadIdx.x, cc = tid & 7;
+  if (tid < 64) s_f[tid] = r0 + tid < p.meta->n_rows ? p.factor(r0 + tid) : 0.f;
+  __syncthreads();
   float fr[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) fr[e] = row_f[r0 + cc * 8 + e];
-  uint16_t* base = HcT + slab_index(d, c0, (int64_t)meta->col_off + r0);
-#pragma unroll
-  for (int it = 0; it < 2; ++it) {
-    const int c = (tid >> 3) + 32 * it;
+  for (int e = 0; e < 8; ++e) fr[e] = s_f[cc * 8 + e];
+  uint16_t* base = p.HcT + slab_index(p.d, 0, (int64_t)p.meta->col_off + r0);
+  const int c1 = min(p.d, c0 + kHctCols);
+#pragma unroll 4
+  for (int c = c0 + (tid >> 3); c < c1; c += 32) {
     uint4* q = reinterpret_cast<uint4*>(base + (int64_t)c * 64 + cc * 8);
     const uint4 v = *q;
     const uint32_t w[4] = {v.x, v.y, v.z, v.w};
@@ -292,49 +294,51 @@ __global__ __launch_bounds__(256) void k_scale_hct(const float* __restrict__ row
   }
 }
 
-// The marked rows of the unit, recomputed against R2 = lse2:
-// u = 2^(z log2e - lse2) = p, and p_y - 1 at the target.  One
-// thread per vocabulary id; each workgroup scans the unit's marks 256 rows at
-// a time and takes the marked ones in batches of 16, whose fp32 logits
-// z = H_c[row] . W^T[v] it accumulates in a fixed order over d.  Without
-// marked rows it only reads the marks.
+// the role of the marked rows, recomputed against R2 = lse2:
+// u = 2^(z log2e - lse2) = p, and p_y - 1 at the target.  One thread per
+// vocabulary id; the workgroup looks for a nonzero count, then scans the
+// unit's marks 256 rows at a time and takes the marked ones in batches of 16,
+// whose fp32 logits z = H_c[row] . W^T[v] it accumulates in a fixed order over
+// d.  Without marked rows it only reads the counts.
 constexpr int kFixBatch = 16;
 
-__global__ __launch_bounds__(256) void k_fixup_rows(
-    const uint16_t* __restrict__ Hc, const uint16_t* __restrict__ WT,
-    const float* __restrict__ lse2, const float* __restrict__ ztgt,
-    const int32_t* __restrict__ row_tgt, const uint8_t* __restrict__ row_bad,
-    const SampleMeta* __restrict__ meta, uint16_t* __restrict__ dZ, int d, int V, int64_t RP,
-    int64_t ldz) {
-  __shared__ int s_list[256];
-  __shared__ int s_cnt;
-  __shared__ float s_h[kFixBatch][64];
+struct FixShared {
+  int list[256];
+  int cnt;
+  float h[kFixBatch][64];
+};
+
+__device__ void fixup_role(const RowTerms& p, int wg, FixShared& sh) {
   const int tid = threadIdx.x;
-  const int v = blockIdx.x * 256 + tid;
-  const int N = meta->n_rows;
-  const int64_t col_off = meta->col_off;
+  const int v = wg * 256 + tid;
+  const int N = p.meta->n_rows;
+  const int64_t col_off = p.meta->col_off;
+  int any = 0;
+  for (int i = tid; i * 64 < N; i += 256) any |= p.bad_count[i];
+  if (!__syncthreads_or(any)) return;
   for (int base = 0; base < N; base += 256) {
-    if (tid == 0) s_cnt = 0;
+    if (tid == 0) sh.cnt = 0;
     __syncthreads();
     const int rr = base + tid;
-    if (rr < N && row_bad[rr]) s_list[atomicAdd(&s_cnt, 1)] = rr;
+    if (rr < N && p.row_bad[rr]) sh.list[atomicAdd(&sh.cnt, 1)] = rr;
     __syncthreads();
-    const int cnt = s_cnt;
+    const int cnt = sh.cnt;
     for (int b0 = 0; b0 < cnt; b0 += kFixBatch) {
       const int nb = min(kFixBatch, cnt - b0);
       float acc[kFixBatch];
 #pragma unroll
       for (int i = 0; i < kFixBatch; ++i) acc[i] = 0.f;
-      for (int kc = 0; kc < d; kc += 64) {
+      for (int kc = 0; kc < p.d; kc += 64) {
         __syncthreads();
         for (int q = tid; q < kFixBatch * 64; q += 256) {
           const int i = q >> 6, k = q & 63;
-          s_h[i][k] = i < nb ? __uint_as_float((uint32_t)Hc[slab_index(RP, s_list[b0 + i], kc + k)] << 16)
-                             : 0.f;
+          sh.h[i][k] = i < nb ? __uint_as_float(
+                                    (uint32_t)p.Hc[slab_index(p.RP, sh.list[b0 + i], kc + k)] << 16)
+                              : 0.f;
         }
         __syncthreads();
-        if (v < V) {
-          const uint16_t* w = WT + (int64_t)v * d + kc;
+        if (v < p.V) {
+          const uint16_t* w = p.WT + (int64_t)v * p.d + kc;
           for (int kk = 0; kk < 64; kk += 8) {
             const uint4 wv = *reinterpret_cast<const uint4*>(w + kk);
             const uint32_t ww[4] = {wv.x, wv.y, wv.z, wv.w};
@@ -343,39 +347,68 @@ __global__ __launch_bounds__(256) void k_fixup_rows(
               const float w0 = __uint_as_float(ww[e] << 16), w1 = __uint_as_float(ww[e] & 0xFFFF0000u);
 #pragma unroll
               for (int i = 0; i < kFixBatch; ++i)
-                acc[i] = fmaf(w1, s_h[i][kk + 2 * e + 1], fmaf(w0, s_h[i][kk + 2 * e], acc[i]));
+                acc[i] = fmaf(w1, sh.h[i][kk + 2 * e + 1], fmaf(w0, sh.h[i][kk + 2 * e], acc[i]));
             }
           }
         }
       }
-      if (v < V) {
+      if (v < p.V) {
 #pragma unroll
         for (int i = 0; i < kFixBatch; ++i) {
           if (i >= nb) break;
-          const int r = s_list[b0 + i];
-          const float l2 = lse2[r];
-          const float val = v == row_tgt[r] ? __builtin_amdgcn_exp2f(fmaf(ztgt[r], kLog2e, -l2)) - 1.f
-                                            : __builtin_amdgcn_exp2f(fmaf(acc[i], kLog2e, -l2));
+          const int r = sh.list[b0 + i];
+          const float l2 = p.lse2[r];
+          const float val = v == p.row_tgt[r]
+                                ? __builtin_amdgcn_exp2f(fmaf(p.ztgt[r], kLog2e, -l2)) - 1.f
+                                : __builtin_amdgcn_exp2f(fmaf(acc[i], kLog2e, -l2));
           const uint16_t b = (uint16_t)(pack_bf16x2(val, 0.f) & 0xFFFFu);
-          dZ[slab_index(ldz, col_off + r, v)] = b;
+          p.dZ[slab_index(p.ldz, col_off + r, v)] = b;
         }
       }
     }
-    __syncthreads();   // s_list / s_cnt are rewritten for the next rows
+    __syncthreads();   // the list is rewritten for the next rows
   }
 }
 
-hipError_t launch_grad_scale(const Workspace& ws, int d, int V, hipStream_t s) {
-  k_grad_rows<<<(unsigned)(ws.RP / 256), 256, 0, s>>>(ws.lse2, ws.row_scale, ws.ztgt, ws.row_tgt,
-                                                      ws.unit(), ws.dZ, ws.row_f, ws.row_bad,
-                                                      ws.ldz);
-  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-  k_scale_hct<<<dim3((unsigned)(ws.RP / 64), (unsigned)(d / 64)), 256, 0, s>>>(ws.row_f, ws.unit(),
-                                                                             ws.HcT, d);
-  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-  k_fixup_rows<<<(unsigned)((V + 255) / 256), 256, 0, s>>>(ws.Hc, ws.WT, ws.lse2, ws.ztgt,
-                                                           ws.row_tgt, ws.row_bad, ws.unit(),
-                                                           ws.dZ, d, V, ws.RP, ws.ldz);
+// workgroup 0: the loss; then the row role, the H_c^T role, the marked rows
+template <bool STORED>
+__global__ __launch_bounds__(256) void k_row_terms(RowTerms p) {
+  __shared__ union {
+    float f[64];
+    FixShared fix;
+  } sh;
+  int wg = blockIdx.x;
+  if (wg == 0) {
+    if (threadIdx.x < 64) add_loss(p);
+    return;
+  }
+  wg -= 1;
+  if (wg < p.n_rows_wg) {
+    row_role<STORED>(p, wg * 256 + threadIdx.x);
+    return;
+  }
+  if constexpr (STORED) {
+    wg -= p.n_rows_wg;
+    if (wg < p.n_hct_wg)
+      hct_role(p, wg, sh.f);
+    else
+      fixup_role(p, wg - p.n_hct_wg, sh.fix);
+  }
+}
+
+hipError_t launch_row_terms(const Workspace& ws, int B, int n_t, int j0, double loss_scale,
+                            const double* g, double* loss, int d, int V, hipStream_t s) {
+  const int64_t rows = ws.g_used * ws.NP;
+  RowTerms p{ws.lse2, ws.ztgt, ws.seq_scale, ws.row_tgt, ws.row_seq, ws.bad_count, ws.row_bad,
+             ws.unit(), ws.dZ, ws.HcT, ws.Hc, ws.WT, ws.row_f, ws.row_scale, ws.ldz, ws.RP, d, V,
+             g, loss, loss_scale, B, n_t, j0, ws.g_used, (int)(rows / 256), 0};
+  if (ws.chunk) {
+    k_row_terms<false><<<(unsigned)(1 + p.n_rows_wg), 256, 0, s>>>(p);
+  } else {
+    p.n_hct_wg = (int)(rows / 64 * ((d + kHctCols - 1) / kHctCols));
+    const unsigned wgs = (unsigned)(1 + p.n_rows_wg + p.n_hct_wg + (V + 255) / 256);
+    k_row_terms<true><<<wgs, 256, 0, s>>>(p);
+  }
   return hipGetLastError();
 }
 

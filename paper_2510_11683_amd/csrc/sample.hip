@@ -480,20 +480,72 @@ hipError_t launch_masks(const uint8_t* resp, const int32_t* targets, int B, int 
 }
 
 // ---------------------------------------------------------------------------
-// Inverse RMS of the masked rows of the pre-norm activations x (for the final
-// RMSNorm h = gamma x r, r = (mean x^2 + eps)^(-1/2)): one wave per row, fp32
-// sum of squares.  Row r of the unit reads sample g = row_seq[r] / B, i.e.
-// x + g * stride.
+// Row r of a unit reads the head input of sample g = row_seq[r] / B at its
+// position, x + g * stride + idx[r] * d.
 template <typename T>
-__global__ __launch_bounds__(256) void k_row_rms(const T* __restrict__ x, int64_t stride,
-                                                 int B, const int32_t* __restrict__ idx,
-                                                 const int32_t* __restrict__ row_seq,
-                                                 const SampleMeta* __restrict__ meta,
-                                                 float* __restrict__ inv_rms, int d, float eps) {
+struct RowInput {
+  const T* x;
+  int64_t stride;
+  int B, d;
+  const int32_t *idx, *row_seq;
+  __device__ const T* row(int r) const {
+    return x + (int64_t)(row_seq[r] / B) * stride + (int64_t)idx[r] * d;
+  }
+};
+
+// The final RMSNorm of 8 elements, bf16(x * ir * gamma) (fp32 arithmetic, one
+// rounding).
+__device__ __forceinline__ uint4 norm8(uint4 v, float ir, const float* gamma) {
+  const float4 g0 = *reinterpret_cast<const float4*>(gamma);
+  const float4 g1 = *reinterpret_cast<const float4*>(gamma + 4);
+  const float gg[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
+  uint32_t a[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float lo = __uint_as_float(a[e] << 16), hi = __uint_as_float(a[e] & 0xFFFF0000u);
+    a[e] = pack_bf16x2(lo * ir * gg[2 * e], hi * ir * gg[2 * e + 1]);
+  }
+  return make_uint4(a[0], a[1], a[2], a[3]);
+}
+
+// Target logit z[row, y] = h[row] . W[:, y] by one wave: 64 lanes split the
+// d-long dot product (fp32), w the target's row of W^T; h the head input
+// (through the norm with NORM).
+template <bool NORM, typename T>
+__device__ __forceinline__ float target_logit(const T* xr, const uint16_t* w, float ir,
+                                              const float* gamma, int d, int lane) {
+  float acc = 0.f;
+  for (int k = lane * 8; k < d; k += 64 * 8) {
+    uint4 hv = load_bf16x8(xr + k);
+    if constexpr (NORM) hv = norm8(hv, ir, gamma + k);
+    const uint4 wv = *reinterpret_cast<const uint4*>(w + k);
+    const uint32_t ha[4] = {hv.x, hv.y, hv.z, hv.w}, wa[4] = {wv.x, wv.y, wv.z, wv.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      acc = fmaf(__uint_as_float(ha[e] << 16), __uint_as_float(wa[e] << 16), acc);
+      acc = fmaf(__uint_as_float(ha[e] & 0xFFFF0000u), __uint_as_float(wa[e] & 0xFFFF0000u), acc);
+    }
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+  return acc;
+}
+
+// Inverse RMS of the masked rows of the pre-norm activations x (for the final
+// RMSNorm h = gamma x r, r = (mean x^2 + eps)^(-1/2)) and the rows' target
+// logits: one wave per row, fp32 sum of squares.
+template <typename T>
+__global__ __launch_bounds__(256) void k_row_rms(RowInput<T> in, const SampleMeta* __restrict__ meta,
+                                                 const float* __restrict__ gamma, float eps,
+                                                 const uint16_t* __restrict__ WT,
+                                                 const int32_t* __restrict__ row_tgt,
+                                                 float* __restrict__ inv_rms,
+                                                 float* __restrict__ ztgt) {
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (row >= meta->n_rows) return;
-  const T* xr = x + (int64_t)(row_seq[row] / B) * stride + (int64_t)idx[row] * d;
+  const T* xr = in.row(row);
+  const int d = in.d;
   float acc = 0.f;
   for (int k = lane * 8; k < d; k += 64 * 8) {
     const uint4 v = load_bf16x8(xr + k);
@@ -507,46 +559,65 @@ __global__ __launch_bounds__(256) void k_row_rms(const T* __restrict__ x, int64_
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-  if (lane == 0) inv_rms[row] = 1.f / sqrtf(acc / (float)d + eps);
+  const float ir = 1.f / sqrtf(acc / (float)d + eps);
+  const float z = target_logit<true>(xr, WT + (int64_t)row_tgt[row] * d, ir, gamma, d, lane);
+  if (lane == 0) {
+    inv_rms[row] = ir;
+    ztgt[row] = z;
+  }
+}
+
+template <typename T>
+static RowInput<T> row_input(const void* x, int64_t stride, int B, const Workspace& ws, int d) {
+  return RowInput<T>{static_cast<const T*>(x), stride, B, d, ws.idx, ws.row_seq};
 }
 
 hipError_t launch_row_rms(const void* x, bool f32, int64_t stride, int B, const Workspace& ws,
-                          int d, float eps, hipStream_t s) {
-  const unsigned grid = (unsigned)(ws.RP / 4);
+                          const float* gamma, int d, float eps, hipStream_t s) {
+  const unsigned grid = (unsigned)(ws.g_used * ws.NP / 4);
   if (f32)
-    k_row_rms<float><<<grid, 256, 0, s>>>(static_cast<const float*>(x), stride, B, ws.idx,
-                                          ws.row_seq, ws.unit(), ws.inv_rms, d, eps);
+    k_row_rms<float><<<grid, 256, 0, s>>>(row_input<float>(x, stride, B, ws, d), ws.unit(), gamma,
+                                          eps, ws.WT, ws.row_tgt, ws.inv_rms, ws.ztgt);
   else
-    k_row_rms<uint16_t><<<grid, 256, 0, s>>>(static_cast<const uint16_t*>(x), stride, B, ws.idx,
-                                             ws.row_seq, ws.unit(), ws.inv_rms, d, eps);
+    k_row_rms<uint16_t><<<grid, 256, 0, s>>>(row_input<uint16_t>(x, stride, B, ws, d), ws.unit(),
+                                             gamma, eps, ws.WT, ws.row_tgt, ws.inv_rms, ws.ztgt);
   return hipGetLastError();
 }
 
-// Gather: Hc[r, :] = hidden_g[idx[r], :] and HcT[:, col_off + r] for the unit's
-// rows r < N (g = row_seq[r] / B: the row's sample, hidden_g = hidden + g *
-// stride); zeros for N <= r < N_pad.  Both are slab-major (Hc with RP rows
-// per slab, HcT with d), so each 64x64 tile of either is 8 KB of contiguous
-// memory; the tiles are staged in LDS for the transposed copy.  With `gamma`, `hidden` holds the pre-norm activations and
-// the gathered row is the final RMSNorm bf16(x * inv_rms[r] * gamma) (fp32
-// arithmetic, one rounding to bfloat16).  fp32 inputs are rounded to bf16
-// first (load_bf16x8), then treated the same way.
+// Gather: Hc[r, :] = h[r, :] and HcT[:, col_off + r] for the unit's rows r < N;
+// zeros for N <= r < N_pad.  Both are slab-major (Hc with RP rows per slab,
+// HcT with d), so each 64x64 tile of either is 8 KB of contiguous memory; the
+// tiles are staged in LDS for the transposed copy.  With `gamma`, the input
+// holds the pre-norm activations and the gathered row is the final RMSNorm of
+// it.  fp32 inputs are rounded to bf16 first (load_bf16x8), then treated the
+// same way.  Without the norm the launch's last workgroups (from n_tile_wg)
+// form the rows' target logits, one wave per row, straight from the input;
+// with it k_row_rms has done so.  Bound by HBM.
 template <typename T>
-__global__ __launch_bounds__(256) void k_gather(const T* __restrict__ hidden,
-                                                int64_t stride, int B,
-                                                const int32_t* __restrict__ idx,
-                                                const int32_t* __restrict__ row_seq,
-                                                const SampleMeta* __restrict__ meta,
+__global__ __launch_bounds__(256) void k_gather(RowInput<T> in, const SampleMeta* __restrict__ meta,
                                                 const float* __restrict__ gamma,
                                                 const float* __restrict__ inv_rms,
                                                 uint16_t* __restrict__ Hc,
-                                                uint16_t* __restrict__ HcT, int d, int64_t RP) {
+                                                uint16_t* __restrict__ HcT, int64_t RP,
+                                                unsigned n_tile_wg,
+                                                const uint16_t* __restrict__ WT,
+                                                const int32_t* __restrict__ row_tgt,
+                                                float* __restrict__ ztgt) {
   __shared__ uint16_t tile[64][72];
-  const int r0 = blockIdx.x * 64;
-  if (r0 >= meta->n_rows_pad) return;
+  const int tid = threadIdx.x, d = in.d;
   const int N = meta->n_rows;
+  if (blockIdx.x >= n_tile_wg) {
+    const int row = (blockIdx.x - n_tile_wg) * 4 + (tid >> 6), lane = tid & 63;
+    if (row >= N) return;
+    const float z = target_logit<false>(in.row(row), WT + (int64_t)row_tgt[row] * d, 0.f, nullptr,
+                                        d, lane);
+    if (lane == 0) ztgt[row] = z;
+    return;
+  }
+  const int cts = d / 64;
+  const int r0 = (int)(blockIdx.x / cts) * 64, c0 = (int)(blockIdx.x % cts) * 64;
+  if (r0 >= meta->n_rows_pad) return;
   const int coff = meta->col_off;
-  const int c0 = blockIdx.y * 64;
-  const int tid = threadIdx.x;
 #pragma unroll
   for (int it = 0; it < 2; ++it) {
     const int q = tid + it * 256;
@@ -554,21 +625,8 @@ __global__ __launch_bounds__(256) void k_gather(const T* __restrict__ hidden,
     const int r = r0 + row;
     uint4 v = make_uint4(0, 0, 0, 0);
     if (r < N) {
-      const T* src = hidden + (int64_t)(row_seq[r] / B) * stride + (int64_t)idx[r] * d;
-      v = load_bf16x8(src + c0 + ch * 8);
-      if (gamma) {
-        const float ir = inv_rms[r];
-        const float4 g0 = *reinterpret_cast<const float4*>(gamma + c0 + ch * 8);
-        const float4 g1 = *reinterpret_cast<const float4*>(gamma + c0 + ch * 8 + 4);
-        const float gg[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
-        uint32_t a[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float lo = __uint_as_float(a[e] << 16), hi = __uint_as_float(a[e] & 0xFFFF0000u);
-          a[e] = pack_bf16x2(lo * ir * gg[2 * e], hi * ir * gg[2 * e + 1]);
-        }
-        v = make_uint4(a[0], a[1], a[2], a[3]);
-      }
+      v = load_bf16x8(in.row(r) + c0 + ch * 8);
+      if (gamma) v = norm8(v, inv_rms[r], gamma + c0 + ch * 8);
     }
     *reinterpret_cast<uint4*>(Hc + slab_index(RP, r, c0 + ch * 8)) = v;
     *reinterpret_cast<uint4*>(&tile[row][ch * 8]) = v;
@@ -589,15 +647,17 @@ __global__ __launch_bounds__(256) void k_gather(const T* __restrict__ hidden,
 
 hipError_t launch_gather(const void* hidden, bool f32, int64_t stride, int B, const float* gamma,
                          const Workspace& ws, int d, hipStream_t s) {
-  dim3 grid((unsigned)(ws.RP / 64), (unsigned)(d / 64));
+  const int64_t rows = ws.g_used * ws.NP;
+  const unsigned tiles = (unsigned)(rows / 64 * (d / 64));
+  const unsigned grid = tiles + (gamma ? 0 : (unsigned)(rows / 4));
   if (f32)
-    k_gather<float><<<grid, 256, 0, s>>>(static_cast<const float*>(hidden), stride, B, ws.idx,
-                                         ws.row_seq, ws.unit(), gamma, ws.inv_rms, ws.Hc, ws.HcT,
-                                         d, ws.RP);
+    k_gather<float><<<grid, 256, 0, s>>>(row_input<float>(hidden, stride, B, ws, d), ws.unit(),
+                                         gamma, ws.inv_rms, ws.Hc, ws.HcT, ws.RP, tiles, ws.WT,
+                                         ws.row_tgt, ws.ztgt);
   else
-    k_gather<uint16_t><<<grid, 256, 0, s>>>(static_cast<const uint16_t*>(hidden), stride, B,
-                                            ws.idx, ws.row_seq, ws.unit(), gamma, ws.inv_rms,
-                                            ws.Hc, ws.HcT, d, ws.RP);
+    k_gather<uint16_t><<<grid, 256, 0, s>>>(row_input<uint16_t>(hidden, stride, B, ws, d),
+                                            ws.unit(), gamma, ws.inv_rms, ws.Hc, ws.HcT, ws.RP,
+                                            tiles, ws.WT, ws.row_tgt, ws.ztgt);
   return hipGetLastError();
 }
 
