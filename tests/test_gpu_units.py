@@ -157,3 +157,35 @@ def test_empty_splits_of_the_last_vocabulary_chunk(d):
     assert np.array_equal(o["ell"], q.out()["ell"])
     assert rel_maxnorm(o["dX"], ref.dX) <= 2e-2
     assert rel_maxnorm(o["dW"], ref.dW) <= 2e-2
+
+
+@pytest.mark.parametrize("n", [1, 3, 1024, 4097, (24 << 20) - 1, (24 << 20) + 5])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_moments_around_the_streaming_line(n, offset):
+    """Both forms of the moment kernels (streaming from 24 * 2^20 elements), a
+    ragged tail, and a summary of arrays off 16 bytes: the update against
+    float64 (a few fp32 roundings per element: 1e-6), the summary against
+    float64 sums of the same fp32 values (sums of positive terms: 1e-12)."""
+    b = lib()
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    g, mean, m2, ref = (torch.randn(n + offset, generator=gen, device="cuda")[offset:] for _ in range(4))
+    m2 = m2.square_()
+    if offset == 0:
+        delta = g.double() - mean.double()
+        want = mean.double() + delta / 3
+        want2 = m2.double() + delta * (g.double() - want)
+        b.bgpo_moments_update(g, mean, m2, 2)
+        assert float((mean.double() - want).norm() / want.norm()) <= 1e-6
+        assert float((m2.double() - want2).norm() / want2.norm()) <= 1e-6
+        m2.abs_()
+    out = torch.zeros(3, dtype=torch.float64, device="cuda")
+    for r in (ref, None):
+        ws = b.moments_workspace()
+        st = b._lib.bgpo_moments_summary(mean.data_ptr(), m2.data_ptr(), r.data_ptr() if r is not None else None,
+                                         n, 3, out.data_ptr(), ws.data_ptr(), ws.numel(), None)
+        torch.cuda.synchronize()
+        assert st == 0
+        exp = [(m2.double() / 2).sqrt().mean(), 0.0, 0.0]
+        if r is not None:
+            exp[1:] = (mean.double() - r.double()).abs().mean(), r.double().abs().mean()
+        np.testing.assert_allclose(out.cpu().numpy(), [float(e) for e in exp], rtol=1e-12)
