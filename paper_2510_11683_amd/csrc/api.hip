@@ -80,10 +80,9 @@ size_t workspace_layout(const Dims& dm, const Plan& pl, void* base, Workspace* w
   // of a large allocation the forward ran up to 5 % slower (measured), at
   // its head not.
   auto take_unit = [&](Workspace& w) {
-    w.meta = static_cast<SampleMeta*>(take(2 * G * sizeof(SampleMeta)));
+    w.meta = static_cast<SampleMeta*>(take(2 * G * sizeof(SampleMeta)));   // and meta2
     w.meta2 = w.meta + (b ? G : 0);
     w.idx = static_cast<int32_t*>(take(G * P * 4));
-    w.inv = static_cast<int32_t*>(take(G * P * 4));
     w.row_tgt = static_cast<int32_t*>(take(RP * 4));
     w.row_seq = static_cast<int32_t*>(take(RP * 4));
     w.seg_off = static_cast<int32_t*>(take(G * (dm.B + 1) * 4));
@@ -92,15 +91,17 @@ size_t workspace_layout(const Dims& dm, const Plan& pl, void* base, Workspace* w
     w.ztgt = static_cast<float*>(take(RP * 4));
     w.lse2 = static_cast<float*>(take(RP * 4));
     w.lp = static_cast<float*>(take(RP * 4));
-    w.row_scale = static_cast<float*>(take(RP * 4));
-    w.row_f = static_cast<float*>(take(RP * 4));
-    w.row_bad = static_cast<uint8_t*>(take(RP));
-    w.bad_count = static_cast<int32_t*>(take(RP / 64 * 4));
+    w.row_scale = w.row_f = static_cast<float*>(take(RP * 4));   // one mode uses one of them
+    w.inv = static_cast<int32_t*>(take(RP * 4));                 // G P <= RP
+    w.row_bad = static_cast<uint64_t*>(take(RP));
     w.inv_rms = static_cast<float*>(take(RP * 4));
     w.mask_scratch = take(mask_scratch_bytes(dm.B, dm.L));
     w.part_m = static_cast<float*>(take(nvt * RP * 4));
     w.part_s = static_cast<float*>(take(nvt * RP * 4));
     w.Hc = static_cast<uint16_t*>(take(RP * dm.d * 2));
+    // (the last step of a unit's backward, when its H_c has been read)
+    w.gpart = reinterpret_cast<float*>(w.Hc);
+    static_assert(kGammaRows >= 2, "dgamma's partial sums fit in H_c");
     if (chunk) w.dZ = static_cast<uint16_t*>(take(RP * chunk * 2));
   };
   Workspace w{};
@@ -108,7 +109,8 @@ size_t workspace_layout(const Dims& dm, const Plan& pl, void* base, Workspace* w
   const size_t unit_bytes = off;   // the same for every unit (all pieces 256-byte aligned)
   off = unit_bytes * n_units;
   w.dbar = static_cast<double*>(take(dm.B * 8));
-  w.gpart = static_cast<float*>(take(RP / kGammaRows * dm.d * 4));
+  take((NP / 256) * dm.d * 4);   // not used: a problem's layouts keep their sizes, so that a
+                                 // budget or the static scratch holds what it always held
   w.HcT = static_cast<uint16_t*>(take(KT * dm.d * 2));
   w.WT = static_cast<uint16_t*>(take((size_t)dm.V * dm.d * 2));
   // the slab-major bf16 W of the dX GEMM (without it the GEMM reads the

@@ -57,7 +57,7 @@ struct SampleMeta {
   int32_t dx_kslab;    // 64-wide vocabulary slabs per split
   int32_t s_rows;      // N_j: masked rows of this sample (all responses)
   int32_t s_row_off;   // first row of this sample in the unit's row space
-  int32_t pad[56];
+  int32_t pad[24];     // one 128-byte line per record
 };
 
 // Rows per partial sum of dgamma.
@@ -103,12 +103,13 @@ struct Workspace {
   float* lp;           // [RP]         log p of the target
   float* row_scale;    // [RP]         gradient scale s of each row (0 for padding)
   float* row_f;        // [RP]         stored backward: dZ row factor s 2^(R2 - lse2) (0 for padding)
-  uint8_t* row_bad;    // [RP]         stored backward: row recomputed against R2 = lse2
+  uint64_t* row_bad;   // [RP/64]      stored backward: bit r % 64 of word r / 64 marks a row
+                       //              recomputed against R2 = lse2
   double* dbar;        // [B]          mean log-ratio over all samples (exact objective)
-  int32_t* bad_count;  // [RP/64]      marked rows among each 64
   float* inv_rms;      // [RP]         final-RMSNorm 1/rms of each compacted row
   void* mask_scratch;  // mask_scratch_bytes(B, L): the multi-block mask passes
-  float* gpart;        // [RP/kGammaRows, d] dgamma partial sums over chunks of a unit's rows
+  float* gpart;        // [RP/kGammaRows, d] dgamma partial sums over chunks of a unit's rows (in H_c's
+                       //              memory, which nothing reads any more by then)
   uint16_t* dZ;        // stored mode: [KT rows, V] the forward's bf16 exponentials against
                        // the row's reference, i.e. s (softmax - onehot) up to the row factor
                        // (target entries rewritten), the units of a dW batch one after the

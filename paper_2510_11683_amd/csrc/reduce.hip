@@ -29,8 +29,8 @@ __device__ __forceinline__ bool out_of_range(float lse2, float ztgt) {
 __global__ __launch_bounds__(64 * kCombineWaves) void k_combine_rows(
     const float* __restrict__ part_m, const float* __restrict__ part_s,
     const float* __restrict__ ztgt, const SampleMeta* __restrict__ meta,
-    float* __restrict__ lse2, float* __restrict__ lp, uint8_t* __restrict__ row_bad,
-    int32_t* __restrict__ bad_count, int nvt, int64_t ldp) {
+    float* __restrict__ lse2, float* __restrict__ lp, uint64_t* __restrict__ row_bad, int nvt,
+    int64_t ldp) {
   __shared__ float sm[kCombineWaves][64], ss[kCombineWaves][64];
   const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
   const int row = blockIdx.x * 64 + lane;
@@ -71,10 +71,8 @@ __global__ __launch_bounds__(64 * kCombineWaves) void k_combine_rows(
     lse2[row] = l2;
     lp[row] = zt - l2 * kLn2;
     if (row_bad) {
-      const bool bad = out_of_range(l2, zt);
-      row_bad[row] = bad;
-      const int n = __popcll(__ballot(bad));   // (row 64 blockIdx.x is valid)
-      if (lane == 0) bad_count[blockIdx.x] = n;
+      const uint64_t bad = __ballot(out_of_range(l2, zt));   // (row 64 blockIdx.x is valid)
+      if (lane == 0) row_bad[blockIdx.x] = bad;
     }
   }
 }
@@ -82,7 +80,7 @@ __global__ __launch_bounds__(64 * kCombineWaves) void k_combine_rows(
 hipError_t launch_combine_rows(const Workspace& ws, int V, bool mark, hipStream_t s) {
   k_combine_rows<<<(unsigned)(ws.g_used * ws.NP / 64), 64 * kCombineWaves, 0, s>>>(
       ws.part_m, ws.part_s, ws.ztgt, ws.unit(), ws.lse2, ws.lp, mark ? ws.row_bad : nullptr,
-      ws.bad_count, (int)ws.nvt, ws.RP);
+      (int)ws.nvt, ws.RP);
   return hipGetLastError();
 }
 
@@ -201,8 +199,8 @@ hipError_t launch_mean_ratio(const double* ell, const double* ell_old, int B, in
 // V1024 n_t 4 62.5 -> 55.6 us, of B3 L201 d576 V4288 n_t 6 113.5 -> 106.9 us.
 struct RowTerms {
   const float *lse2, *ztgt, *seq_scale;
-  const int32_t *row_tgt, *row_seq, *bad_count;
-  const uint8_t* row_bad;
+  const int32_t *row_tgt, *row_seq;
+  const uint64_t* row_bad;
   const SampleMeta* meta;
   uint16_t *dZ, *HcT;
   const uint16_t *Hc, *WT;
@@ -296,10 +294,10 @@ __device__ void hct_role(const RowTerms& p, int wg, float (&s_f)[64]) {
 
 // the role of the marked rows, recomputed against R2 = lse2:
 // u = 2^(z log2e - lse2) = p, and p_y - 1 at the target.  One thread per
-// vocabulary id; the workgroup looks for a nonzero count, then scans the
+// vocabulary id; the workgroup looks for a nonzero mark word, then scans the
 // unit's marks 256 rows at a time and takes the marked ones in batches of 16,
 // whose fp32 logits z = H_c[row] . W^T[v] it accumulates in a fixed order over
-// d.  Without marked rows it only reads the counts.
+// d.  Without marked rows it only reads the mark words.
 constexpr int kFixBatch = 16;
 
 struct FixShared {
@@ -314,13 +312,13 @@ __device__ void fixup_role(const RowTerms& p, int wg, FixShared& sh) {
   const int N = p.meta->n_rows;
   const int64_t col_off = p.meta->col_off;
   int any = 0;
-  for (int i = tid; i * 64 < N; i += 256) any |= p.bad_count[i];
+  for (int i = tid; i * 64 < N; i += 256) any |= p.row_bad[i] != 0;
   if (!__syncthreads_or(any)) return;
   for (int base = 0; base < N; base += 256) {
     if (tid == 0) sh.cnt = 0;
     __syncthreads();
     const int rr = base + tid;
-    if (rr < N && p.row_bad[rr]) sh.list[atomicAdd(&sh.cnt, 1)] = rr;
+    if (rr < N && (p.row_bad[rr >> 6] >> (rr & 63)) & 1) sh.list[atomicAdd(&sh.cnt, 1)] = rr;
     __syncthreads();
     const int cnt = sh.cnt;
     for (int b0 = 0; b0 < cnt; b0 += kFixBatch) {
@@ -399,7 +397,7 @@ __global__ __launch_bounds__(256) void k_row_terms(RowTerms p) {
 hipError_t launch_row_terms(const Workspace& ws, int B, int n_t, int j0, double loss_scale,
                             const double* g, double* loss, int d, int V, hipStream_t s) {
   const int64_t rows = ws.g_used * ws.NP;
-  RowTerms p{ws.lse2, ws.ztgt, ws.seq_scale, ws.row_tgt, ws.row_seq, ws.bad_count, ws.row_bad,
+  RowTerms p{ws.lse2, ws.ztgt, ws.seq_scale, ws.row_tgt, ws.row_seq, ws.row_bad,
              ws.unit(), ws.dZ, ws.HcT, ws.Hc, ws.WT, ws.row_f, ws.row_scale, ws.ldz, ws.RP, d, V,
              g, loss, loss_scale, B, n_t, j0, ws.g_used, (int)(rows / 256), 0};
   if (ws.chunk) {
