@@ -665,13 +665,27 @@ hipError_t launch_gather(const void* hidden, bool f32, int64_t stride, int B, co
 // W_head [d, V] -> WT [V, d] (row-major) and, unless Wk is NULL, Wk: W in
 // slab-major order with d rows per slab (the dX GEMM's operand; each 64x64
 // tile is 8 KB of contiguous memory there).  64x64 tiles through LDS; fp32 W
-// is rounded to bf16 as it is read.
-template <typename T>
+// is rounded to bf16 as it is read.  Bound by HBM.  With NT the outputs are
+// streamed past the caches and consecutive workgroups take the k tiles of one
+// 64-id vocabulary slab, so that the rows of W^T are written whole at about the
+// same time; else they take the vocabulary tiles of one k slab.
+template <bool NT>
+__device__ __forceinline__ void store16(uint16_t* p, uint4 v) {
+  typedef uint32_t vec4u __attribute__((ext_vector_type(4)));
+  if constexpr (NT)
+    __builtin_nontemporal_store((vec4u){v.x, v.y, v.z, v.w}, reinterpret_cast<vec4u*>(p));
+  else
+    *reinterpret_cast<uint4*>(p) = v;
+}
+
+template <typename T, bool NT>
 __global__ __launch_bounds__(256) void k_transpose_w(const T* __restrict__ W,
                                                      uint16_t* __restrict__ WT,
                                                      uint16_t* __restrict__ Wk, int d, int V) {
   __shared__ uint16_t tile[64][72];
-  const int v0 = blockIdx.x * 64, k0 = blockIdx.y * 64;
+  const unsigned kts = d / 64, vts = V / 64;
+  const int v0 = (int)(NT ? blockIdx.x / kts : blockIdx.x % vts) * 64;
+  const int k0 = (int)(NT ? blockIdx.x % kts : blockIdx.x / vts) * 64;
   const int tid = threadIdx.x;
 #pragma unroll
   for (int it = 0; it < 2; ++it) {
@@ -679,7 +693,7 @@ __global__ __launch_bounds__(256) void k_transpose_w(const T* __restrict__ W,
     const int kr = q >> 3, ch = q & 7;
     const uint4 v = load_bf16x8(W + (int64_t)(k0 + kr) * V + v0 + ch * 8);
     *reinterpret_cast<uint4*>(&tile[kr][ch * 8]) = v;
-    if (Wk) *reinterpret_cast<uint4*>(Wk + slab_index(d, k0 + kr, v0 + ch * 8)) = v;
+    if (Wk) store16<NT>(Wk + slab_index(d, k0 + kr, v0 + ch * 8), v);
   }
   __syncthreads();
 #pragma unroll
@@ -690,18 +704,25 @@ __global__ __launch_bounds__(256) void k_transpose_w(const T* __restrict__ W,
 #pragma unroll
     for (int e = 0; e < 4; ++e)
       w[e] = (uint32_t)tile[kch * 8 + 2 * e][v] | ((uint32_t)tile[kch * 8 + 2 * e + 1][v] << 16);
-    *reinterpret_cast<uint4*>(WT + (int64_t)(v0 + v) * d + k0 + kch * 8) =
-        make_uint4(w[0], w[1], w[2], w[3]);
+    store16<NT>(WT + (int64_t)(v0 + v) * d + k0 + kch * 8, make_uint4(w[0], w[1], w[2], w[3]));
   }
 }
 
+// Bytes of an output of k_transpose_w from which it is streamed, well past what
+// the 256 MB last-level cache keeps for the GEMMs: 1.04 GB (d 4096 V 126464) 612
+// -> 577 us with both outputs; 0.54 GB 312 and 320, 0.13 GB 69 and 83 streamed.
+constexpr int64_t kStreamBytes = int64_t(768) << 20;
+
 hipError_t launch_transpose_w(const void* W, bool f32, uint16_t* WT, uint16_t* Wk, int d, int V,
                               hipStream_t s) {
-  dim3 grid((unsigned)(V / 64), (unsigned)(d / 64));
+  const unsigned grid = (unsigned)(V / 64) * (unsigned)(d / 64);   // at most 2^24
+  const bool nt = (int64_t)d * V * 2 >= kStreamBytes;
   if (f32)
-    k_transpose_w<float><<<grid, 256, 0, s>>>(static_cast<const float*>(W), WT, Wk, d, V);
+    (nt ? k_transpose_w<float, true> : k_transpose_w<float, false>)<<<grid, 256, 0, s>>>(
+        static_cast<const float*>(W), WT, Wk, d, V);
   else
-    k_transpose_w<uint16_t><<<grid, 256, 0, s>>>(static_cast<const uint16_t*>(W), WT, Wk, d, V);
+    (nt ? k_transpose_w<uint16_t, true> : k_transpose_w<uint16_t, false>)<<<grid, 256, 0, s>>>(
+        static_cast<const uint16_t*>(W), WT, Wk, d, V);
   return hipGetLastError();
 }
 
