@@ -21,6 +21,7 @@
 // samples (except in the retained-state contrast mode of the exact
 // objective).
 #include <math.h>
+#include <stdlib.h>
 #include <string.h>
 
 #include <algorithm>
@@ -664,6 +665,21 @@ static int elbo_fwd_impl(const bgpo_problem* prob, const Act& act, const void* W
   return BGPO_OK;
 }
 
+// Whether the slab-major copy of a bf16 W, where the plan has room for it, is
+// worth its making for a call over so many positions of its samples (else the
+// dX GEMM reads W in place).  It costs 2 d V bytes of writes, about 0.16 ms at d
+// 4096 V 126464, and makes the dX GEMM 2 % faster when that has many rows and no
+// faster when it has few.  Steps without and with the copy: 2048-4096 positions
+// 7.49 and 7.62 ms, 8192 (as 4 samples of 2048) 10.19 and 10.30, 16384 20.73 and
+// 20.77, 32768 38.49 and 38.36; d 2048 V 32000, 4096 positions 0.931 and 0.947;
+// V 65600, 2048 positions 1.51 and 1.56.  Some row pitches of W are slow in
+// place: V 66048 (129 KB) dX 677 us against 418, V 65024 (127 KB) 470 and 387, up
+// to 6 % at other pitches of 127-137 KB, and V 65536 15 %; of 60 others between 9
+// and 255 KB, 0.89 to 1.03 of the time with the copy.
+static bool copy_pays(int64_t positions, int V) {
+  return positions > 8192 || V % 1024 == 0 || std::abs(V - 65536) <= 5120;
+}
+
 // dX (and dgamma with the norm) are per sample at dX + (j - j_begin) * stride.
 static int elbo_bwd_impl(const bgpo_problem* prob, const Act& act, const void* W_head,
                          const int32_t* targets, const uint8_t* resp_mask, const float* adv,
@@ -703,6 +719,7 @@ static int elbo_bwd_impl(const bgpo_problem* prob, const Act& act, const void* W
   }
   Workspace ws;
   workspace_layout(dm, pl, workspace, &ws, nullptr);
+  if (!act.f32 && !copy_pays((int64_t)prob->j_count * ws.P, dm.V)) ws.Wk = nullptr;
   BGPO_TRY(tm.begin(BGPO_K_TRANSPOSE_W));
   BGPO_TRY(launch_transpose_w(W_head, act.f32, ws.WT, ws.Wk, dm.d, dm.V, s));
   BGPO_TRY(tm.end());

@@ -189,3 +189,28 @@ def test_moments_around_the_streaming_line(n, offset):
         if r is not None:
             exp[1:] = (mean.double() - r.double()).abs().mean(), r.double().abs().mean()
         np.testing.assert_allclose(out.cpu().numpy(), [float(e) for e in exp], rtol=1e-12)
+
+
+@pytest.mark.parametrize("B,L,V", [
+    (32, 128, 576),     # the largest call that reads W in place
+    (32, 129, 576),     # the smallest that makes the slab-major copy
+    (4, 33, 1024),      # rows a multiple of 2 KB apart: the copy at any size
+])
+def test_w_in_place_or_copied(B, L, V):
+    """The dX GEMM on the caller's row-major bf16 W and on its slab-major copy,
+    around the line between them; the call's two samples split in two calls
+    (in place) give the same dX up to the order of the fp32 sums over the
+    vocabulary splits (1e-5)."""
+    w = workloads.Workload("copy", B=B, L=L, d=192, V=V, n_t=2, adv="normal", group=4, data_seed=2400 + L,
+                           philox_seed=0xB6B60000 + L)
+    x = workloads.generate(w)
+    ref = elbo.elbo_collapsed(elbo.Problem(B, L, 192, V, 2, seed=w.philox_seed), x["hidden"], x["W"],
+                              x["targets"], x["resp_mask"], x["adv"])
+    r, q = Runner(w, x), Runner(w, x)
+    r.bwd()
+    for j in range(2):
+        q.bwd(j_begin=j, j_count=1)
+    o = r.out()
+    assert rel_maxnorm(o["dX"], ref.dX) <= 2e-2
+    assert rel_maxnorm(o["dW"], ref.dW) <= 2e-2
+    assert rel_maxnorm(q.out()["dX"], o["dX"]) <= 1e-5
