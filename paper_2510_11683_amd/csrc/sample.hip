@@ -25,14 +25,18 @@ struct MaskWalker {
   int L, j;
   int cached_b = -1, cached_blk = -1;
   u32x4 w;
-  // the Philox test of response position i of response b
-  __device__ bool test(const uint32_t* sT, int b, int i) {
+  // the counter block of response position i of response b
+  __device__ void load(int b, int i) {
     const int blk = i >> 2;
     if (blk != cached_blk || b != cached_b) {
       w = philox4x32_10(u32x4{(uint32_t)blk, seq_base + (uint32_t)b, (uint32_t)j, 0u}, k0, k1);
       cached_blk = blk;
       cached_b = b;
     }
+  }
+  // the Philox test of response position i of response b
+  __device__ bool test(const uint32_t* sT, int b, int i) {
+    load(b, i);
     return (pick_word(w, i & 3) >> 8) < sT[b];
   }
 };
@@ -105,31 +109,42 @@ __device__ void write_record(SampleMeta* m, int row0, int col0, int total, const
 // in LDS, kSpan positions at a time (all of them up to kSingleBlockPositions;
 // only the mask-only entry point goes beyond), every thread a contiguous run
 // of at most 64 positions whose mask bits stay in a register between the
-// count and the output, one block-wide scan.  Bound by the Philox arithmetic
-// of one compute unit and by latency.  The first row of a sample follows from
-// the mask counts of the unit's earlier samples, which every workgroup counts
-// again for itself (one Philox block per four positions), so that the samples
-// of a unit run side by side in one launch.  Against one launch per sample: a
-// whole step of 4 samples of 128 positions 117 -> 99 us, of 6 samples of 603
-// positions 192 -> 171 us.
+// count and the output, one block-wide scan.  The first row of a sample follows
+// from the mask counts of the unit's earlier samples, which every workgroup
+// counts again for itself (one Philox block per four positions, the runs of
+// all earlier samples spread over the threads), so that the samples of a unit
+// run side by side in one launch.  Against one launch per sample: a whole step
+// of 4 samples of 128 positions 117 -> 99 us, of 6 samples of 603 positions
+// 192 -> 171 us.
+//
+// Bound by the Philox arithmetic of one compute unit and by a chain of
+// latencies, so whatever does not need the timesteps is in flight before the
+// barrier that publishes them (the first run's response mask, targets and
+// Philox block), and the unit's record is written by the last wave while the
+// others write rows: one sample of 4096 positions 7.6 -> 6.5 us, a unit of 4
+// samples of 128 positions 10.8 -> 8.2, of 6 of 603 15.4 -> 11.4.
 constexpr int kSpan = 64 * kMaskThreads;
 static_assert(kSingleBlockPositions <= kSpan, "one span per sample in a unit");
 
-// The mask bits of positions p0 .. p1 - 1 (at most 64): response position i0
-// of response b0 onwards.  p0 is a multiple of 4, so that the response-mask
-// bytes load four at a time.
-__device__ __forceinline__ uint64_t mask_run(MaskWalker& mw, const uint8_t* resp,
-                                             const uint32_t* sT, int p0, int p1, int b, int i) {
-  const bool words = ((uintptr_t)resp & 3) == 0;
+// The response-mask bytes of positions p .. min(p + 4, p1) - 1 (p a multiple of
+// 4; `words`: the mask is 4-byte aligned).
+__device__ __forceinline__ uint32_t resp_word(const uint8_t* resp, int p, int p1, bool words) {
+  if (words && p + 4 <= p1) return *reinterpret_cast<const uint32_t*>(resp + p);
+  uint32_t r4 = 0;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) r4 |= p + e < p1 ? (uint32_t)resp[p + e] << (8 * e) : 0u;
+  return r4;
+}
+
+// The mask bits of positions p0 .. p1 - 1 (at most 64): response position i
+// of response b onwards.  p0 is a multiple of 4, so that the response-mask
+// bytes load four at a time; r4 holds the first four.
+__device__ __forceinline__ uint64_t mask_run(MaskWalker& mw, const uint8_t* resp, bool words,
+                                             const uint32_t* sT, int p0, int p1, int b, int i,
+                                             uint32_t r4) {
   uint64_t bits = 0;
   for (int p = p0; p < p1; p += 4) {
-    uint32_t r4 = 0;
-    if (words && p + 4 <= p1) {
-      r4 = *reinterpret_cast<const uint32_t*>(resp + p);
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) r4 |= p + e < p1 ? (uint32_t)resp[p + e] << (8 * e) : 0u;
-    }
+    if (p > p0) r4 = resp_word(resp, p, p1, words);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       if (p + e < p1) {
@@ -144,6 +159,18 @@ __device__ __forceinline__ uint64_t mask_run(MaskWalker& mw, const uint8_t* resp
   return bits;
 }
 
+// Inclusive sum over the lanes of a wave (data-parallel moves inside and across
+// the rows of 16 lanes: no LDS round trips).
+__device__ __forceinline__ int wave_inclusive_sum(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast:15 into rows 1, 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // row_bcast:31 into rows 2, 3
+  return v;
+}
+
 __global__ __launch_bounds__(kMaskThreads) void k_mask_compact(
     const uint8_t* __restrict__ resp, const int32_t* __restrict__ targets, int B, int L, int n_t,
     int j0, int t_mode, uint32_t k0, uint32_t k1, uint32_t seq_base, MaskOut out,
@@ -156,48 +183,66 @@ __global__ __launch_bounds__(kMaskThreads) void k_mask_compact(
   const int lane = tid & 63, wave = tid >> 6;
   const int g = blockIdx.x;
   const int P = B * L;
+  const bool words = ((uintptr_t)resp & 3) == 0;
+
+  // this thread's run of the first span
+  int n = min(kSpan, P);
+  int chunk = ((n + kMaskThreads - 1) / kMaskThreads + 3) & ~3;
+  int p0 = min(n, tid * chunk), p1 = min(n, p0 + chunk);
+  int b0 = p0 / L, i0 = p0 - b0 * L;
+  uint32_t r4 = resp_word(resp, p0, p1, words);
+  int32_t tgt[4] = {0, 0, 0, 0};
+  const bool tgt_ahead = chunk == 4 && out.row_tgt;   // (targets of longer runs are read when written)
+  if (tgt_ahead)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (p0 + e < p1) tgt[e] = targets[p0 + e];
+  // the unit's columns follow the previous unit's of the dW batch
+  const int col0 = prev ? prev->col_end : 0;
+  MaskWalker mw{k0, k1, seq_base, L, j0 + g};
 
   // counts of the unit's earlier samples, then this sample's timesteps at
   // sT + t_base
   int earlier = 0, t_base = 0;
   const int per = kMaxB / B;
+  const int n_runs = (n + chunk - 1) / chunk;
   for (int q0 = 0; q0 <= g; q0 += per) {
     const int nq = min(per, g + 1 - q0);
     if (q0) __syncthreads();          // the previous samples' timesteps are done with
-    for (int e = tid; e < nq * B; e += kMaskThreads)
-      sT[e] = timestep_t24(k0, k1, seq_base + (uint32_t)(e % B), j0 + q0 + e / B, n_t, t_mode);
+    for (int e = tid; e < nq * B; e += kMaskThreads) {
+      const int q = e / B;
+      sT[e] = timestep_t24(k0, k1, seq_base + (uint32_t)(e - q * B), j0 + q0 + q, n_t, t_mode);
+    }
+    if (q0 == 0 && r4) mw.load(b0, i0);
     __syncthreads();
-    for (int q = 0; q < nq; ++q) {
-      t_base = q * B;
-      if (q0 + q == g) break;
-      MaskWalker mw{k0, k1, seq_base, L, j0 + q0 + q};
-      const int chunk = ((P + kMaskThreads - 1) / kMaskThreads + 3) & ~3;
-      const int p0 = min(P, tid * chunk), p1 = min(P, p0 + chunk);
-      earlier += __popcll(mask_run(mw, resp, sT + t_base, p0, p1, p0 / L, p0 % L));
+    t_base = (nq - 1) * B;
+    const int n_earlier = min(nq, g - q0);
+    for (int e = tid; e < n_earlier * n_runs; e += kMaskThreads) {
+      const int q = e / n_runs, c0 = (e - q * n_runs) * chunk, c1 = min(n, c0 + chunk);
+      const int b = c0 / L;
+      MaskWalker me{k0, k1, seq_base, L, j0 + q0 + q};
+      earlier += __popcll(mask_run(me, resp, words, sT + q * B, c0, c1, b, c0 - b * L,
+                                   resp_word(resp, c0, c1, words)));
     }
   }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) earlier += __shfl_xor(earlier, off, 64);
-  if (lane == 0) sEarlier[wave] = earlier;
-  // the unit's columns follow the previous unit's of the dW batch
-  const int col0 = prev ? prev->col_end : 0;
+  earlier = wave_inclusive_sum(earlier);
+  if (lane == 63) sEarlier[wave] = earlier;
 
-  MaskWalker mw{k0, k1, seq_base, L, j0 + g};
   int row0 = 0, total = 0;
   for (int s0 = 0; s0 < P; s0 += kSpan) {
-    const int n = min(kSpan, P - s0);
-    const int chunk = ((n + kMaskThreads - 1) / kMaskThreads + 3) & ~3;
-    const int p0 = s0 + min(n, tid * chunk), p1 = min(s0 + n, p0 + chunk);
-    const int b0 = p0 / L;
-    const uint64_t bits = mask_run(mw, resp, sT + t_base, p0, p1, b0, p0 - b0 * L);
+    if (s0) {
+      n = min(kSpan, P - s0);
+      chunk = ((n + kMaskThreads - 1) / kMaskThreads + 3) & ~3;
+      p0 = s0 + min(n, tid * chunk);
+      p1 = min(s0 + n, p0 + chunk);
+      b0 = p0 / L;
+      i0 = p0 - b0 * L;
+      r4 = resp_word(resp, p0, p1, words);
+    }
+    const uint64_t bits = mask_run(mw, resp, words, sT + t_base, p0, p1, b0, i0, r4);
     const int cnt = __popcll(bits);
     // block-wide exclusive scan of the per-thread counts
-    int incl = cnt;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int v = __shfl_up(incl, off, 64);
-      if (lane >= off) incl += v;
-    }
+    const int incl = wave_inclusive_sum(cnt);
     if (s0) __syncthreads();          // the previous span's wave sums are done with
     if (lane == 63) sWave[wave] = incl;
     __syncthreads();
@@ -210,7 +255,7 @@ __global__ __launch_bounds__(kMaskThreads) void k_mask_compact(
       row0 += s0 ? 0 : sEarlier[q];
     }
     // offsets of the responses that start in this thread's run
-    for (int b = (p0 + L - 1) / L; b < B && b * L < p1; ++b)
+    for (int b = b0 + (i0 > 0); b < B && b * L < p1; ++b)
       sSeg[b] = base + __popcll(bits & ((1ull << (b * L - p0)) - 1));
     if (out.inv) {
       int32_t* const inv = out.inv + (int64_t)g * P;
@@ -219,17 +264,19 @@ __global__ __launch_bounds__(kMaskThreads) void k_mask_compact(
     }
     int b = b0, r = row0 + base;
     for (uint64_t m = bits; m; m &= m - 1, ++r) {
-      const int p = p0 + __builtin_ctzll(m);
+      const int o = __builtin_ctzll(m), p = p0 + o;
       out.idx[r] = p;
       if (out.row_tgt) {
         // ids outside [0, V) are clamped so that no kernel reads outside W
-        const int y = targets[p];
+        const int y = !tgt_ahead ? targets[p] : o == 0 ? tgt[0] : o == 1 ? tgt[1] : o == 2 ? tgt[2] : tgt[3];
         out.row_tgt[r] = y < 0 ? 0 : (y >= V ? V - 1 : y);
         while (p >= (b + 1) * L) ++b;
         out.row_seq[r] = g * B + b;
       }
     }
   }
+  if (wave == kMaskThreads / 64 - 1)
+    write_record(out.meta ? out.meta + g : nullptr, row0, col0, total, plan, lane);
   if (tid == 0) sSeg[B] = total;
   __syncthreads();
 
@@ -242,7 +289,6 @@ __global__ __launch_bounds__(kMaskThreads) void k_mask_compact(
     if (out.t24) out.t24[g * B + b] = T;
   }
   if (tid == 0 && out.seg_off) out.seg_off[g * (B + 1) + B] = rows;
-  if (wave == 0) write_record(out.meta ? out.meta + g : nullptr, row0, col0, total, plan, lane);
   // the last sample pads the unit's rows up to the next row tile
   if (g == (int)gridDim.x - 1 && out.row_tgt) {
     const int pad_end = min((rows + kRowPad - 1) / kRowPad * kRowPad, out.row_cap);
