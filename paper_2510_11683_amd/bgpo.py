@@ -150,6 +150,10 @@ class Problem:
 
 
 def _ptr(t: Optional[torch.Tensor], name: str, dtypes=None, shape=None, allow_none=False):
+    """The device address of a checked tensor (an integer, or None)."""
+    if (t is not None and t.is_cuda and t.is_contiguous() and (dtypes is None or t.dtype in dtypes) and
+            (shape is None or t.shape == shape)):
+        return t.data_ptr()
     if t is None:
         if allow_none:
             return None
@@ -162,7 +166,7 @@ def _ptr(t: Optional[torch.Tensor], name: str, dtypes=None, shape=None, allow_no
         raise ValueError(f"{name} has dtype {t.dtype}, expected one of {dtypes}")
     if shape is not None and tuple(t.shape) != tuple(shape):
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 _BF16 = (torch.bfloat16, torch.int16, torch.uint16)
@@ -174,8 +178,9 @@ def _in_types(prob: "Problem"):
 
 
 def _stream(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is None:   # the current device's current stream, without a Stream object
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def bgpo_version() -> int:

@@ -202,17 +202,12 @@ static double recompute_cost(const Dims& dm, const Plan& pl) {
 // (the dX GEMM at the best split the capacity allows, about 2 % faster on
 // the slab-major copy of W), the forward's stores of the kept exponentials
 // (2 bytes per entry) and the dW read-modify-write once per batch of units.
-static double stored_cost(const Dims& dm, const Plan& pl) {
+// fwd_fill, dx_fill: the forward's and the dX GEMM's grid fills.
+static double stored_cost(const Dims& dm, const Plan& pl, double fwd_fill, double dx_fill) {
   const double NP = (double)padded_positions(dm);
-  const double rows = pl.G * NP;
-  const double col_t = std::ceil(dm.d / 256.0);
-  double dx_fill = 0.0;
-  for (int64_t sp = 1; sp <= pl.n_split; ++sp)
-    dx_fill = std::max(dx_fill, mean_fill(rows, col_t, (double)sp));
   const double pass = 2.0 * NP * 0.5 * dm.d * (double)dm.V / 1.35e15;
   const double dx_rate = pl.w_copy ? 0.98 : 1.0;
-  const double gemm =
-      pass * (1.0 / mean_fill(rows, std::ceil(dm.V / 256.0), 1.0) + dx_rate / dx_fill + 1.0);
+  const double gemm = pass * (1.0 / fwd_fill + dx_rate / dx_fill + 1.0);
   const double mem = (2.0 * NP * 0.5 * dm.V + (double)dm.V * dm.d * 8.0 / (pl.G * pl.dw_batch)) / 5e12;
   return gemm + mem;
 }
@@ -248,15 +243,29 @@ static int choose_plan(const bgpo_problem* p, Plan* out) {
     bool found = false;
     Plan best{};
     double best_cost = 0.0;
+    // Every call on a budget runs this search before it launches anything, so
+    // the fills are formed once per unit size and the splits that fit follow
+    // from the size of one split's partials (58 us -> 2 us of host time at B3
+    // L201 d576 V4288 in 128 MiB, where the whole step takes 106).
     for (int64_t G = max_unit(dm); G >= 1; --G) {
+      const double rows = (double)(G * NP), col_t = std::ceil(p->d / 256.0);
+      const int64_t split_bytes = G * NP * p->d * 4;   // (a multiple of the layout's alignment)
+      const int64_t ns_max = std::max<int64_t>(1, std::min<int64_t>(kMaxDxSplit, 4 * kGiB / split_bytes));
+      const double fwd_fill = mean_fill(rows, std::ceil(dm.V / 256.0), 1.0);
+      double dx_fill[kMaxDxSplit + 1] = {0.0};         // the best fill of up to ns splits
+      for (int64_t ns = 1; ns <= ns_max; ++ns)
+        dx_fill[ns] = std::max(dx_fill[ns - 1], mean_fill(rows, col_t, (double)ns));
       for (int64_t dwb = kDwUnits; dwb >= 1; --dwb) {
         if (dwb * G * NP > kMaxColumns) continue;
-        const int64_t ns_max = std::max<int64_t>(1, std::min<int64_t>(16, 4 * kGiB / (G * NP * p->d * 4)));
         for (int wc = 1; wc >= f32; --wc) {   // with and (bf16 inputs) without the W copy
-          for (int64_t ns = 1; ns <= ns_max; ++ns) {
-            const Plan pl{G, dwb, ns, 0, 0, wc};
-            if (plan_bytes(dm, pl) > budget) break;   // more splits only take more memory
-            const double c = stored_cost(dm, pl);
+          Plan pl{G, dwb, 1, 0, 0, wc};
+          const size_t one = plan_bytes(dm, pl);
+          if (one > budget) continue;
+          const int64_t ns_fit = (int64_t)std::min<uint64_t>(ns_max, 1 + (budget - one) / split_bytes);
+          for (int64_t ns = 1; ns <= ns_fit; ++ns) {
+            if (dx_fill[ns] == dx_fill[ns - 1]) continue;   // no better than with one split less
+            pl.n_split = ns;
+            const double c = stored_cost(dm, pl, fwd_fill, dx_fill[ns]);
             if (!found || c < best_cost) {
               found = true;
               best = pl;
