@@ -420,13 +420,14 @@ struct Act {
 };
 
 // forward part of the unit of samples j0 .. j0 + n_s - 1: masks .. l (and,
-// with backward, g / loss / scale); prev_unit: record of the previous unit of
-// the dW batch (NULL for the first)
+// with backward, g / loss / scale); dw_units: the units of the dW batch that
+// this unit ends (0: none); prev_unit: record of the previous unit of the dW
+// batch (NULL for the first)
 static int run_forward_unit(const bgpo_problem* p, Workspace& ws, Timer& tm, int grid, int j0,
                             int n_s, const Act& act, const int32_t* targets, const uint8_t* resp,
                             const float* adv, const double* ell_old, double loss_scale,
                             double* ell, double* g, int32_t* n_masked, float* t_out,
-                            int32_t* flags, bool backward, bool store_u,
+                            int32_t* flags, bool backward, bool store_u, int dw_units,
                             const SampleMeta* prev_unit, const double* dbar, hipStream_t s) {
   const Dims dm = dims_of(p);
   ws.g_used = n_s;
@@ -434,7 +435,7 @@ static int run_forward_unit(const bgpo_problem* p, Workspace& ws, Timer& tm, int
   BGPO_TRY(launch_masks(resp, targets, dm.B, dm.L, dm.n_t, j0, n_s, p->t_mode, p->seed,
                         p->seq_id_base, &ws, nullptr, n_masked + j0, dm.n_t,
                         t_out ? t_out + j0 : nullptr, dm.n_t, dm.V, prev_unit,
-                        dx_plan(ws, dm.d, dm.V, grid), ws.mask_scratch, false, s));
+                        dx_plan(ws, dm.d, dm.V, grid, dw_units), ws.mask_scratch, false, s));
   BGPO_TRY(tm.end(n_s));
   BGPO_TRY(tm.begin(BGPO_K_GATHER));
   if (act.gamma)
@@ -547,17 +548,23 @@ namespace bgpo {
 // dW[:, chunk] accumulated.  Then each sample's rows are added into dX in
 // sample order (with the norm backward).  W: the caller's W_head (bf16
 // inputs), read by the dX GEMM when the plan keeps no slab-major copy.
+// dw_units > 0: the unit ends a dW batch of so many units, and its dW GEMM runs
+// here, beside the dX GEMM or last.
 static int unit_backward(const Workspace& ws, const Act& act, int j0, int j_begin,
                          const uint16_t* W, double loss_scale, const double* g, double* loss,
-                         float* dX, float* dgamma, float* dW, const Dims& dm, int grid, Timer& tm,
-                         hipStream_t s) {
+                         float* dX, float* dgamma, float* dW, const Dims& dm, int grid,
+                         int dw_units, Timer& tm, hipStream_t s) {
   // (one launch; in the stored mode it does the three steps of its class)
   BGPO_TRY(tm.begin(ws.chunk ? BGPO_K_ELL : BGPO_K_SOFTMAX_GRAD));
   BGPO_TRY(launch_row_terms(ws, dm.B, dm.n_t, j0, loss_scale, g, loss, dm.d, dm.V, s));
   BGPO_TRY(tm.end(ws.chunk ? 0 : 3));
+  bool paired = false;
   if (!ws.chunk) {
     BGPO_TRY(tm.begin(BGPO_K_DX));
-    BGPO_TRY(launch_gemm_dx(ws, W, dm.d, dm.V, grid, s));
+    if (dw_units)
+      BGPO_TRY(launch_gemm_dx_dw(ws, W, dW, dm.d, dm.V, grid, dw_units, s, &paired));
+    else
+      BGPO_TRY(launch_gemm_dx(ws, W, dm.d, dm.V, grid, s));
     BGPO_TRY(tm.end());
   } else {
     for (int v0 = 0; v0 < dm.V; v0 += (int)ws.chunk) {
@@ -581,6 +588,11 @@ static int unit_backward(const Workspace& ws, const Act& act, int j0, int j_begi
   else
     BGPO_TRY(launch_dx_reduce(ws, dm.B, dXj, act.stride, dm.d, s));
   BGPO_TRY(tm.end(ws.g_used * (act.gamma ? 3 : 1)));   // the norm backward is 3 kernels
+  if (dw_units) {
+    BGPO_TRY(tm.begin(BGPO_K_DW));
+    if (!paired) BGPO_TRY(launch_gemm_dw(ws, dW, dm.d, dm.V, grid, s));
+    BGPO_TRY(tm.end());
+  }
   return BGPO_OK;
 }
 
@@ -608,7 +620,7 @@ static int bwd_retained(const bgpo_problem* prob, const Plan& pl, const Act& act
     const int j0 = u * G, n_s = std::min(G, dm.n_t - j0);
     const int st = run_forward_unit(prob, U[u], tm, grid, j0, n_s, act, targets, resp_mask,
                                     nullptr, nullptr, 0.0, ell, nullptr, n_masked, t_out,
-                                    status_flags, false, true, u ? U[u - 1].unit() : nullptr,
+                                    status_flags, false, true, 0, u ? U[u - 1].unit() : nullptr,
                                     nullptr, s);
     if (st != BGPO_OK) return st;
   }
@@ -627,7 +639,7 @@ static int bwd_retained(const bgpo_problem* prob, const Plan& pl, const Act& act
     BGPO_TRY(tm.end());
     const int st = unit_backward(U[u], act, j0, 0, static_cast<const uint16_t*>(W_head),
                                  loss_scale, g, loss, dX,
-                                 dgamma, dW, dm, grid, tm, s);
+                                 dgamma, dW, dm, grid, 0, tm, s);
     if (st != BGPO_OK) return st;
   }
   BGPO_TRY(tm.begin(BGPO_K_DW));
@@ -666,7 +678,7 @@ static int elbo_fwd_impl(const bgpo_problem* prob, const Act& act, const void* W
   for (int j0 = prob->j_begin; j0 < j_end; j0 += (int)ws.G) {
     const int n_s = std::min<int>(j_end - j0, (int)ws.G);
     st = run_forward_unit(prob, ws, tm, grid, j0, n_s, act, targets, resp_mask, nullptr, nullptr,
-                          0.0, ell, nullptr, n_masked, t_out, nullptr, false, false,
+                          0.0, ell, nullptr, n_masked, t_out, nullptr, false, false, 0,
                           nullptr, nullptr, s);
     if (st != BGPO_OK) return st;
   }
@@ -740,7 +752,7 @@ static int elbo_bwd_impl(const bgpo_problem* prob, const Act& act, const void* W
       const int n_s = std::min<int>(prob->n_t - j0, (int)ws.G);
       st = run_forward_unit(prob, ws, tm, grid, j0, n_s, act, targets, resp_mask, nullptr, nullptr,
                             0.0, ell, nullptr, n_masked, t_out, status_flags, false,
-                            false, nullptr, nullptr, s);
+                            false, 0, nullptr, nullptr, s);
       if (st != BGPO_OK) return st;
     }
     BGPO_TRY(tm.begin(BGPO_K_ELL));
@@ -759,23 +771,21 @@ static int elbo_bwd_impl(const bgpo_problem* prob, const Act& act, const void* W
     // writes this unit's: the two take turns in two sets of records
     const SampleMeta* prev = in_batch ? last : nullptr;
     std::swap(ws.meta, ws.meta2);
+    // stored mode: one dW GEMM per batch of units, K over all their rows (the
+    // recompute mode accumulates dW chunk by chunk)
+    ++in_batch;
+    const bool ends_batch = !ws.chunk && (in_batch == (int)ws.dw_batch || j0 + n_s >= j_end);
+    const int dw_units = ends_batch ? in_batch : 0;
     st = run_forward_unit(prob, ws, tm, grid, j0, n_s, act, targets, resp_mask, adv, ell_old,
                           loss_scale, ell, g, n_masked, t_out, status_flags, true, store_u,
-                          prev, dbar, s);
+                          dw_units, prev, dbar, s);
     if (st != BGPO_OK) return st;
     st = unit_backward(ws, act, j0, prob->j_begin, static_cast<const uint16_t*>(W_head),
                        loss_scale, g, loss, dX,
-                       dgamma, dW, dm, grid, tm, s);
+                       dgamma, dW, dm, grid, dw_units, tm, s);
     if (st != BGPO_OK) return st;
     last = ws.unit();
-    // stored mode: one dW GEMM per batch of units, K over all their rows (the
-    // recompute mode accumulated dW chunk by chunk)
-    if (!ws.chunk && (++in_batch == (int)ws.dw_batch || j0 + n_s >= j_end)) {
-      BGPO_TRY(tm.begin(BGPO_K_DW));
-      BGPO_TRY(launch_gemm_dw(ws, dW, dm.d, dm.V, grid, s));
-      BGPO_TRY(tm.end());
-      in_batch = 0;
-    }
+    if (ends_batch || ws.chunk) in_batch = 0;
   }
   BGPO_TRY(tm.finish());
   return BGPO_OK;

@@ -228,8 +228,10 @@ __device__ __forceinline__ void epi_f32_16t(const f32x4 (&acc)[TM][TN], float* o
   }
 }
 
+// The work of workgroup w of the G that walk the tiles of p; smem holds the
+// ring, STAGES * (BM + BN) * 128 bytes.
 template <int EPI, int AL, int BM, int BN, int BK, int STAGES, int WN>
-__global__ __launch_bounds__(256, 1) void k_gemm4w(GemmParams p) {
+__device__ __forceinline__ void gemm4w(const GemmParams& p, uint4* smem, uint32_t w, uint32_t G) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass needs only the signature
   constexpr int WM = 128;
   using C = Cfg<BM, BN, BK, WM, WN>;
@@ -243,7 +245,6 @@ __global__ __launch_bounds__(256, 1) void k_gemm4w(GemmParams p) {
   // waves that share the load of one 64-wide M slab of A
   constexpr int WPS = C::NWAVES / (BM / 64);
   static_assert(!kMSlabA || WPS * (BM / 64) == C::NWAVES, "whole waves per M slab of A");
-  __shared__ uint4 smem[STAGES * (BM + BN) * KCH];
   uint4* As = smem;                           // [STAGES][BM][KCH]
   uint4* Bs = smem + STAGES * BM * KCH;       // [STAGES][BN][KCH]
 
@@ -278,8 +279,6 @@ __global__ __launch_bounds__(256, 1) void k_gemm4w(GemmParams p) {
   const uint32_t total = __builtin_amdgcn_readfirstlane(per_split * (uint32_t)n_split);
   const uint32_t GM = __builtin_amdgcn_readfirstlane(max(1, min(p.group_m, (int)tilesM)));
   const uint32_t band_tiles = GM * tilesN;
-  const uint32_t G = gridDim.x;
-  const uint32_t w = blockIdx.x;
   const uint32_t xcd_slot = G % 8 == 0 ? (w % 8) * (G / 8) + w / 8 : w;
 
   for (uint32_t t = xcd_slot; t < total; t += G) {
@@ -658,6 +657,26 @@ __global__ __launch_bounds__(256, 1) void k_gemm4w(GemmParams p) {
 #endif
 }
 
+template <int EPI, int AL, int BM, int BN, int BK, int STAGES, int WN>
+__global__ __launch_bounds__(256, 1) void k_gemm4w(GemmParams p) {
+  __shared__ uint4 smem[STAGES * (BM + BN) * (BK / 8)];
+  gemm4w<EPI, AL, BM, BN, BK, STAGES, WN>(p, smem, blockIdx.x, gridDim.x);
+}
+
+// Two GEMMs that do not depend on each other (the dX GEMM of a unit and the dW
+// GEMM of the batch it ends) in one launch: the first n_dx workgroups (a
+// multiple of 8, so that both keep their XCDs) walk the tiles of dX, the others
+// those of dW.
+template <int AL, int BM, int BN, int BK, int STAGES, int WN>
+__global__ __launch_bounds__(256, 1) void k_gemm4w_dx_dw(GemmParams dx, GemmParams dw, uint32_t n_dx) {
+  __shared__ uint4 smem[STAGES * (BM + BN) * (BK / 8)];
+  if (blockIdx.x < n_dx)
+    gemm4w<EPI_F32_STORE, AL, BM, BN, BK, STAGES, WN>(dx, smem, blockIdx.x, n_dx);
+  else
+    gemm4w<EPI_F32_ACCUM, A_MSLAB, BM, BN, BK, STAGES, WN>(dw, smem, blockIdx.x - n_dx,
+                                                           gridDim.x - n_dx);
+}
+
 // Tile configuration of the production kernels (k_gemm4w): 256x256 block
 // tile, K slab 64 in a 2-stage LDS ring, four waves of 128x128, 256-byte LDS
 // swizzle.
@@ -752,14 +771,36 @@ static bool dx_small_tiles(const Workspace& ws, int d, int V, int grid) {
   return w128 < 3 * w256 + 24 * (int64_t)grid;
 }
 
-DxPlan dx_plan(const Workspace& ws, int d, int V, int grid) {
-  const bool small = dx_small_tiles(ws, d, V, grid);
-  const int e = small ? 128 : 256;
-  return DxPlan{(int)(dx_k(ws, V) / 64), (d + e - 1) / e, grid, (int)ws.n_split, e, small ? 26 : 13};
+// Workgroups of the dX GEMM when it shares a launch with the dW GEMM of a batch
+// of `units` units, 0 when the two run one after the other.  Both must be small
+// (128-wide tiles, dW's within kPairRounds rounds): alone, each leaves a part of
+// the chip idle and pays a launch.  The grid is shared by the slabs of their
+// tiles, with about 8 slabs' time to load and store a dW tile.  One after the
+// other against together: B2 L64 d128 V1024 n_t 4 (8 dW tiles) 54 us a step
+// against 45, B3 L201 d576 V4288 n_t 6 (170) 102 and 91, B8 L512 d256 V4096 n_t 16
+// (64) 719 and 647, B2 L100 d640 V12800 n_t 16 (500) 214 and 205; with two whole
+// rounds of dW (512 tiles, B2 L256 d1024 V8192 n_t 4) 142 and 142.
+constexpr int64_t kPairRounds = 4;
+
+static int pair_dx_workgroups(const Workspace& ws, int d, int V, int grid, int units) {
+  if (ws.chunk || !small_tiles(V, d, grid) || !dx_small_tiles(ws, d, V, grid) ||
+      rounds(V, d, 128, grid) > kPairRounds || grid < 64)
+    return 0;
+  const int64_t rows = rows_estimate(ws), cols = (d + 127) / 128;
+  const double dx = (double)(cols * ((rows + 127) / 128) * (V / 64));
+  const double dw = (double)(cols * ((V + 127) / 128) * (units * rows / 64 + 8));
+  return std::max(8, std::min(grid / 8 * 8 - 8, (int)(grid * dx / (dx + dw) / 8.0 + 0.5) * 8));
 }
 
-hipError_t launch_gemm_dx(const Workspace& ws, const uint16_t* W, int d, int V, int grid,
-                          hipStream_t s) {
+DxPlan dx_plan(const Workspace& ws, int d, int V, int grid, int units) {
+  const bool small = dx_small_tiles(ws, d, V, grid);
+  const int e = small ? 128 : 256;
+  const int n_dx = units ? pair_dx_workgroups(ws, d, V, grid, units) : 0;
+  return DxPlan{(int)(dx_k(ws, V) / 64), (d + e - 1) / e, n_dx ? n_dx : grid, (int)ws.n_split, e,
+                small ? 26 : 13};
+}
+
+static GemmParams dx_params(const Workspace& ws, const uint16_t* W, int d, int V) {
   // dX^T[c][row] = W[c][:] . dZ[row][:] over the unit's rows of dZ, stored
   // transposed: dx_part[row][c]
   GemmParams p = base_params();
@@ -773,12 +814,10 @@ hipError_t launch_gemm_dx(const Workspace& ws, const uint16_t* W, int d, int V, 
   p.dyn_split = 1;
   p.group_m = kGroupMdX;
   p.out = ws.dx_part; p.ldo = d; p.split_stride = ws.RP * d;
-  const bool small = dx_small_tiles(ws, d, V, grid);
-  if (ws.Wk) return launch_tiled<EPI_F32_STORE, A_KSLAB>(small, grid, p, s);
-  return launch_tiled<EPI_F32_STORE, A_ROW>(small, grid, p, s);
+  return p;
 }
 
-hipError_t launch_gemm_dw(const Workspace& ws, float* dW, int d, int V, int grid, hipStream_t s) {
+static GemmParams dw_params(const Workspace& ws, float* dW, int d, int V) {
   // dW^T[v][c] += dZ[:][v] . H_c^T[c][:] over the batch's rows (dZ read
   // M-slab-major)
   GemmParams p = base_params();
@@ -787,7 +826,32 @@ hipError_t launch_gemm_dw(const Workspace& ws, float* dW, int d, int V, int grid
   p.M = V; p.N = d; p.dyn_k = 1; p.meta = ws.unit();
   p.group_m = kGroupMdW;
   p.out = dW; p.ldo = V;
-  return launch_tiled<EPI_F32_ACCUM, A_MSLAB>(small_tiles(V, d, grid), grid, p, s);
+  return p;
+}
+
+hipError_t launch_gemm_dx(const Workspace& ws, const uint16_t* W, int d, int V, int grid,
+                          hipStream_t s) {
+  const GemmParams p = dx_params(ws, W, d, V);
+  const bool small = dx_small_tiles(ws, d, V, grid);
+  if (ws.Wk) return launch_tiled<EPI_F32_STORE, A_KSLAB>(small, grid, p, s);
+  return launch_tiled<EPI_F32_STORE, A_ROW>(small, grid, p, s);
+}
+
+hipError_t launch_gemm_dw(const Workspace& ws, float* dW, int d, int V, int grid, hipStream_t s) {
+  return launch_tiled<EPI_F32_ACCUM, A_MSLAB>(small_tiles(V, d, grid), grid, dw_params(ws, dW, d, V), s);
+}
+
+hipError_t launch_gemm_dx_dw(const Workspace& ws, const uint16_t* W, float* dW, int d, int V,
+                             int grid, int units, hipStream_t s, bool* paired) {
+  const int n_dx = pair_dx_workgroups(ws, d, V, grid, units);
+  *paired = n_dx > 0;
+  if (!n_dx) return launch_gemm_dx(ws, W, d, V, grid, s);
+  const GemmParams dx = dx_params(ws, W, d, V), dw = dw_params(ws, dW, d, V);
+  if (ws.Wk)
+    k_gemm4w_dx_dw<A_KSLAB, BGPO_TILE4S><<<grid, kGemmThreads4, 0, s>>>(dx, dw, (uint32_t)n_dx);
+  else
+    k_gemm4w_dx_dw<A_ROW, BGPO_TILE4S><<<grid, kGemmThreads4, 0, s>>>(dx, dw, (uint32_t)n_dx);
+  return hipGetLastError();
 }
 
 hipError_t launch_gemm_recompute(const Workspace& ws, int d, int v0, int width, int grid,

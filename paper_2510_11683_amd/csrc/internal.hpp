@@ -215,6 +215,10 @@ hipError_t launch_dx_reduce_rmsnorm(const Workspace& ws, int B, const void* x, b
                                     const float* gamma, float* dx, int64_t stride, float* dgamma,
                                     int d, hipStream_t s);
 hipError_t launch_gemm_dw(const Workspace& ws, float* dW, int d, int V, int grid, hipStream_t s);
+// the dX GEMM of a unit that ends a dW batch of `units` units, together with
+// the batch's dW GEMM where that pays (*paired; else dW is still to do)
+hipError_t launch_gemm_dx_dw(const Workspace& ws, const uint16_t* W, float* dW, int d, int V,
+                             int grid, int units, hipStream_t s, bool* paired);
 // recompute mode, vocabulary chunk [v0, v0 + width): the chunk's logits from
 // W^T and H_c, turned into dZ = s (softmax - onehot) (bf16);
 // dX^T partials (+)= W[:, chunk] . dZ^T (first chunk: stored);
@@ -227,8 +231,9 @@ hipError_t launch_gemm_dx_chunk(const Workspace& ws, const uint16_t* W, int d, i
 hipError_t launch_gemm_dw_chunk(const Workspace& ws, float* dW, int d, int V, int v0, int width,
                                 int grid, hipStream_t s);
 
-// the split choice of a unit of g_used samples (set before): tile, K, grid
-DxPlan dx_plan(const Workspace& ws, int d, int V, int grid);
+// the split choice of a unit of g_used samples (set before): tile, K, grid;
+// units: the units of the dW batch that this unit ends, 0 if it ends none
+DxPlan dx_plan(const Workspace& ws, int d, int V, int grid, int units);
 
 int gemm_grid(int device);  // persistent grid size of the GEMM kernels on `device`
 
