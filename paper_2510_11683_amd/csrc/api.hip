@@ -616,11 +616,17 @@ static int bwd_retained(const bgpo_problem* prob, const Plan& pl, const Act& act
   BGPO_TRY(tm.begin(BGPO_K_TRANSPOSE_W));
   BGPO_TRY(launch_transpose_w(W_head, act.f32, ws.WT, ws.Wk, dm.d, dm.V, s));
   BGPO_TRY(tm.end());
+  // the dX splits are those of the two-pass mode, which ends a dW batch every
+  // `batch` units (so that both modes give the same bits)
+  const int batch = kDwUnits * ws.RP <= kMaxColumns ? (int)kDwUnits : 1;
   for (int u = 0; u < n_units; ++u) {
     const int j0 = u * G, n_s = std::min(G, dm.n_t - j0);
+    const int in_batch = u % batch + 1;
+    const int dw_units = in_batch == batch || u == n_units - 1 ? in_batch : 0;
     const int st = run_forward_unit(prob, U[u], tm, grid, j0, n_s, act, targets, resp_mask,
                                     nullptr, nullptr, 0.0, ell, nullptr, n_masked, t_out,
-                                    status_flags, false, true, 0, u ? U[u - 1].unit() : nullptr,
+                                    status_flags, false, true, dw_units,
+                                    u ? U[u - 1].unit() : nullptr,
                                     nullptr, s);
     if (st != BGPO_OK) return st;
   }
