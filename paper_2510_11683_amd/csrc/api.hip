@@ -420,14 +420,13 @@ struct Act {
 };
 
 // forward part of the unit of samples j0 .. j0 + n_s - 1: masks .. l (and,
-// with backward, g / loss / scale); dw_units: the units of the dW batch that
-// this unit ends (0: none); prev_unit: record of the previous unit of the dW
-// batch (NULL for the first)
+// with backward, g / loss / scale); prev_unit: record of the previous unit of
+// the dW batch (NULL for the first)
 static int run_forward_unit(const bgpo_problem* p, Workspace& ws, Timer& tm, int grid, int j0,
                             int n_s, const Act& act, const int32_t* targets, const uint8_t* resp,
                             const float* adv, const double* ell_old, double loss_scale,
                             double* ell, double* g, int32_t* n_masked, float* t_out,
-                            int32_t* flags, bool backward, bool store_u, int dw_units,
+                            int32_t* flags, bool backward, bool store_u,
                             const SampleMeta* prev_unit, const double* dbar, hipStream_t s) {
   const Dims dm = dims_of(p);
   ws.g_used = n_s;
@@ -435,7 +434,7 @@ static int run_forward_unit(const bgpo_problem* p, Workspace& ws, Timer& tm, int
   BGPO_TRY(launch_masks(resp, targets, dm.B, dm.L, dm.n_t, j0, n_s, p->t_mode, p->seed,
                         p->seq_id_base, &ws, nullptr, n_masked + j0, dm.n_t,
                         t_out ? t_out + j0 : nullptr, dm.n_t, dm.V, prev_unit,
-                        dx_plan(ws, dm.d, dm.V, grid, dw_units), ws.mask_scratch, false, s));
+                        dx_plan(ws, dm.d, dm.V, grid), ws.mask_scratch, false, s));
   BGPO_TRY(tm.end(n_s));
   BGPO_TRY(tm.begin(BGPO_K_GATHER));
   if (act.gamma)
@@ -616,17 +615,11 @@ static int bwd_retained(const bgpo_problem* prob, const Plan& pl, const Act& act
   BGPO_TRY(tm.begin(BGPO_K_TRANSPOSE_W));
   BGPO_TRY(launch_transpose_w(W_head, act.f32, ws.WT, ws.Wk, dm.d, dm.V, s));
   BGPO_TRY(tm.end());
-  // the dX splits are those of the two-pass mode, which ends a dW batch every
-  // `batch` units (so that both modes give the same bits)
-  const int batch = kDwUnits * ws.RP <= kMaxColumns ? (int)kDwUnits : 1;
   for (int u = 0; u < n_units; ++u) {
     const int j0 = u * G, n_s = std::min(G, dm.n_t - j0);
-    const int in_batch = u % batch + 1;
-    const int dw_units = in_batch == batch || u == n_units - 1 ? in_batch : 0;
     const int st = run_forward_unit(prob, U[u], tm, grid, j0, n_s, act, targets, resp_mask,
                                     nullptr, nullptr, 0.0, ell, nullptr, n_masked, t_out,
-                                    status_flags, false, true, dw_units,
-                                    u ? U[u - 1].unit() : nullptr,
+                                    status_flags, false, true, u ? U[u - 1].unit() : nullptr,
                                     nullptr, s);
     if (st != BGPO_OK) return st;
   }
@@ -684,7 +677,7 @@ static int elbo_fwd_impl(const bgpo_problem* prob, const Act& act, const void* W
   for (int j0 = prob->j_begin; j0 < j_end; j0 += (int)ws.G) {
     const int n_s = std::min<int>(j_end - j0, (int)ws.G);
     st = run_forward_unit(prob, ws, tm, grid, j0, n_s, act, targets, resp_mask, nullptr, nullptr,
-                          0.0, ell, nullptr, n_masked, t_out, nullptr, false, false, 0,
+                          0.0, ell, nullptr, n_masked, t_out, nullptr, false, false,
                           nullptr, nullptr, s);
     if (st != BGPO_OK) return st;
   }
@@ -758,7 +751,7 @@ static int elbo_bwd_impl(const bgpo_problem* prob, const Act& act, const void* W
       const int n_s = std::min<int>(prob->n_t - j0, (int)ws.G);
       st = run_forward_unit(prob, ws, tm, grid, j0, n_s, act, targets, resp_mask, nullptr, nullptr,
                             0.0, ell, nullptr, n_masked, t_out, status_flags, false,
-                            false, 0, nullptr, nullptr, s);
+                            false, nullptr, nullptr, s);
       if (st != BGPO_OK) return st;
     }
     BGPO_TRY(tm.begin(BGPO_K_ELL));
@@ -784,7 +777,7 @@ static int elbo_bwd_impl(const bgpo_problem* prob, const Act& act, const void* W
     const int dw_units = ends_batch ? in_batch : 0;
     st = run_forward_unit(prob, ws, tm, grid, j0, n_s, act, targets, resp_mask, adv, ell_old,
                           loss_scale, ell, g, n_masked, t_out, status_flags, true, store_u,
-                          dw_units, prev, dbar, s);
+                          prev, dbar, s);
     if (st != BGPO_OK) return st;
     st = unit_backward(ws, act, j0, prob->j_begin, static_cast<const uint16_t*>(W_head),
                        loss_scale, g, loss, dX,

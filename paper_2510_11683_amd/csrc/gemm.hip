@@ -772,19 +772,18 @@ static bool dx_small_tiles(const Workspace& ws, int d, int V, int grid) {
 }
 
 // Workgroups of the dX GEMM when it shares a launch with the dW GEMM of a batch
-// of `units` units, 0 when the two run one after the other.  Both must be small
-// (128-wide tiles, dW's within kPairRounds rounds): alone, each leaves a part of
-// the chip idle and pays a launch.  The grid is shared by the slabs of their
-// tiles, with about 8 slabs' time to load and store a dW tile.  One after the
-// other against together: B2 L64 d128 V1024 n_t 4 (8 dW tiles) 54 us a step
-// against 45, B3 L201 d576 V4288 n_t 6 (170) 102 and 91, B8 L512 d256 V4096 n_t 16
-// (64) 719 and 647, B2 L100 d640 V12800 n_t 16 (500) 214 and 205; with two whole
-// rounds of dW (512 tiles, B2 L256 d1024 V8192 n_t 4) 142 and 142.
-constexpr int64_t kPairRounds = 4;
-
+// of `units` units, 0 when the two run one after the other.  Both must be on
+// 128-wide tiles, dW's within one round: alone, each leaves a part of the chip
+// idle and pays a launch.  The grid is shared by the slabs of their tiles, with
+// about 8 slabs' time to load and store a dW tile.  (The dX split stays the one
+// for the whole grid: dX must not depend on how dW is batched.)  One after the
+// other against together: B2 L64 d128 V1024 n_t 4 (8 dW tiles) 54 us a step and
+// 45, B3 L201 d576 V4288 n_t 6 (170) 102 and 91, B8 L512 d256 V4096 n_t 16 (64)
+// 719 and 637; with dW in two rounds 142 and 146 (B2 L256 d1024 V8192 n_t 4,
+// 512 tiles), 214 and 208 (B2 L100 d640 V12800 n_t 16, 500).
 static int pair_dx_workgroups(const Workspace& ws, int d, int V, int grid, int units) {
   if (ws.chunk || !small_tiles(V, d, grid) || !dx_small_tiles(ws, d, V, grid) ||
-      rounds(V, d, 128, grid) > kPairRounds || grid < 64)
+      rounds(V, d, 128, grid) > 1 || grid < 64)
     return 0;
   const int64_t rows = rows_estimate(ws), cols = (d + 127) / 128;
   const double dx = (double)(cols * ((rows + 127) / 128) * (V / 64));
@@ -792,12 +791,10 @@ static int pair_dx_workgroups(const Workspace& ws, int d, int V, int grid, int u
   return std::max(8, std::min(grid / 8 * 8 - 8, (int)(grid * dx / (dx + dw) / 8.0 + 0.5) * 8));
 }
 
-DxPlan dx_plan(const Workspace& ws, int d, int V, int grid, int units) {
+DxPlan dx_plan(const Workspace& ws, int d, int V, int grid) {
   const bool small = dx_small_tiles(ws, d, V, grid);
   const int e = small ? 128 : 256;
-  const int n_dx = units ? pair_dx_workgroups(ws, d, V, grid, units) : 0;
-  return DxPlan{(int)(dx_k(ws, V) / 64), (d + e - 1) / e, n_dx ? n_dx : grid, (int)ws.n_split, e,
-                small ? 26 : 13};
+  return DxPlan{(int)(dx_k(ws, V) / 64), (d + e - 1) / e, grid, (int)ws.n_split, e, small ? 26 : 13};
 }
 
 static GemmParams dx_params(const Workspace& ws, const uint16_t* W, int d, int V) {

@@ -231,9 +231,8 @@ hipError_t launch_gemm_dx_chunk(const Workspace& ws, const uint16_t* W, int d, i
 hipError_t launch_gemm_dw_chunk(const Workspace& ws, float* dW, int d, int V, int v0, int width,
                                 int grid, hipStream_t s);
 
-// the split choice of a unit of g_used samples (set before): tile, K, grid;
-// units: the units of the dW batch that this unit ends, 0 if it ends none
-DxPlan dx_plan(const Workspace& ws, int d, int V, int grid, int units);
+// the split choice of a unit of g_used samples (set before): tile, K, grid
+DxPlan dx_plan(const Workspace& ws, int d, int V, int grid);
 
 int gemm_grid(int device);  // persistent grid size of the GEMM kernels on `device`
 
