@@ -420,21 +420,32 @@ struct Act {
 };
 
 // forward part of the unit of samples j0 .. j0 + n_s - 1: masks .. l (and,
-// with backward, g / loss / scale); prev_unit: record of the previous unit of
-// the dW batch (NULL for the first)
+// with backward, g / loss / scale); W: the caller's W_head in the first unit of
+// a call, whose copies are made beside the masks, else NULL; prev_unit: record
+// of the previous unit of the dW batch (NULL for the first)
 static int run_forward_unit(const bgpo_problem* p, Workspace& ws, Timer& tm, int grid, int j0,
-                            int n_s, const Act& act, const int32_t* targets, const uint8_t* resp,
-                            const float* adv, const double* ell_old, double loss_scale,
+                            int n_s, const void* W, const Act& act, const int32_t* targets,
+                            const uint8_t* resp, const float* adv, const double* ell_old, double loss_scale,
                             double* ell, double* g, int32_t* n_masked, float* t_out,
                             int32_t* flags, bool backward, bool store_u,
                             const SampleMeta* prev_unit, const double* dbar, hipStream_t s) {
   const Dims dm = dims_of(p);
   ws.g_used = n_s;
+  const DxPlan plan = dx_plan(ws, dm.d, dm.V, grid);
+  float* const t_j0 = t_out ? t_out + j0 : nullptr;
+  bool masks_done = false;
+  if (W) {
+    BGPO_TRY(tm.begin(BGPO_K_TRANSPOSE_W));
+    BGPO_TRY(launch_masks_and_w(W, act.f32, resp, targets, dm.B, dm.L, dm.d, dm.n_t, j0, p->t_mode,
+                                p->seed, p->seq_id_base, ws, n_masked + j0, t_j0, dm.V, plan, s,
+                                &masks_done));
+    BGPO_TRY(tm.end());
+  }
   BGPO_TRY(tm.begin(BGPO_K_MASK));
-  BGPO_TRY(launch_masks(resp, targets, dm.B, dm.L, dm.n_t, j0, n_s, p->t_mode, p->seed,
-                        p->seq_id_base, &ws, nullptr, n_masked + j0, dm.n_t,
-                        t_out ? t_out + j0 : nullptr, dm.n_t, dm.V, prev_unit,
-                        dx_plan(ws, dm.d, dm.V, grid), ws.mask_scratch, false, s));
+  if (!masks_done)
+    BGPO_TRY(launch_masks(resp, targets, dm.B, dm.L, dm.n_t, j0, n_s, p->t_mode, p->seed,
+                          p->seq_id_base, &ws, nullptr, n_masked + j0, dm.n_t, t_j0, dm.n_t, dm.V,
+                          prev_unit, plan, ws.mask_scratch, false, s));
   BGPO_TRY(tm.end(n_s));
   BGPO_TRY(tm.begin(BGPO_K_GATHER));
   if (act.gamma)
@@ -612,13 +623,10 @@ static int bwd_retained(const bgpo_problem* prob, const Plan& pl, const Act& act
   const int G = (int)ws.G, n_units = (int)ws.dw_batch;
   std::vector<Workspace> U(n_units);
   workspace_layout(dm, pl, workspace, nullptr, U.data());
-  BGPO_TRY(tm.begin(BGPO_K_TRANSPOSE_W));
-  BGPO_TRY(launch_transpose_w(W_head, act.f32, ws.WT, ws.Wk, dm.d, dm.V, s));
-  BGPO_TRY(tm.end());
   for (int u = 0; u < n_units; ++u) {
     const int j0 = u * G, n_s = std::min(G, dm.n_t - j0);
-    const int st = run_forward_unit(prob, U[u], tm, grid, j0, n_s, act, targets, resp_mask,
-                                    nullptr, nullptr, 0.0, ell, nullptr, n_masked, t_out,
+    const int st = run_forward_unit(prob, U[u], tm, grid, j0, n_s, u ? nullptr : W_head, act, targets,
+                                    resp_mask, nullptr, nullptr, 0.0, ell, nullptr, n_masked, t_out,
                                     status_flags, false, true, u ? U[u - 1].unit() : nullptr,
                                     nullptr, s);
     if (st != BGPO_OK) return st;
@@ -670,13 +678,12 @@ static int elbo_fwd_impl(const bgpo_problem* prob, const Act& act, const void* W
   int grid = 0;
   if ((st = device_grid(&grid)) != BGPO_OK) return st;
   Timer tm(prof, s);
-  BGPO_TRY(tm.begin(BGPO_K_TRANSPOSE_W));
-  BGPO_TRY(launch_transpose_w(W_head, act.f32, ws.WT, nullptr, prob->d, prob->V, s));
-  BGPO_TRY(tm.end());
+  ws.Wk = nullptr;   // no dX GEMM reads it
   const int j_end = prob->j_begin + prob->j_count;
-  for (int j0 = prob->j_begin; j0 < j_end; j0 += (int)ws.G) {
+  const void* W = W_head;
+  for (int j0 = prob->j_begin; j0 < j_end; j0 += (int)ws.G, W = nullptr) {
     const int n_s = std::min<int>(j_end - j0, (int)ws.G);
-    st = run_forward_unit(prob, ws, tm, grid, j0, n_s, act, targets, resp_mask, nullptr, nullptr,
+    st = run_forward_unit(prob, ws, tm, grid, j0, n_s, W, act, targets, resp_mask, nullptr, nullptr,
                           0.0, ell, nullptr, n_masked, t_out, nullptr, false, false,
                           nullptr, nullptr, s);
     if (st != BGPO_OK) return st;
@@ -740,17 +747,15 @@ static int elbo_bwd_impl(const bgpo_problem* prob, const Act& act, const void* W
   Workspace ws;
   workspace_layout(dm, pl, workspace, &ws, nullptr);
   if (!act.f32 && !copy_pays((int64_t)prob->j_count * ws.P, dm.V)) ws.Wk = nullptr;
-  BGPO_TRY(tm.begin(BGPO_K_TRANSPOSE_W));
-  BGPO_TRY(launch_transpose_w(W_head, act.f32, ws.WT, ws.Wk, dm.d, dm.V, s));
-  BGPO_TRY(tm.end());
+  const void* W_new = W_head;   // until the first unit has made the copies of W
   // exact objective off-policy: a forward pass over every sample gives the
   // mean log-ratio, which scales every sample's gradient (on-policy it is 0)
   const double* dbar = nullptr;
   if (exact && ell_old) {
-    for (int j0 = 0; j0 < prob->n_t; j0 += (int)ws.G) {
+    for (int j0 = 0; j0 < prob->n_t; j0 += (int)ws.G, W_new = nullptr) {
       const int n_s = std::min<int>(prob->n_t - j0, (int)ws.G);
-      st = run_forward_unit(prob, ws, tm, grid, j0, n_s, act, targets, resp_mask, nullptr, nullptr,
-                            0.0, ell, nullptr, n_masked, t_out, status_flags, false,
+      st = run_forward_unit(prob, ws, tm, grid, j0, n_s, W_new, act, targets, resp_mask, nullptr,
+                            nullptr, 0.0, ell, nullptr, n_masked, t_out, status_flags, false,
                             false, nullptr, nullptr, s);
       if (st != BGPO_OK) return st;
     }
@@ -763,7 +768,7 @@ static int elbo_bwd_impl(const bgpo_problem* prob, const Act& act, const void* W
   const bool store_u = !ws.chunk;   // stored mode keeps the forward's exponentials
   int in_batch = 0;        // units already in the current dW batch
   const SampleMeta* last = nullptr;   // the record of the previous unit
-  for (int j0 = prob->j_begin; j0 < j_end; j0 += (int)ws.G) {
+  for (int j0 = prob->j_begin; j0 < j_end; j0 += (int)ws.G, W_new = nullptr) {
     const int n_s = std::min<int>(j_end - j0, (int)ws.G);
     // a unit after the first of its batch puts its dZ rows / H_c^T columns
     // after the previous unit's, whose record the mask kernel reads while it
@@ -775,7 +780,7 @@ static int elbo_bwd_impl(const bgpo_problem* prob, const Act& act, const void* W
     ++in_batch;
     const bool ends_batch = !ws.chunk && (in_batch == (int)ws.dw_batch || j0 + n_s >= j_end);
     const int dw_units = ends_batch ? in_batch : 0;
-    st = run_forward_unit(prob, ws, tm, grid, j0, n_s, act, targets, resp_mask, adv, ell_old,
+    st = run_forward_unit(prob, ws, tm, grid, j0, n_s, W_new, act, targets, resp_mask, adv, ell_old,
                           loss_scale, ell, g, n_masked, t_out, status_flags, true, store_u,
                           prev, dbar, s);
     if (st != BGPO_OK) return st;

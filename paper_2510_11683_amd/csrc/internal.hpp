@@ -174,6 +174,13 @@ hipError_t launch_masks(const uint8_t* resp, const int32_t* targets, int B, int 
                         int nm_stride, float* t_out, int t_stride, int V,
                         const SampleMeta* prev_unit, const DxPlan& plan, void* scratch,
                         bool force_multi, hipStream_t s);
+// The copies of W, with the masks of a call's first unit in the same launch where
+// its size allows (*masks_done; else they are still to draw).
+hipError_t launch_masks_and_w(const void* W, bool f32, const uint8_t* resp, const int32_t* targets,
+                              int B, int L, int d, int n_t, int j0, int t_mode, uint64_t seed,
+                              uint32_t seq_base, const Workspace& ws, int32_t* n_masked_out,
+                              float* t_out, int V, const DxPlan& plan, hipStream_t s,
+                              bool* masks_done);
 // scratch bytes the multi-block mask passes need (mask words, block counts and
 // offsets, timesteps); with scratch NULL the single-workgroup kernel runs, and
 // with scratch the multi-block passes run above 65536 positions (or always,

@@ -6,6 +6,8 @@
 // independently with probability t; the ELBO term (Eq. per_step_loss) only
 // touches masked positions, so the rows that reach the LM-head GEMMs are the
 // masked ones, compacted in ascending flat order b*L + i.
+#include <algorithm>
+
 #include "common.hpp"
 #include "internal.hpp"
 
@@ -106,8 +108,9 @@ __device__ void write_record(SampleMeta* m, int row0, int col0, int total, const
 }
 
 // Single-workgroup form: workgroup g handles sample j0 + g of a unit, timesteps
-// in LDS, kSpan positions at a time (all of them up to kSingleBlockPositions;
-// only the mask-only entry point goes beyond), every thread a contiguous run
+// in LDS, 64 positions per thread at a time (all of them in one span up to
+// kSingleBlockPositions; only the mask-only entry point goes beyond), every
+// thread a contiguous run
 // of at most 64 positions whose mask bits stay in a register between the
 // count and the output, one block-wide scan.  The first row of a sample follows
 // from the mask counts of the unit's earlier samples, which every workgroup
@@ -123,8 +126,7 @@ __device__ void write_record(SampleMeta* m, int row0, int col0, int total, const
 // Philox block), and the unit's record is written by the last wave while the
 // others write rows: one sample of 4096 positions 7.6 -> 6.5 us, a unit of 4
 // samples of 128 positions 10.8 -> 8.2, of 6 of 603 15.4 -> 11.4.
-constexpr int kSpan = 64 * kMaskThreads;
-static_assert(kSingleBlockPositions <= kSpan, "one span per sample in a unit");
+static_assert(kSingleBlockPositions <= 64 * kMaskThreads, "one span per sample in a unit");
 
 // The response-mask bytes of positions p .. min(p + 4, p1) - 1 (p a multiple of
 // 4; `words`: the mask is 4-byte aligned).
@@ -171,23 +173,52 @@ __device__ __forceinline__ int wave_inclusive_sum(int v) {
   return v;
 }
 
-__global__ __launch_bounds__(kMaskThreads) void k_mask_compact(
-    const uint8_t* __restrict__ resp, const int32_t* __restrict__ targets, int B, int L, int n_t,
-    int j0, int t_mode, uint32_t k0, uint32_t k1, uint32_t seq_base, MaskOut out,
-    int32_t* __restrict__ nm_out, int nm_stride, float* __restrict__ t_out, int t_stride, int V,
-    const SampleMeta* prev, DxPlan plan) {
-  __shared__ uint32_t sT[kMaxB];      // timesteps of kMaxB / B samples at a time
-  __shared__ int32_t sSeg[kMaxB + 1];
-  __shared__ int32_t sWave[kMaskThreads / 64], sEarlier[kMaskThreads / 64];
+struct MaskArgs {
+  const uint8_t* resp;
+  const int32_t* targets;
+  int B, L, n_t, j0, t_mode;
+  uint32_t k0, k1, seq_base;
+  MaskOut out;
+  int32_t* nm_out;
+  int nm_stride;
+  float* t_out;
+  int t_stride, V;
+  const SampleMeta* prev;
+  DxPlan plan;
+};
+
+template <int THREADS, int MAXB>
+struct MaskShared {
+  uint32_t T[MAXB];            // timesteps of MAXB / B samples at a time
+  int32_t seg[MAXB + 1];
+  int32_t wave[THREADS / 64], earlier[THREADS / 64];
+};
+
+// Sample j0 + g of n_samples by one workgroup of THREADS threads; B <= MAXB.
+template <int THREADS, int MAXB>
+__device__ __forceinline__ void mask_sample(const MaskArgs& a, int g, int n_samples,
+                                            MaskShared<THREADS, MAXB>& sh) {
+  constexpr int kSpan = 64 * THREADS;
+  uint32_t* const sT = sh.T;
+  int32_t *const sSeg = sh.seg, *const sWave = sh.wave, *const sEarlier = sh.earlier;
+  const uint8_t* const resp = a.resp;
+  const int32_t* const targets = a.targets;
+  const int B = a.B, L = a.L, n_t = a.n_t, j0 = a.j0, t_mode = a.t_mode, V = a.V;
+  const uint32_t k0 = a.k0, k1 = a.k1, seq_base = a.seq_base;
+  const MaskOut& out = a.out;
+  int32_t* const nm_out = a.nm_out;
+  float* const t_out = a.t_out;
+  const int nm_stride = a.nm_stride, t_stride = a.t_stride;
+  const SampleMeta* const prev = a.prev;
+  const DxPlan& plan = a.plan;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
-  const int g = blockIdx.x;
   const int P = B * L;
   const bool words = ((uintptr_t)resp & 3) == 0;
 
   // this thread's run of the first span
   int n = min(kSpan, P);
-  int chunk = ((n + kMaskThreads - 1) / kMaskThreads + 3) & ~3;
+  int chunk = ((n + THREADS - 1) / THREADS + 3) & ~3;
   int p0 = min(n, tid * chunk), p1 = min(n, p0 + chunk);
   int b0 = p0 / L, i0 = p0 - b0 * L;
   uint32_t r4 = resp_word(resp, p0, p1, words);
@@ -204,12 +235,12 @@ __global__ __launch_bounds__(kMaskThreads) void k_mask_compact(
   // counts of the unit's earlier samples, then this sample's timesteps at
   // sT + t_base
   int earlier = 0, t_base = 0;
-  const int per = kMaxB / B;
+  const int per = MAXB / B;
   const int n_runs = (n + chunk - 1) / chunk;
   for (int q0 = 0; q0 <= g; q0 += per) {
     const int nq = min(per, g + 1 - q0);
     if (q0) __syncthreads();          // the previous samples' timesteps are done with
-    for (int e = tid; e < nq * B; e += kMaskThreads) {
+    for (int e = tid; e < nq * B; e += THREADS) {
       const int q = e / B;
       sT[e] = timestep_t24(k0, k1, seq_base + (uint32_t)(e - q * B), j0 + q0 + q, n_t, t_mode);
     }
@@ -217,7 +248,7 @@ __global__ __launch_bounds__(kMaskThreads) void k_mask_compact(
     __syncthreads();
     t_base = (nq - 1) * B;
     const int n_earlier = min(nq, g - q0);
-    for (int e = tid; e < n_earlier * n_runs; e += kMaskThreads) {
+    for (int e = tid; e < n_earlier * n_runs; e += THREADS) {
       const int q = e / n_runs, c0 = (e - q * n_runs) * chunk, c1 = min(n, c0 + chunk);
       const int b = c0 / L;
       MaskWalker me{k0, k1, seq_base, L, j0 + q0 + q};
@@ -232,7 +263,7 @@ __global__ __launch_bounds__(kMaskThreads) void k_mask_compact(
   for (int s0 = 0; s0 < P; s0 += kSpan) {
     if (s0) {
       n = min(kSpan, P - s0);
-      chunk = ((n + kMaskThreads - 1) / kMaskThreads + 3) & ~3;
+      chunk = ((n + THREADS - 1) / THREADS + 3) & ~3;
       p0 = s0 + min(n, tid * chunk);
       p1 = min(s0 + n, p0 + chunk);
       b0 = p0 / L;
@@ -248,7 +279,7 @@ __global__ __launch_bounds__(kMaskThreads) void k_mask_compact(
     __syncthreads();
     int base = total + incl - cnt;    // masked positions of this sample before the run
 #pragma unroll
-    for (int q = 0; q < kMaskThreads / 64; ++q) {
+    for (int q = 0; q < THREADS / 64; ++q) {
       const int v = sWave[q];
       base += q < wave ? v : 0;
       total += v;
@@ -275,13 +306,13 @@ __global__ __launch_bounds__(kMaskThreads) void k_mask_compact(
       }
     }
   }
-  if (wave == kMaskThreads / 64 - 1)
+  if (wave == THREADS / 64 - 1)
     write_record(out.meta ? out.meta + g : nullptr, row0, col0, total, plan, lane);
   if (tid == 0) sSeg[B] = total;
   __syncthreads();
 
   const int rows = row0 + total;
-  for (int b = tid; b < B; b += kMaskThreads) {
+  for (int b = tid; b < B; b += THREADS) {
     const uint32_t T = sT[t_base + b];
     if (nm_out) nm_out[(int64_t)b * nm_stride + g] = sSeg[b + 1] - sSeg[b];
     if (t_out) t_out[(int64_t)b * t_stride + g] = (float)T * (1.0f / 16777216.0f);
@@ -290,13 +321,18 @@ __global__ __launch_bounds__(kMaskThreads) void k_mask_compact(
   }
   if (tid == 0 && out.seg_off) out.seg_off[g * (B + 1) + B] = rows;
   // the last sample pads the unit's rows up to the next row tile
-  if (g == (int)gridDim.x - 1 && out.row_tgt) {
+  if (g == n_samples - 1 && out.row_tgt) {
     const int pad_end = min((rows + kRowPad - 1) / kRowPad * kRowPad, out.row_cap);
-    for (int r = rows + tid; r < pad_end; r += kMaskThreads) {
+    for (int r = rows + tid; r < pad_end; r += THREADS) {
       out.row_tgt[r] = 0;
       out.row_seq[r] = 0;
     }
   }
+}
+
+__global__ __launch_bounds__(kMaskThreads) void k_mask_compact(MaskArgs a) {
+  __shared__ MaskShared<kMaskThreads, kMaxB> sh;
+  mask_sample<kMaskThreads, kMaxB>(a, blockIdx.x, gridDim.x, sh);
 }
 
 // ---------------------------------------------------------------------------
@@ -460,12 +496,10 @@ size_t mask_scratch_bytes(int B, int L) {
   return (size_t)(words * 8 + nblk * 8 + (int64_t)B * 4 + 4 * 256);
 }
 
-hipError_t launch_masks(const uint8_t* resp, const int32_t* targets, int B, int L, int n_t, int j0,
-                        int n_samples, int t_mode, uint64_t seed, uint32_t seq_base,
-                        const Workspace* ws, int32_t* idx_out, int32_t* n_masked_out,
-                        int nm_stride, float* t_out, int t_stride, int V,
-                        const SampleMeta* prev_unit, const DxPlan& plan, void* scratch,
-                        bool force_multi, hipStream_t s) {
+static MaskArgs mask_args(const uint8_t* resp, const int32_t* targets, int B, int L, int n_t, int j0,
+                          int t_mode, uint64_t seed, uint32_t seq_base, const Workspace* ws,
+                          int32_t* idx_out, int32_t* n_masked_out, int nm_stride, float* t_out,
+                          int t_stride, int V, const SampleMeta* prev_unit, const DxPlan& plan) {
   MaskOut out{idx_out, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0};
   if (ws) {
     out.idx = ws->idx;
@@ -477,12 +511,24 @@ hipError_t launch_masks(const uint8_t* resp, const int32_t* targets, int B, int 
     out.meta = ws->meta;
     out.row_cap = (int)ws->RP;
   }
+  return MaskArgs{resp, targets, B, L, n_t, j0, t_mode, (uint32_t)(seed & 0xFFFFFFFFu),
+                  (uint32_t)(seed >> 32), seq_base, out, n_masked_out, nm_stride, t_out, t_stride, V,
+                  prev_unit, plan};
+}
+
+hipError_t launch_masks(const uint8_t* resp, const int32_t* targets, int B, int L, int n_t, int j0,
+                        int n_samples, int t_mode, uint64_t seed, uint32_t seq_base,
+                        const Workspace* ws, int32_t* idx_out, int32_t* n_masked_out,
+                        int nm_stride, float* t_out, int t_stride, int V,
+                        const SampleMeta* prev_unit, const DxPlan& plan, void* scratch,
+                        bool force_multi, hipStream_t s) {
+  const MaskArgs args = mask_args(resp, targets, B, L, n_t, j0, t_mode, seed, seq_base, ws, idx_out,
+                                  n_masked_out, nm_stride, t_out, t_stride, V, prev_unit, plan);
+  const MaskOut& out = args.out;
   const uint32_t k0 = (uint32_t)(seed & 0xFFFFFFFFu), k1 = (uint32_t)(seed >> 32);
   const int64_t P = (int64_t)B * L;
   if ((P <= kSingleBlockPositions && !force_multi) || !scratch) {
-    k_mask_compact<<<n_samples, kMaskThreads, 0, s>>>(resp, targets, B, L, n_t, j0, t_mode, k0, k1,
-                                                      seq_base, out, n_masked_out, nm_stride,
-                                                      t_out, t_stride, V, prev_unit, plan);
+    k_mask_compact<<<n_samples, kMaskThreads, 0, s>>>(args);
     return hipGetLastError();
   }
   // scratch: mask words, block counts and offsets, and (without a unit) the
@@ -724,14 +770,15 @@ __device__ __forceinline__ void store16(uint16_t* p, uint4 v) {
     *reinterpret_cast<uint4*>(p) = v;
 }
 
+typedef uint16_t WTile[64][72];
+
 template <typename T, bool NT>
-__global__ __launch_bounds__(256) void k_transpose_w(const T* __restrict__ W,
-                                                     uint16_t* __restrict__ WT,
-                                                     uint16_t* __restrict__ Wk, int d, int V) {
-  __shared__ uint16_t tile[64][72];
+__device__ __forceinline__ void transpose_w_tile(const T* __restrict__ W, uint16_t* __restrict__ WT,
+                                                 uint16_t* __restrict__ Wk, int d, int V,
+                                                 unsigned wg, WTile& tile) {
   const unsigned kts = d / 64, vts = V / 64;
-  const int v0 = (int)(NT ? blockIdx.x / kts : blockIdx.x % vts) * 64;
-  const int k0 = (int)(NT ? blockIdx.x % kts : blockIdx.x / vts) * 64;
+  const int v0 = (int)(NT ? wg / kts : wg % vts) * 64;
+  const int k0 = (int)(NT ? wg % kts : wg / vts) * 64;
   const int tid = threadIdx.x;
 #pragma unroll
   for (int it = 0; it < 2; ++it) {
@@ -754,6 +801,36 @@ __global__ __launch_bounds__(256) void k_transpose_w(const T* __restrict__ W,
   }
 }
 
+template <typename T, bool NT>
+__global__ __launch_bounds__(256) void k_transpose_w(const T* __restrict__ W,
+                                                     uint16_t* __restrict__ WT,
+                                                     uint16_t* __restrict__ Wk, int d, int V) {
+  __shared__ WTile tile;
+  transpose_w_tile<T, NT>(W, WT, Wk, d, V, blockIdx.x, tile);
+}
+
+// The start of a call in one launch: the masks of its first unit (one workgroup
+// per sample, the first ones) beside the copies of W, neither of which reads
+// what the other writes.  Against two launches: a step of B2 L64 d128 V1024 n_t 4
+// 46 -> 42 us, of B4 L128 d2048 V8192 n_t 4 176 -> 167, of B4 L256 d2048 V32000
+// n_t 4 917 -> 910, one sample of B8 L512 d4096 V126464 7.66 -> 7.63 ms.
+constexpr int kPrepMaxB = 512, kPrepPositions = 64 * 256;
+
+template <typename T, bool NT>
+__global__ __launch_bounds__(256, 8) void k_masks_and_w(MaskArgs a, int n_samples,
+                                                        const T* __restrict__ W,
+                                                        uint16_t* __restrict__ WT,
+                                                        uint16_t* __restrict__ Wk, int d) {
+  __shared__ union {
+    MaskShared<256, kPrepMaxB> mask;
+    WTile tile;
+  } sh;
+  if ((int)blockIdx.x < n_samples)
+    mask_sample<256, kPrepMaxB>(a, blockIdx.x, n_samples, sh.mask);
+  else
+    transpose_w_tile<T, NT>(W, WT, Wk, d, a.V, blockIdx.x - n_samples, sh.tile);
+}
+
 // Bytes of an output of k_transpose_w from which it is streamed, well past what
 // the 256 MB last-level cache keeps for the GEMMs: 1.04 GB (d 4096 V 126464) 612
 // -> 577 us with both outputs; 0.54 GB 312 and 320, 0.13 GB 69 and 83 streamed.
@@ -769,6 +846,36 @@ hipError_t launch_transpose_w(const void* W, bool f32, uint16_t* WT, uint16_t* W
   else
     (nt ? k_transpose_w<uint16_t, true> : k_transpose_w<uint16_t, false>)<<<grid, 256, 0, s>>>(
         static_cast<const uint16_t*>(W), WT, Wk, d, V);
+  return hipGetLastError();
+}
+
+// Whether the masks of n_samples samples are drawn beside the copies of W.  A
+// workgroup of 256 threads takes twice as long as k_mask_compact's for a unit
+// of many positions (8 samples of 4096: 47 us and 20), so they are drawn there
+// if they are few or if the copies take longer (6 d V bytes at 5 TB/s against
+// about 1.2 ns per position).
+static bool masks_beside_w(int B, int L, int d, int V, int n_samples) {
+  const int64_t P = (int64_t)B * L;
+  return B <= kPrepMaxB && P <= kPrepPositions &&
+         n_samples * P <= std::max<int64_t>(8192, (int64_t)d * V / 1024);
+}
+
+hipError_t launch_masks_and_w(const void* W, bool f32, const uint8_t* resp, const int32_t* targets,
+                              int B, int L, int d, int n_t, int j0, int t_mode, uint64_t seed,
+                              uint32_t seq_base, const Workspace& ws, int32_t* n_masked_out,
+                              float* t_out, int V, const DxPlan& plan, hipStream_t s, bool* masks_done) {
+  *masks_done = masks_beside_w(B, L, d, V, ws.g_used);
+  if (!*masks_done) return launch_transpose_w(W, f32, ws.WT, ws.Wk, d, V, s);
+  const MaskArgs a = mask_args(resp, targets, B, L, n_t, j0, t_mode, seed, seq_base, &ws, nullptr,
+                               n_masked_out, n_t, t_out, n_t, V, nullptr, plan);
+  const unsigned grid = (unsigned)ws.g_used + (unsigned)(V / 64) * (unsigned)(d / 64);
+  const bool nt = (int64_t)d * V * 2 >= kStreamBytes;
+  if (f32)
+    (nt ? k_masks_and_w<float, true> : k_masks_and_w<float, false>)<<<grid, 256, 0, s>>>(
+        a, ws.g_used, static_cast<const float*>(W), ws.WT, ws.Wk, d);
+  else
+    (nt ? k_masks_and_w<uint16_t, true> : k_masks_and_w<uint16_t, false>)<<<grid, 256, 0, s>>>(
+        a, ws.g_used, static_cast<const uint16_t*>(W), ws.WT, ws.Wk, d);
   return hipGetLastError();
 }
 

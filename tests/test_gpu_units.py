@@ -28,6 +28,9 @@ def _gpu():
     (3, 7, 17, (1, 7)),         # three units of 8, 8, 1; L not a multiple of the Philox block
     (1500, 3, 9, (1, 3)),       # timesteps of two samples at a time in the mask kernel
     (5, 997, 10, (100, 997)),   # more positions than threads
+    (512, 4, 4, (1, 4)),        # the most responses and positions drawn beside W's copies
+    (513, 3, 4, (1, 3)),        # one response more: a launch of their own
+    (2, 4096, 1, (60, 4096)),   # one sample, 32 positions per thread
 ])
 def test_units_of_samples_match_oracle(B, L, n_t, lengths):
     w = workloads.Workload("unit", B=B, L=L, d=128, V=576, n_t=n_t, lengths=lengths, group=B,
