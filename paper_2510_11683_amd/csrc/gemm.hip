@@ -119,13 +119,16 @@ __device__ __forceinline__ int mslab_swz(int k) {
 // independent of them (the transposing reads of an A_MSLAB operand, which
 // carry no type information); the ring's explicit waits already order them.
 // The LDS-DMA load reads M0 one wait state after the scalar write at the
-// earliest (the s_nop; the compiler does not see inside the statement).
+// earliest (the s_nop; the compiler does not see inside the statement).  The
+// destination is an LDS byte address in a scalar register: taken from a generic
+// pointer, every load carried the conversion's null check, five scalar
+// instructions that one wave per SIMD issues between its MFMAs (dW of B8 L512
+// d4096 V126464 n_t 12 17.84 -> 17.71 ms, n_t 16 ragged 11.50 -> 11.45).
 __device__ __forceinline__ void lds_load16_asm(__amdgpu_buffer_rsrc_t rsrc, uint32_t voff,
-                                               uint32_t soff, const void* lds_dst) {
-  const uint32_t la = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)lds_dst;
+                                               uint32_t soff, uint32_t lds_dst) {
   asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
                :
-               : "v"(voff), "s"(rsrc), "s"(soff), "s"(__builtin_amdgcn_readfirstlane(la))
+               : "v"(voff), "s"(rsrc), "s"(soff), "s"(lds_dst)
                : "memory", "m0");
 }
 
@@ -245,6 +248,8 @@ __device__ __forceinline__ void gemm4w(const GemmParams& p, uint4* smem, uint32_
   // waves that share the load of one 64-wide M slab of A
   constexpr int WPS = C::NWAVES / (BM / 64);
   static_assert(!kMSlabA || WPS * (BM / 64) == C::NWAVES, "whole waves per M slab of A");
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane(
+      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)smem);
   uint4* As = smem;                           // [STAGES][BM][KCH]
   uint4* Bs = smem + STAGES * BM * KCH;       // [STAGES][BN][KCH]
 
@@ -386,18 +391,18 @@ __device__ __forceinline__ void gemm4w(const GemmParams& p, uint4* smem, uint32_
       // slab c + S is loaded into slab c's stage right after the barrier that
       // ends slab c, and slabs past the tile's K range re-load its last slab.
       constexpr int NINS = A_INS + B_INS;
-      auto lds_load = [&](__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff, uint4* dst) {
-        if constexpr (kMSlabA)
-          lds_load16_asm(r, voff, soff, dst);
+      auto lds_load = [&](__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff, int dst) {
+        if constexpr (kMSlabA)   // dst: 16-byte chunk of smem
+          lds_load16_asm(r, voff, soff, lds0 + 16 * dst);
         else
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16,
-                                                   voff, soff, 0, 0);
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(
+              r, (__attribute__((address_space(3))) void*)(smem + dst), 16, voff, soff, 0, 0);
       };
       auto issue_one = [&](int q, int stage, int e) {   // load instruction e of slab q
         const int qc = min(q, nk - 1);
         const int64_t ks = kb / BK + qc;                  // slab index in K
         if (e < A_INS) {
-          uint4* dst = As + stage * BM * KCH + (wave * A_INS + e) * 64;
+          const int dst = stage * BM * KCH + (wave * A_INS + e) * 64;
           if constexpr (kMSlabA) {
             // K slab ks of the wave's M slab: 64 rows of 128 bytes
             lds_load(__builtin_amdgcn_make_buffer_rsrc((void*)(a_tile + a_wslab + ks * 8192), (short)0,
@@ -411,7 +416,7 @@ __device__ __forceinline__ void gemm4w(const GemmParams& p, uint4* smem, uint32_
             lds_load(a_rsrc, a_voff[e], (uint32_t)(ks * BK * 2), dst);
           }
         } else {
-          uint4* dst = Bs + stage * BN * KCH + (wave * B_INS + e - A_INS) * 64;
+          const int dst = STAGES * BM * KCH + stage * BN * KCH + (wave * B_INS + e - A_INS) * 64;
           lds_load(__builtin_amdgcn_make_buffer_rsrc((void*)(b_tile + ks * b_slab), (short)0, 0x7FFFFFFF,
                                                      0x00020000),
                    b_voff[e - A_INS], 0, dst);
