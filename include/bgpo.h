@@ -170,7 +170,8 @@ typedef struct bgpo_problem {
  *                         of a dW batch; 24 GB at B=8, L=512, d=4096,
  *                         V=126464 with units of 8 samples).  The dX GEMM
  *                         reads a slab-major bf16 copy of W_head (2 d V
- *                         bytes, re-staged every call).  A row whose target log2-probability
+ *                         bytes, re-staged every call; calls over few
+ *                         positions read a bf16 W_head in place).  A row whose target log2-probability
  *                         is below -124 (its exponentials would leave the
  *                         range of bf16 and of the fp32 accumulators) is
  *                         recomputed after the forward from fp32 dot
@@ -198,7 +199,8 @@ typedef struct bgpo_problem {
 
 /* Kernel classes reported by the optional timing record. */
 enum {
-  BGPO_K_TRANSPOSE_W = 0,  /* W[d,V] -> W^T[V,d] staging, once per call */
+  BGPO_K_TRANSPOSE_W = 0,  /* W[d,V] -> W^T[V,d] staging, once per call (and the masks of the first
+                              unit, where they share its launch) */
   BGPO_K_MASK = 1,         /* Philox t and masks + stable compaction */
   BGPO_K_GATHER = 2,       /* masked hidden rows (RMSNorm applied) -> H_c and H_c^T */
   BGPO_K_FWD = 3,          /* fused LM-head GEMM + online log-sum-exp partials (in the
@@ -206,9 +208,10 @@ enum {
   BGPO_K_ELL = 4,          /* partial combine, log p, l, d, g, loss, gradient scale */
   BGPO_K_SOFTMAX_GRAD = 5, /* stored exponentials -> dZ = s (softmax - onehot): row factors,
                               target entries, H_c^T scaled, out-of-range rows recomputed */
-  BGPO_K_DX = 6,           /* dZ W^T split over the vocabulary */
+  BGPO_K_DX = 6,           /* dZ W^T split over the vocabulary (small problems: and dW, in one launch) */
   BGPO_K_DX_REDUCE = 7,    /* split reduction + scatter-add into dX (+ RMSNorm backward) */
-  BGPO_K_DW = 8,           /* H_c^T dZ accumulated into dW */
+  BGPO_K_DW = 8,           /* H_c^T dZ accumulated into dW (a launch that only acts where a batch is
+                              full is timed, not counted) */
   BGPO_K_RECOMPUTE = 9,    /* recompute mode: a vocabulary chunk's logits -> its dZ */
   BGPO_K_COUNT = 10
 };
@@ -237,7 +240,8 @@ const char* bgpo_status_string(int status);
 int bgpo_workspace_size(const bgpo_problem* prob, size_t* bytes);
 
 /* The layout bgpo_workspace_size measures for `prob` (see the backward
- * modes above): samples per unit, units per dW GEMM (stored mode), capacity of
+ * modes above): samples per unit, units per dW GEMM (stored mode; with every
+ * position masked: of a large head as many share one as fit), capacity of
  * the dX split partials, vocabulary chunk width (0 = stored exponentials), the
  * workspace bytes and whether the layout keeps a slab-major copy of W_head
  * (the default layout and the budget layouts of least estimated time do; a
@@ -250,7 +254,8 @@ typedef struct bgpo_plan_info {
   int32_t vocab_chunk;
   uint64_t workspace_bytes;
   int32_t w_copy;       /* 1: the workspace holds the slab-major bf16 copy of W_head
-                           that the dX GEMM reads; 0: the dX GEMM reads W_head itself */
+                           that the dX GEMM reads (calls over few positions leave it
+                           out); 0: the dX GEMM reads W_head itself */
 } bgpo_plan_info;
 
 int bgpo_workspace_plan(const bgpo_problem* prob, bgpo_plan_info* info);

@@ -129,6 +129,7 @@ size_t workspace_layout(const Dims& dm, const Plan& pl, void* base, Workspace* w
   w.dw_batch = dw_batch;
   w.KT = KT;
   w.chunk = chunk;
+  w.max_cols = 0;
   w.g_used = (int)G;
   const size_t end = off;
   for (int64_t u = 1; u < n_units; ++u) {
@@ -422,13 +423,15 @@ struct Act {
 // forward part of the unit of samples j0 .. j0 + n_s - 1: masks .. l (and,
 // with backward, g / loss / scale); W: the caller's W_head in the first unit of
 // a call, whose copies are made beside the masks, else NULL; prev_unit: record
-// of the previous unit of the dW batch (NULL for the first)
+// of the previous unit of the dW batch (NULL for the first); flush_dw: dW, where
+// the unit may have to start a new batch by itself, else NULL
 static int run_forward_unit(const bgpo_problem* p, Workspace& ws, Timer& tm, int grid, int j0,
                             int n_s, const void* W, const Act& act, const int32_t* targets,
                             const uint8_t* resp, const float* adv, const double* ell_old, double loss_scale,
                             double* ell, double* g, int32_t* n_masked, float* t_out,
                             int32_t* flags, bool backward, bool store_u,
-                            const SampleMeta* prev_unit, const double* dbar, hipStream_t s) {
+                            const SampleMeta* prev_unit, const double* dbar, float* flush_dw,
+                            hipStream_t s) {
   const Dims dm = dims_of(p);
   ws.g_used = n_s;
   const DxPlan plan = dx_plan(ws, dm.d, dm.V, grid);
@@ -447,6 +450,11 @@ static int run_forward_unit(const bgpo_problem* p, Workspace& ws, Timer& tm, int
                           p->seq_id_base, &ws, nullptr, n_masked + j0, dm.n_t, t_j0, dm.n_t, dm.V,
                           prev_unit, plan, ws.mask_scratch, false, s));
   BGPO_TRY(tm.end(n_s));
+  if (flush_dw) {
+    BGPO_TRY(tm.begin(BGPO_K_DW));
+    BGPO_TRY(launch_gemm_dw_flush(ws, flush_dw, dm.d, dm.V, grid, s));
+    BGPO_TRY(tm.end(0));   // (whether it has anything to do is not known here)
+  }
   BGPO_TRY(tm.begin(BGPO_K_GATHER));
   if (act.gamma)
     BGPO_TRY(launch_row_rms(act.at(j0), act.f32, act.stride, dm.B, ws, act.gamma, dm.d, act.eps,
@@ -628,7 +636,7 @@ static int bwd_retained(const bgpo_problem* prob, const Plan& pl, const Act& act
     const int st = run_forward_unit(prob, U[u], tm, grid, j0, n_s, u ? nullptr : W_head, act, targets,
                                     resp_mask, nullptr, nullptr, 0.0, ell, nullptr, n_masked, t_out,
                                     status_flags, false, true, u ? U[u - 1].unit() : nullptr,
-                                    nullptr, s);
+                                    nullptr, nullptr, s);
     if (st != BGPO_OK) return st;
   }
   const double* dbar = nullptr;
@@ -685,12 +693,17 @@ static int elbo_fwd_impl(const bgpo_problem* prob, const Act& act, const void* W
     const int n_s = std::min<int>(j_end - j0, (int)ws.G);
     st = run_forward_unit(prob, ws, tm, grid, j0, n_s, W, act, targets, resp_mask, nullptr, nullptr,
                           0.0, ell, nullptr, n_masked, t_out, nullptr, false, false,
-                          nullptr, nullptr, s);
+                          nullptr, nullptr, nullptr, s);
     if (st != BGPO_OK) return st;
   }
   BGPO_TRY(tm.finish());
   return BGPO_OK;
 }
+
+// Bytes of dW from which a dW batch takes as many units as fit (d 2048 V 40000,
+// 328 MB, units of few samples: dW 3.17 -> 2.79 ms); for smaller ones the launches
+// that do nothing weigh what a read-modify-write does.
+constexpr int64_t kFlushBytes = int64_t(256) << 20;
 
 // Whether the slab-major copy of a bf16 W, where the plan has room for it, is
 // worth its making for a call over so many positions of its samples (else the
@@ -756,7 +769,7 @@ static int elbo_bwd_impl(const bgpo_problem* prob, const Act& act, const void* W
       const int n_s = std::min<int>(prob->n_t - j0, (int)ws.G);
       st = run_forward_unit(prob, ws, tm, grid, j0, n_s, W_new, act, targets, resp_mask, nullptr,
                             nullptr, 0.0, ell, nullptr, n_masked, t_out, status_flags, false,
-                            false, nullptr, nullptr, s);
+                            false, nullptr, nullptr, nullptr, s);
       if (st != BGPO_OK) return st;
     }
     BGPO_TRY(tm.begin(BGPO_K_ELL));
@@ -766,7 +779,16 @@ static int elbo_bwd_impl(const bgpo_problem* prob, const Act& act, const void* W
   }
   const int j_end = prob->j_begin + prob->j_count;
   const bool store_u = !ws.chunk;   // stored mode keeps the forward's exponentials
-  int in_batch = 0;        // units already in the current dW batch
+  int in_batch = 0;        // units already in the current dW batch (at most, with max_cols)
+  // The dW buffers hold dw_batch units with every position masked, and about
+  // twice as many as masks fall.  Where the read-modify-write of a large dW is
+  // worth it, a unit starts a new batch only when its rows no longer fit, which
+  // the mask kernel sees: from the first unit that might not fit, every unit is
+  // preceded by a dW GEMM that does nothing unless its record asks for it (4 us).
+  // At d 4096 V 126464, units of 8 samples of 4096 positions, n_t 64: dW 97.6 ->
+  // 97.0 ms of 300.5; units of one of 2048 (2 GiB) n_t 8: 12.8 -> 11.8 of 28.2, of
+  // two (3 GiB) n_t 24: 28.0 -> 24.4 of 75.3.
+  ws.max_cols = store_u && (int64_t)dm.d * dm.V * 4 >= kFlushBytes ? ws.KT : 0;
   const SampleMeta* last = nullptr;   // the record of the previous unit
   for (int j0 = prob->j_begin; j0 < j_end; j0 += (int)ws.G, W_new = nullptr) {
     const int n_s = std::min<int>(j_end - j0, (int)ws.G);
@@ -778,11 +800,13 @@ static int elbo_bwd_impl(const bgpo_problem* prob, const Act& act, const void* W
     // stored mode: one dW GEMM per batch of units, K over all their rows (the
     // recompute mode accumulates dW chunk by chunk)
     ++in_batch;
-    const bool ends_batch = !ws.chunk && (in_batch == (int)ws.dw_batch || j0 + n_s >= j_end);
+    const bool ends_batch = !ws.chunk && (j0 + n_s >= j_end ||
+                                          (in_batch == (int)ws.dw_batch && !ws.max_cols));
+    float* const flush_dw = ws.max_cols && in_batch > (int)ws.dw_batch ? dW : nullptr;
     const int dw_units = ends_batch ? in_batch : 0;
     st = run_forward_unit(prob, ws, tm, grid, j0, n_s, W_new, act, targets, resp_mask, adv, ell_old,
                           loss_scale, ell, g, n_masked, t_out, status_flags, true, store_u,
-                          prev, dbar, s);
+                          prev, dbar, flush_dw, s);
     if (st != BGPO_OK) return st;
     st = unit_backward(ws, act, j0, prob->j_begin, static_cast<const uint16_t*>(W_head),
                        loss_scale, g, loss, dX,

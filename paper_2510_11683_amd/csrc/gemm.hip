@@ -64,7 +64,8 @@ struct GemmParams {
   int64_t ldb;               // rows per slab (B is always slab-major)
   int dyn_boff;              // B starts at row meta->col_off (the unit's rows of dZ)
   int M, N, K;               // static extents
-  int dyn_m, dyn_n, dyn_k;   // extents taken from the device sample metadata
+  int dyn_m, dyn_n, dyn_k;   // extents taken from the device sample metadata (dyn_k 2: of the
+                             // batch before the unit)
   int dyn_split;             // K split taken from the metadata (dX)
   int n_split;               // K split count
   int64_t k_split;           // K per split (multiple of BK)
@@ -263,7 +264,8 @@ __device__ __forceinline__ void gemm4w(const GemmParams& p, uint4* smem, uint32_
     n_valid = p.meta->n_rows;
     N = BN < kRowPad ? (n_valid + BN - 1) / BN * BN : p.meta->n_rows_pad;
   }
-  if (p.dyn_k) K = p.meta->col_end;    // batched dW: all samples' columns (multiple of 64)
+  // batched dW: all samples' columns (multiple of 64)
+  if (p.dyn_k) K = p.dyn_k == 2 ? p.meta->flush_cols : p.meta->col_end;
   // first row of the unit in dZ (EPI_FWDU), read once into a scalar register
   const int zt_col = EPI == EPI_FWDU ? __builtin_amdgcn_readfirstlane(p.meta->col_off) : 0;
   // first row of B (the unit's rows of a dZ shared by a dW batch)
@@ -841,6 +843,13 @@ hipError_t launch_gemm_dx(const Workspace& ws, const uint16_t* W, int d, int V, 
 
 hipError_t launch_gemm_dw(const Workspace& ws, float* dW, int d, int V, int grid, hipStream_t s) {
   return launch_tiled<EPI_F32_ACCUM, A_MSLAB>(small_tiles(V, d, grid), grid, dw_params(ws, dW, d, V), s);
+}
+
+hipError_t launch_gemm_dw_flush(const Workspace& ws, float* dW, int d, int V, int grid,
+                                hipStream_t s) {
+  GemmParams p = dw_params(ws, dW, d, V);
+  p.dyn_k = 2;
+  return launch_tiled<EPI_F32_ACCUM, A_MSLAB>(small_tiles(V, d, grid), grid, p, s);
 }
 
 hipError_t launch_gemm_dx_dw(const Workspace& ws, const uint16_t* W, float* dW, int d, int V,

@@ -57,7 +57,9 @@ struct SampleMeta {
   int32_t dx_kslab;    // 64-wide vocabulary slabs per split
   int32_t s_rows;      // N_j: masked rows of this sample (all responses)
   int32_t s_row_off;   // first row of this sample in the unit's row space
-  int32_t pad[24];     // one 128-byte line per record
+  int32_t flush_cols;  // columns of the dW batch to be accumulated before this unit's rows are written
+                       // (it starts the next batch), 0: none
+  int32_t pad[23];     // one 128-byte line per record
 };
 
 // Rows per partial sum of dgamma.
@@ -124,6 +126,8 @@ struct Workspace {
   int64_t KT;          // dw_batch * RP: columns of H_c^T, rows of the stored dZ
   int64_t ldz;         // rows per slab of dZ: KT + kDzPadRows (stored), RP (recompute)
   int64_t chunk;       // 0: stored exponentials; > 0: recompute backward, vocabulary chunk width
+  int64_t max_cols;    // columns after which a unit starts a new dW batch by itself (0: batches of
+                       // dw_batch units, ended by the host)
   int g_used;          // samples in the current unit (host side; its record meta[g_used - 1]
                        // describes the unit)
   const SampleMeta* unit() const { return meta + (g_used - 1); }
@@ -222,6 +226,10 @@ hipError_t launch_dx_reduce_rmsnorm(const Workspace& ws, int B, const void* x, b
                                     const float* gamma, float* dx, int64_t stride, float* dgamma,
                                     int d, hipStream_t s);
 hipError_t launch_gemm_dw(const Workspace& ws, float* dW, int d, int V, int grid, hipStream_t s);
+// dW of the batch before this unit, if the unit's rows no longer fit beside it
+// (its record says so; else the launch does nothing)
+hipError_t launch_gemm_dw_flush(const Workspace& ws, float* dW, int d, int V, int grid,
+                                hipStream_t s);
 // the dX GEMM of a unit that ends a dW batch of `units` units, together with
 // the batch's dW GEMM where that pays (*paired; else dW is still to do)
 hipError_t launch_gemm_dx_dw(const Workspace& ws, const uint16_t* W, float* dW, int d, int V,

@@ -84,15 +84,21 @@ struct MaskOut {
   uint32_t* t24;         // [G, B]  every sample's timesteps
   SampleMeta* meta;      // [G]     every sample's record
   int row_cap;           // rows the unit holds (padding is written up to it)
+  int max_cols;          // columns of a dW batch, 0: batches of whole units
 };
 
-// The record of a sample whose `total` masked rows follow row0 rows of its
-// unit, with the unit's columns from col0 (called by one whole wave).
-__device__ void write_record(SampleMeta* m, int row0, int col0, int total, const DxPlan& plan,
-                             int lane) {
+// The record of a sample whose `total` masked rows follow row0 rows of its unit
+// (called by one whole wave).  The unit's columns follow the prev_end columns of
+// the units before it in the dW batch; with max_cols > 0, where its (padded) rows
+// do not fit after them any more, it starts the next batch at column 0 and asks
+// for the dW GEMM over the columns so far.
+__device__ void write_record(SampleMeta* m, int row0, int prev_end, int total, int max_cols,
+                             const DxPlan& plan, int lane) {
   if (!m) return;
   const int rows = row0 + total;
   const int rows_pad = (rows + kRowPad - 1) / kRowPad * kRowPad;
+  const bool flush = max_cols > 0 && prev_end > max_cols - rows_pad;
+  const int col0 = flush ? 0 : prev_end;
   int split, kslab;
   choose_dx_split((rows + plan.tile - 1) / plan.tile, plan, lane, &split, &kslab);
   if (lane == 0) {
@@ -104,6 +110,7 @@ __device__ void write_record(SampleMeta* m, int row0, int col0, int total, const
     m->s_row_off = row0;
     m->dx_split = split;
     m->dx_kslab = kslab;
+    m->flush_cols = flush ? prev_end : 0;
   }
 }
 
@@ -229,7 +236,7 @@ __device__ __forceinline__ void mask_sample(const MaskArgs& a, int g, int n_samp
     for (int e = 0; e < 4; ++e)
       if (p0 + e < p1) tgt[e] = targets[p0 + e];
   // the unit's columns follow the previous unit's of the dW batch
-  const int col0 = prev ? prev->col_end : 0;
+  const int prev_end = prev ? prev->col_end : 0;
   MaskWalker mw{k0, k1, seq_base, L, j0 + g};
 
   // counts of the unit's earlier samples, then this sample's timesteps at
@@ -307,7 +314,7 @@ __device__ __forceinline__ void mask_sample(const MaskArgs& a, int g, int n_samp
     }
   }
   if (wave == THREADS / 64 - 1)
-    write_record(out.meta ? out.meta + g : nullptr, row0, col0, total, plan, lane);
+    write_record(out.meta ? out.meta + g : nullptr, row0, prev_end, total, out.max_cols, plan, lane);
   if (tid == 0) sSeg[B] = total;
   __syncthreads();
 
@@ -427,7 +434,8 @@ __global__ __launch_bounds__(1024) void k_mask_scan(
     const uint32_t* __restrict__ bits, const int32_t* __restrict__ wprefix,
     const int32_t* __restrict__ blk_count,
     int32_t* __restrict__ blk_off, int nblk, int B, int L, int g, MaskOut out,
-    int32_t* __restrict__ nm_out, int nm_stride, const SampleMeta* prev, DxPlan plan) {
+    int32_t* __restrict__ nm_out, int nm_stride, const SampleMeta* prev,
+    const SampleMeta* prev_unit, DxPlan plan) {
   __shared__ int s_total;
   __shared__ int32_t s_off[kMbMaxBlocks];
   const int tid = threadIdx.x;
@@ -443,7 +451,7 @@ __global__ __launch_bounds__(1024) void k_mask_scan(
   __syncthreads();
   const int total = s_total;
   const int row0 = (g > 0 && prev) ? prev->n_rows : 0;
-  const int col0 = prev ? (g > 0 ? prev->col_off : prev->col_end) : 0;
+  const int prev_end = prev_unit ? prev_unit->col_end : 0;
   for (int b = tid; b < B; b += 1024) {
     const int s0 = masked_before(bits, wprefix, s_off, (int64_t)b * L);
     const int s1 = b + 1 < B ? masked_before(bits, wprefix, s_off, (int64_t)(b + 1) * L) : total;
@@ -453,7 +461,7 @@ __global__ __launch_bounds__(1024) void k_mask_scan(
   const int rows = row0 + total;
   const int rows_pad = (rows + kRowPad - 1) / kRowPad * kRowPad;
   if (tid == 0 && out.seg_off) out.seg_off[B] = rows;
-  if (tid < 64) write_record(out.meta, row0, col0, total, plan, tid);
+  if (tid < 64) write_record(out.meta, row0, prev_end, total, out.max_cols, plan, tid);
   const int pad_end = min(rows_pad, out.row_cap);
   for (int r = rows + tid; r < pad_end; r += 1024) {
     if (out.row_tgt) out.row_tgt[r] = 0;
@@ -500,7 +508,7 @@ static MaskArgs mask_args(const uint8_t* resp, const int32_t* targets, int B, in
                           int t_mode, uint64_t seed, uint32_t seq_base, const Workspace* ws,
                           int32_t* idx_out, int32_t* n_masked_out, int nm_stride, float* t_out,
                           int t_stride, int V, const SampleMeta* prev_unit, const DxPlan& plan) {
-  MaskOut out{idx_out, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0};
+  MaskOut out{idx_out, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0};
   if (ws) {
     out.idx = ws->idx;
     out.inv = ws->inv;
@@ -510,6 +518,7 @@ static MaskArgs mask_args(const uint8_t* resp, const int32_t* targets, int B, in
     out.t24 = ws->t24;
     out.meta = ws->meta;
     out.row_cap = (int)ws->RP;
+    out.max_cols = (int)ws->max_cols;
   }
   return MaskArgs{resp, targets, B, L, n_t, j0, t_mode, (uint32_t)(seed & 0xFFFFFFFFu),
                   (uint32_t)(seed >> 32), seq_base, out, n_masked_out, nm_stride, t_out, t_stride, V,
@@ -562,7 +571,7 @@ hipError_t launch_masks(const uint8_t* resp, const int32_t* targets, int B, int 
     if ((e = hipGetLastError()) != hipSuccess) return e;
     k_mask_scan<<<1, 1024, 0, s>>>(bits, wprefix, blk_count, blk_off, (int)nblk, B, L, g, og,
                                    n_masked_out ? n_masked_out + g : nullptr, nm_stride, prev,
-                                   plan);
+                                   prev_unit, plan);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     k_mask_scatter<<<(unsigned)nblk, kMbThreads, 0, s>>>(bits, wprefix, blk_off, targets, B, L, P,
                                                          g, V, og, prev);

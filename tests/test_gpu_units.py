@@ -217,3 +217,32 @@ def test_w_in_place_or_copied(B, L, V):
     assert rel_maxnorm(o["dX"], ref.dX) <= 2e-2
     assert rel_maxnorm(o["dW"], ref.dW) <= 2e-2
     assert rel_maxnorm(q.out()["dX"], o["dX"]) <= 1e-5
+
+
+@pytest.mark.parametrize("budget_mib", [400, 450])
+def test_dw_batches_end_where_rows_no_longer_fit(budget_mib):
+    """Units of one sample on buffers for one and for two fully masked units:
+    how many of the partly masked ones share a dW GEMM follows from their rows
+    (responses of 500 with random timesteps: some pairs fit in one unit's rows,
+    some do not).  The whole range in one call against one call per sample on
+    the same layout, which flushes after each: dX bit for bit, dW up to the
+    order of fp32 sums (1e-5)."""
+    b = lib()
+    w = workloads.Workload("flush", B=2, L=500, d=1024, V=65600, n_t=10, adv="normal", group=2,
+                           targets="uniform", data_seed=2500, philox_seed=0xB6B70001)
+    plan = b.bgpo_workspace_plan(b.Problem(2, 500, 1024, 65600, 10, ws_budget=budget_mib << 20))
+    assert (plan["mode"], plan["samples_per_unit"], plan["dw_batch"]) == ("stored", 1, budget_mib // 225)
+    x = workloads.generate(w)
+    outs = []
+    for ranges in ([(0, 10)], [(j, 1) for j in range(10)]):
+        r = Runner(w, x, ws_budget=budget_mib << 20)
+        for j0, n in ranges:
+            r.bwd(j_begin=j0, j_count=n)
+        outs.append(r.out())
+    one, many = outs
+    rows = one["nm"].sum(0)
+    fits = [(int(a) + 63) // 64 * 64 + (int(c) + 255) // 256 * 256 <= 1024 for a, c in zip(rows, rows[1:])]
+    assert any(fits) and not all(fits)
+    for k in ("ell", "g", "nm", "dX"):
+        assert np.array_equal(one[k], many[k]), k
+    assert rel_maxnorm(one["dW"], many["dW"]) <= 1e-5
