@@ -36,10 +36,15 @@ __device__ __forceinline__ void welford(float g, float& mean, float& m2, float i
 
 // k = number of estimates already folded in: delta = g - mean,
 // mean += delta / (k + 1), m2 += delta (g - mean_new).  Four elements per
-// thread, one step per workgroup (the grid covers n up to 2^40 elements; a
-// loop over 4096 resident workgroups kept fewer loads in flight).  Bound by
-// HBM, 20 bytes per element: 518M elements 2215 us (4.7 TB/s) in the loop,
-// 1707 us (6.1 TB/s) so, streaming.
+// thread, one step per workgroup (up to kMaxUpdateBlocks of them; a loop over
+// 4096 resident workgroups kept fewer loads in flight).  Bound by HBM, 20 bytes
+// per element: 518M elements 2215 us (4.7 TB/s) in the loop, 1707 us (6.1
+// TB/s) so, streaming.
+//
+// A launch takes fewer than 2^32 work-items; above 2^33 elements the workgroups
+// take several steps each.
+constexpr int64_t kMaxUpdateBlocks = int64_t(1) << 23;
+
 template <bool NT>
 __global__ __launch_bounds__(256) void k_moments_update(const float* __restrict__ g,
                                                         float* __restrict__ mean,
@@ -159,7 +164,7 @@ int bgpo_moments_update(const float* g, float* mean, float* m2, int64_t n, int32
   if (!g || !mean || !m2 || n < 0 || count < 0) return BGPO_ERR_INVALID_ARG;
   if (((uintptr_t)g | (uintptr_t)mean | (uintptr_t)m2) & 15) return BGPO_ERR_INVALID_ARG;
   if (n == 0) return BGPO_OK;
-  const int64_t blocks = std::min<int64_t>((n + 1023) / 1024, int64_t(1) << 30);
+  const int64_t blocks = std::min<int64_t>((n - 1) / 1024 + 1, kMaxUpdateBlocks);
   const auto kernel = n >= kStreamElements ? k_moments_update<true> : k_moments_update<false>;
   kernel<<<(unsigned)blocks, 256, 0, (hipStream_t)stream>>>(g, mean, m2, n, count);
   return hipGetLastError() == hipSuccess ? BGPO_OK : BGPO_ERR_HIP;
