@@ -13,6 +13,17 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));  // 32x32 MFMA accumu
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
+// Workgroups of 256 numbered in one line.  A launch takes fewer than 2^32
+// work-items in x, so the line is folded into rows of kGridRow workgroups; the
+// last row may reach past the end.
+constexpr int64_t kGridRow = int64_t(1) << 23;
+inline dim3 line_grid(int64_t wgs) {
+  return dim3((unsigned)(wgs < kGridRow ? wgs : kGridRow), (unsigned)((wgs + kGridRow - 1) / kGridRow));
+}
+__device__ __forceinline__ unsigned line_index() {
+  return blockIdx.y * (unsigned)kGridRow + blockIdx.x;
+}
+
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11): 10 rounds of two 32x32->64
 // multiplies with key mixing; the key advances by the Weyl constants between
 // rounds.  (The products are 64-bit, one v_mad_u64_u32 each: high and low

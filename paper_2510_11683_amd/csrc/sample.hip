@@ -707,16 +707,17 @@ __global__ __launch_bounds__(256) void k_gather(RowInput<T> in, const SampleMeta
   __shared__ uint16_t tile[64][72];
   const int tid = threadIdx.x, d = in.d;
   const int N = meta->n_rows;
-  if (blockIdx.x >= n_tile_wg) {
-    const int row = (blockIdx.x - n_tile_wg) * 4 + (tid >> 6), lane = tid & 63;
-    if (row >= N) return;
+  const unsigned wg = line_index();
+  if (wg >= n_tile_wg) {
+    const int row = (wg - n_tile_wg) * 4 + (tid >> 6), lane = tid & 63;
+    if (gamma || row >= N) return;
     const float z = target_logit<false>(in.row(row), WT + (int64_t)row_tgt[row] * d, 0.f, nullptr,
                                         d, lane);
     if (lane == 0) ztgt[row] = z;
     return;
   }
   const int cts = d / 64;
-  const int r0 = (int)(blockIdx.x / cts) * 64, c0 = (int)(blockIdx.x % cts) * 64;
+  const int r0 = (int)(wg / cts) * 64, c0 = (int)(wg % cts) * 64;
   if (r0 >= meta->n_rows_pad) return;
   const int coff = meta->col_off;
 #pragma unroll
@@ -749,8 +750,8 @@ __global__ __launch_bounds__(256) void k_gather(RowInput<T> in, const SampleMeta
 hipError_t launch_gather(const void* hidden, bool f32, int64_t stride, int B, const float* gamma,
                          const Workspace& ws, int d, hipStream_t s) {
   const int64_t rows = ws.g_used * ws.NP;
-  const unsigned tiles = (unsigned)(rows / 64 * (d / 64));
-  const unsigned grid = tiles + (gamma ? 0 : (unsigned)(rows / 4));
+  const unsigned tiles = (unsigned)(rows / 64 * (d / 64));   // at most 2^26
+  const dim3 grid = line_grid(tiles + (gamma ? 0 : rows / 4));
   if (f32)
     k_gather<float><<<grid, 256, 0, s>>>(row_input<float>(hidden, stride, B, ws, d), ws.unit(),
                                          gamma, ws.inv_rms, ws.Hc, ws.HcT, ws.RP, tiles, ws.WT,
@@ -786,6 +787,7 @@ __device__ __forceinline__ void transpose_w_tile(const T* __restrict__ W, uint16
                                                  uint16_t* __restrict__ Wk, int d, int V,
                                                  unsigned wg, WTile& tile) {
   const unsigned kts = d / 64, vts = V / 64;
+  if (wg >= kts * vts) return;
   const int v0 = (int)(NT ? wg / kts : wg % vts) * 64;
   const int k0 = (int)(NT ? wg % kts : wg / vts) * 64;
   const int tid = threadIdx.x;
@@ -815,7 +817,7 @@ __global__ __launch_bounds__(256) void k_transpose_w(const T* __restrict__ W,
                                                      uint16_t* __restrict__ WT,
                                                      uint16_t* __restrict__ Wk, int d, int V) {
   __shared__ WTile tile;
-  transpose_w_tile<T, NT>(W, WT, Wk, d, V, blockIdx.x, tile);
+  transpose_w_tile<T, NT>(W, WT, Wk, d, V, line_index(), tile);
 }
 
 // The start of a call in one launch: the masks of its first unit (one workgroup
@@ -834,10 +836,11 @@ __global__ __launch_bounds__(256, 8) void k_masks_and_w(MaskArgs a, int n_sample
     MaskShared<256, kPrepMaxB> mask;
     WTile tile;
   } sh;
-  if ((int)blockIdx.x < n_samples)
-    mask_sample<256, kPrepMaxB>(a, blockIdx.x, n_samples, sh.mask);
+  const unsigned wg = line_index();
+  if (wg < (unsigned)n_samples)
+    mask_sample<256, kPrepMaxB>(a, wg, n_samples, sh.mask);
   else
-    transpose_w_tile<T, NT>(W, WT, Wk, d, a.V, blockIdx.x - n_samples, sh.tile);
+    transpose_w_tile<T, NT>(W, WT, Wk, d, a.V, wg - n_samples, sh.tile);
 }
 
 // Bytes of an output of k_transpose_w from which it is streamed, well past what
@@ -847,7 +850,7 @@ constexpr int64_t kStreamBytes = int64_t(768) << 20;
 
 hipError_t launch_transpose_w(const void* W, bool f32, uint16_t* WT, uint16_t* Wk, int d, int V,
                               hipStream_t s) {
-  const unsigned grid = (unsigned)(V / 64) * (unsigned)(d / 64);   // at most 2^24
+  const dim3 grid = line_grid((int64_t)(V / 64) * (d / 64));   // at most 2^24 workgroups
   const bool nt = (int64_t)d * V * 2 >= kStreamBytes;
   if (f32)
     (nt ? k_transpose_w<float, true> : k_transpose_w<float, false>)<<<grid, 256, 0, s>>>(
@@ -877,7 +880,7 @@ hipError_t launch_masks_and_w(const void* W, bool f32, const uint8_t* resp, cons
   if (!*masks_done) return launch_transpose_w(W, f32, ws.WT, ws.Wk, d, V, s);
   const MaskArgs a = mask_args(resp, targets, B, L, n_t, j0, t_mode, seed, seq_base, &ws, nullptr,
                                n_masked_out, n_t, t_out, n_t, V, nullptr, plan);
-  const unsigned grid = (unsigned)ws.g_used + (unsigned)(V / 64) * (unsigned)(d / 64);
+  const dim3 grid = line_grid(ws.g_used + (int64_t)(V / 64) * (d / 64));
   const bool nt = (int64_t)d * V * 2 >= kStreamBytes;
   if (f32)
     (nt ? k_masks_and_w<float, true> : k_masks_and_w<float, false>)<<<grid, 256, 0, s>>>(

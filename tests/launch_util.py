@@ -57,7 +57,7 @@ def _child(recorder, lib_path):
                 c.append(ctypes.c_void_p((i + 1) << 44))
             elif a == "ws":
                 n = ctypes.c_size_t(0)
-                assert lib.bgpo_workspace_size(prob, ctypes.byref(n)) == 0
+                assert lib.bgpo_workspace_size(prob, ctypes.byref(n)) == 0, (fn, args)
                 c += [ctypes.c_void_p((i + 1) << 44), n]
             elif a == "timing":
                 c.append(ctypes.byref(timing))
