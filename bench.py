@@ -305,23 +305,26 @@ def main():
         torch.cuda.synchronize()
 
     kt = timing.as_dict()
-    # algorithmic FLOPs: each GEMM class does 2 * N_j * d * V per sample
+    # algorithmic FLOPs: each GEMM class does 2 * N_j * d * V per sample.  In
+    # small problems the dX launch that ends a dW batch does the batch's dW too:
+    # the class then has no rate of its own (fewer dW launches than batches)
     gemm_flop_per_step = 2.0 * tokens * d * V
+    batches = -(-(-(-nt // plan["samples_per_unit"])) // plan["dw_batch"])
+    paired = plan["mode"] == "stored" and kt["dw"][1] < args.steps * batches
     per_kernel = {}
     for k, (kms, n) in kt.items():
         if n == 0:
             continue
         e = {"ms_per_step": kms / args.steps, "launches_per_step": n / args.steps,
              "avg_launch_us": 1e3 * kms / n}
-        if k in GEMM_CLASSES:
+        if k in GEMM_CLASSES and not (paired and k in ("dx", "dw")):
             e["tflops"] = gemm_flop_per_step / (kms / args.steps / 1e3) / 1e12
         per_kernel[k] = e
     # HBM-bound kernel classes: achieved bandwidth from the committed counter
     # bytes and from the algorithmic bytes, against the 8 TB/s peak
     def algo_bytes(k, launches):                         # per launch
         rows = tokens / launches                         # masked rows one launch processes
-        # (softmax_grad: three small kernels per unit, counter bytes only;
-        # dx_reduce: depends on the split count)
+        # (softmax_grad, dx_reduce: counter bytes only)
         return {"gather": 6.0 * rows * d,                # read rows, write H_c and H_c^T
                 "transpose_w": 6.0 * d * V}.get(k)       # read W, write W^T and W slab-major
     for k, e in per_kernel.items():
@@ -336,12 +339,12 @@ def main():
         if ab:
             e["algorithmic_gbs"] = ab / secs / 1e9
             e["algorithmic_hbm_frac"] = e["algorithmic_gbs"] / PEAK_HBM_GBS
-    dom = max((k for k in per_kernel if k in GEMM_CLASSES), key=lambda k: per_kernel[k]["ms_per_step"])
+    dom = max((k for k in per_kernel if "tflops" in per_kernel[k]), key=lambda k: per_kernel[k]["ms_per_step"])
     achieved = per_kernel[dom]["tflops"]
     # GEMM passes per sample: forward logits, dX, dW (stored mode: the
     # backward reuses the forward's exponentials, so executed = useful 6 d V),
     # plus the chunked logits recompute in the recompute mode (8 d V executed)
-    passes = sum(1 for k in GEMM_CLASSES if k in per_kernel)
+    passes = sum(1 for k in GEMM_CLASSES if k in per_kernel or (paired and k == "dw"))
     exec_flops = 2.0 * passes * d * V * value
     useful_flops = 6.0 * d * V * value
 

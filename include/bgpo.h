@@ -202,7 +202,7 @@ enum {
   BGPO_K_TRANSPOSE_W = 0,  /* W[d,V] -> W^T[V,d] staging, once per call (and the masks of the first
                               unit, where they share its launch) */
   BGPO_K_MASK = 1,         /* Philox t and masks + stable compaction */
-  BGPO_K_GATHER = 2,       /* masked hidden rows (RMSNorm applied) -> H_c and H_c^T */
+  BGPO_K_GATHER = 2,       /* masked hidden rows (RMSNorm applied) -> H_c and H_c^T, target logits */
   BGPO_K_FWD = 3,          /* fused LM-head GEMM + online log-sum-exp partials (in the
                               backward it also stores the exponentials) */
   BGPO_K_ELL = 4,          /* partial combine, log p, l, d, g, loss, gradient scale */
@@ -210,8 +210,8 @@ enum {
                               target entries, H_c^T scaled, out-of-range rows recomputed */
   BGPO_K_DX = 6,           /* dZ W^T split over the vocabulary (small problems: and dW, in one launch) */
   BGPO_K_DX_REDUCE = 7,    /* split reduction + scatter-add into dX (+ RMSNorm backward) */
-  BGPO_K_DW = 8,           /* H_c^T dZ accumulated into dW (a launch that only acts where a batch is
-                              full is timed, not counted) */
+  BGPO_K_DW = 8,           /* H_c^T dZ accumulated into dW (of a large head also launches that
+                              only act where a batch is full) */
   BGPO_K_RECOMPUTE = 9,    /* recompute mode: a vocabulary chunk's logits -> its dZ */
   BGPO_K_COUNT = 10
 };
@@ -219,8 +219,8 @@ enum {
 /* Optional per-kernel timing (host memory).  When passed to an entry point,
  * elapsed milliseconds (HIP events on `stream`) and launch counts of every
  * kernel class are ADDED to the record, after the call waits for its events.
- * A launch that does the work of several samples, or several of a class's
- * steps, counts as that many. */
+ * A launch that does the work of two classes counts for the one whose comment
+ * above says so. */
 typedef struct bgpo_timing {
   double ms[BGPO_K_COUNT];
   int64_t launches[BGPO_K_COUNT];

@@ -444,16 +444,18 @@ static int run_forward_unit(const bgpo_problem* p, Workspace& ws, Timer& tm, int
                                 &masks_done));
     BGPO_TRY(tm.end());
   }
-  BGPO_TRY(tm.begin(BGPO_K_MASK));
-  if (!masks_done)
+  if (!masks_done) {
+    int launches = 0;
+    BGPO_TRY(tm.begin(BGPO_K_MASK));
     BGPO_TRY(launch_masks(resp, targets, dm.B, dm.L, dm.n_t, j0, n_s, p->t_mode, p->seed,
                           p->seq_id_base, &ws, nullptr, n_masked + j0, dm.n_t, t_j0, dm.n_t, dm.V,
-                          prev_unit, plan, ws.mask_scratch, false, s));
-  BGPO_TRY(tm.end(n_s));
+                          prev_unit, plan, ws.mask_scratch, false, s, &launches));
+    BGPO_TRY(tm.end(launches));
+  }
   if (flush_dw) {
     BGPO_TRY(tm.begin(BGPO_K_DW));
     BGPO_TRY(launch_gemm_dw_flush(ws, flush_dw, dm.d, dm.V, grid, s));
-    BGPO_TRY(tm.end(0));   // (whether it has anything to do is not known here)
+    BGPO_TRY(tm.end());   // (whether it has anything to do is not known here)
   }
   BGPO_TRY(tm.begin(BGPO_K_GATHER));
   if (act.gamma)
@@ -468,7 +470,7 @@ static int run_forward_unit(const bgpo_problem* p, Workspace& ws, Timer& tm, int
   BGPO_TRY(launch_combine_rows(ws, dm.V, store_u, s));
   BGPO_TRY(launch_seq_terms(ws, dm.B, dm.n_t, j0, adv, ell_old, loss_scale, ell, g, flags,
                             backward, p->bound, dbar, s));
-  BGPO_TRY(tm.end(3));   // (the target logits, formed with the gather, are a step of this class)
+  BGPO_TRY(tm.end(2));
   return BGPO_OK;
 }
 
@@ -529,9 +531,11 @@ int bgpo_sample_masks(const bgpo_problem* prob, const uint8_t* resp_mask, int32_
   const int st = plan_problem(prob, &pl);
   if (st != BGPO_OK) return st;
   if (!resp_mask || !idx || !n_masked || j < 0 || j >= prob->n_t) return BGPO_ERR_INVALID_ARG;
+  int launches = 0;
   if (launch_masks(resp_mask, nullptr, prob->B, prob->L, prob->n_t, j, 1, prob->t_mode, prob->seed,
                    prob->seq_id_base, nullptr, idx, n_masked, 1, t_out, 1, prob->V, nullptr,
-                   DxPlan{1, 1, 1, 1, 256, 13}, nullptr, false, (hipStream_t)stream) != hipSuccess)
+                   DxPlan{1, 1, 1, 1, 256, 13}, nullptr, false, (hipStream_t)stream,
+                   &launches) != hipSuccess)
     return BGPO_ERR_HIP;
   return BGPO_OK;
 }
@@ -572,10 +576,9 @@ static int unit_backward(const Workspace& ws, const Act& act, int j0, int j_begi
                          const uint16_t* W, double loss_scale, const double* g, double* loss,
                          float* dX, float* dgamma, float* dW, const Dims& dm, int grid,
                          int dw_units, Timer& tm, hipStream_t s) {
-  // (one launch; in the stored mode it does the three steps of its class)
   BGPO_TRY(tm.begin(ws.chunk ? BGPO_K_ELL : BGPO_K_SOFTMAX_GRAD));
   BGPO_TRY(launch_row_terms(ws, dm.B, dm.n_t, j0, loss_scale, g, loss, dm.d, dm.V, s));
-  BGPO_TRY(tm.end(ws.chunk ? 0 : 3));
+  BGPO_TRY(tm.end());
   bool paired = false;
   if (!ws.chunk) {
     BGPO_TRY(tm.begin(BGPO_K_DX));
@@ -600,15 +603,16 @@ static int unit_backward(const Workspace& ws, const Act& act, int j0, int j_begi
   }
   BGPO_TRY(tm.begin(BGPO_K_DX_REDUCE));
   float* dXj = dX + (int64_t)(j0 - j_begin) * act.stride;
+  int reduce_launches = 0;
   if (act.gamma)
     BGPO_TRY(launch_dx_reduce_rmsnorm(ws, dm.B, act.at(j0), act.f32, act.gamma, dXj, act.stride,
-                                      dgamma, dm.d, s));
+                                      dgamma, dm.d, s, &reduce_launches));
   else
-    BGPO_TRY(launch_dx_reduce(ws, dm.B, dXj, act.stride, dm.d, s));
-  BGPO_TRY(tm.end(ws.g_used * (act.gamma ? 3 : 1)));   // the norm backward is 3 kernels
-  if (dw_units) {
+    BGPO_TRY(launch_dx_reduce(ws, dm.B, dXj, act.stride, dm.d, s, &reduce_launches));
+  BGPO_TRY(tm.end(reduce_launches));
+  if (dw_units && !paired) {
     BGPO_TRY(tm.begin(BGPO_K_DW));
-    if (!paired) BGPO_TRY(launch_gemm_dw(ws, dW, dm.d, dm.V, grid, s));
+    BGPO_TRY(launch_gemm_dw(ws, dW, dm.d, dm.V, grid, s));
     BGPO_TRY(tm.end());
   }
   return BGPO_OK;
@@ -942,9 +946,11 @@ extern "C" int bgpo_test_mask_multiblock(const bgpo_problem* prob, const uint8_t
   if (!scratch || ((uintptr_t)scratch % 256) != 0 ||
       scratch_bytes < mask_scratch_bytes(prob->B, prob->L))
     return BGPO_ERR_WORKSPACE;
+  int launches = 0;
   if (launch_masks(resp_mask, nullptr, prob->B, prob->L, prob->n_t, j, 1, prob->t_mode, prob->seed,
                    prob->seq_id_base, nullptr, idx, n_masked, 1, t_out, 1, prob->V, nullptr,
-                   DxPlan{1, 1, 1, 1, 256, 13}, scratch, true, (hipStream_t)stream) != hipSuccess)
+                   DxPlan{1, 1, 1, 1, 256, 13}, scratch, true, (hipStream_t)stream,
+                   &launches) != hipSuccess)
     return BGPO_ERR_HIP;
   return BGPO_OK;
 }

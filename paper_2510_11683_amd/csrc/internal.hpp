@@ -161,7 +161,8 @@ struct Plan {
 size_t workspace_layout(const Dims& dm, const Plan& pl, void* base, Workspace* ws,
                         Workspace* units);
 
-// ---- launchers (return hipSuccess or the launch error) ----
+// ---- launchers (return hipSuccess or the launch error; those whose kernel count
+// depends on the problem add it to *launches) ----
 // W_head -> W^T (bf16, row-major) and W (bf16, slab-major with d rows per
 // slab); fp32 W (f32) is rounded to bf16 as it is read
 hipError_t launch_transpose_w(const void* W, bool f32, uint16_t* WT, uint16_t* Wk, int d, int V,
@@ -177,7 +178,7 @@ hipError_t launch_masks(const uint8_t* resp, const int32_t* targets, int B, int 
                         const Workspace* ws, int32_t* idx_out, int32_t* n_masked_out,
                         int nm_stride, float* t_out, int t_stride, int V,
                         const SampleMeta* prev_unit, const DxPlan& plan, void* scratch,
-                        bool force_multi, hipStream_t s);
+                        bool force_multi, hipStream_t s, int* launches);
 // The copies of W, with the masks of a call's first unit in the same launch where
 // its size allows (*masks_done; else they are still to draw).
 hipError_t launch_masks_and_w(const void* W, bool f32, const uint8_t* resp, const int32_t* targets,
@@ -221,10 +222,10 @@ hipError_t launch_gemm_dx(const Workspace& ws, const uint16_t* W, int d, int V, 
 // (stride: elements between the samples' dX and head inputs, 0 = shared; dX
 // and x those of the unit's first sample)
 hipError_t launch_dx_reduce(const Workspace& ws, int B, float* dX, int64_t stride, int d,
-                            hipStream_t s);
+                            hipStream_t s, int* launches);
 hipError_t launch_dx_reduce_rmsnorm(const Workspace& ws, int B, const void* x, bool f32,
                                     const float* gamma, float* dx, int64_t stride, float* dgamma,
-                                    int d, hipStream_t s);
+                                    int d, hipStream_t s, int* launches);
 hipError_t launch_gemm_dw(const Workspace& ws, float* dW, int d, int V, int grid, hipStream_t s);
 // dW of the batch before this unit, if the unit's rows no longer fit beside it
 // (its record says so; else the launch does nothing)

@@ -490,21 +490,22 @@ static DxTarget dx_target(const Workspace& ws, int B, int d, int64_t stride) {
 }
 
 // launches `run` once for the unit, or once per sample where the samples' dX
-// overlap
+// overlap; the number of launches
 template <typename F>
-static void for_disjoint(DxTarget tg, F run) {
+static int for_disjoint(DxTarget tg, F run) {
   if (tg.stride == 0 || tg.stride >= tg.P * tg.d) {
     run(tg);
-  } else {
-    for (tg.only = 0; tg.only < tg.n_samples; ++tg.only) run(tg);
+    return 1;
   }
+  for (tg.only = 0; tg.only < tg.n_samples; ++tg.only) run(tg);
+  return tg.n_samples;
 }
 
 hipError_t launch_dx_reduce(const Workspace& ws, int B, float* dX, int64_t stride, int d,
-                            hipStream_t s) {
+                            hipStream_t s, int* launches) {
   const float* rowf = ws.chunk ? nullptr : ws.row_f;
   const unsigned cols = (unsigned)((d / 4 + 255) / 256);
-  for_disjoint(dx_target(ws, B, d, stride), [&](const DxTarget& tg) {
+  *launches += for_disjoint(dx_target(ws, B, d, stride), [&](const DxTarget& tg) {
     if (stride == 0)
       k_dx_reduce<true><<<dim3((unsigned)ws.P, cols), 256, 0, s>>>(ws.dx_part, tg, ws.unit(), rowf,
                                                                    dX, d, ws.RP * d);
@@ -630,9 +631,9 @@ __global__ __launch_bounds__(64) void k_dgamma_final(const float* __restrict__ g
 }
 
 template <typename T, bool SHARED>
-static void dx_reduce_rmsnorm(const Workspace& ws, int B, const void* x, const float* gamma,
-                              float* dx, int64_t stride, int d, hipStream_t s) {
-  for_disjoint(dx_target(ws, B, d, stride), [&](const DxTarget& tg) {
+static int dx_reduce_rmsnorm(const Workspace& ws, int B, const void* x, const float* gamma,
+                             float* dx, int64_t stride, int d, hipStream_t s) {
+  return for_disjoint(dx_target(ws, B, d, stride), [&](const DxTarget& tg) {
     k_dx_reduce_rmsnorm<T, SHARED><<<(unsigned)(SHARED ? ws.P : ws.g_used * ws.NP), 256, 0, s>>>(
         ws.dx_part, tg, ws.unit(), ws.chunk ? nullptr : ws.row_f, static_cast<const T*>(x), gamma,
         ws.inv_rms, dx, d, ws.RP * d);
@@ -641,13 +642,10 @@ static void dx_reduce_rmsnorm(const Workspace& ws, int B, const void* x, const f
 
 hipError_t launch_dx_reduce_rmsnorm(const Workspace& ws, int B, const void* x, bool f32,
                                     const float* gamma, float* dx, int64_t stride, float* dgamma,
-                                    int d, hipStream_t s) {
-  if (f32)
-    (stride ? dx_reduce_rmsnorm<float, false>
-            : dx_reduce_rmsnorm<float, true>)(ws, B, x, gamma, dx, stride, d, s);
-  else
-    (stride ? dx_reduce_rmsnorm<uint16_t, false>
-            : dx_reduce_rmsnorm<uint16_t, true>)(ws, B, x, gamma, dx, stride, d, s);
+                                    int d, hipStream_t s, int* launches) {
+  const auto reduce = f32 ? (stride ? dx_reduce_rmsnorm<float, false> : dx_reduce_rmsnorm<float, true>)
+                          : (stride ? dx_reduce_rmsnorm<uint16_t, false> : dx_reduce_rmsnorm<uint16_t, true>);
+  *launches += 2 + reduce(ws, B, x, gamma, dx, stride, d, s);   // (dgamma takes two)
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const dim3 g1((unsigned)((d + 255) / 256),

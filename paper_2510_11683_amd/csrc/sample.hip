@@ -530,7 +530,7 @@ hipError_t launch_masks(const uint8_t* resp, const int32_t* targets, int B, int 
                         const Workspace* ws, int32_t* idx_out, int32_t* n_masked_out,
                         int nm_stride, float* t_out, int t_stride, int V,
                         const SampleMeta* prev_unit, const DxPlan& plan, void* scratch,
-                        bool force_multi, hipStream_t s) {
+                        bool force_multi, hipStream_t s, int* launches) {
   const MaskArgs args = mask_args(resp, targets, B, L, n_t, j0, t_mode, seed, seq_base, ws, idx_out,
                                   n_masked_out, nm_stride, t_out, t_stride, V, prev_unit, plan);
   const MaskOut& out = args.out;
@@ -538,6 +538,7 @@ hipError_t launch_masks(const uint8_t* resp, const int32_t* targets, int B, int 
   const int64_t P = (int64_t)B * L;
   if ((P <= kSingleBlockPositions && !force_multi) || !scratch) {
     k_mask_compact<<<n_samples, kMaskThreads, 0, s>>>(args);
+    ++*launches;
     return hipGetLastError();
   }
   // scratch: mask words, block counts and offsets, and (without a unit) the
@@ -576,6 +577,7 @@ hipError_t launch_masks(const uint8_t* resp, const int32_t* targets, int B, int 
     k_mask_scatter<<<(unsigned)nblk, kMbThreads, 0, s>>>(bits, wprefix, blk_off, targets, B, L, P,
                                                          g, V, og, prev);
     if ((e = hipGetLastError()) != hipSuccess) return e;
+    *launches += 4;
   }
   return hipSuccess;
 }

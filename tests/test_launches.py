@@ -1,6 +1,8 @@
 """What the library launches, recorded on the CPU (launch_util.py): every call
-stays within the runtime's launch limits up to its largest sizes."""
+stays within the runtime's launch limits up to its largest sizes, and the
+timing record counts what was launched."""
 import os
+import re
 
 import pytest
 
@@ -60,3 +62,46 @@ def test_launches_at_the_corners_of_the_supported_shapes(recorder):
         for k, n in need.items():      # (a range's last unit may be smaller)
             wgs = [grid[0] * grid[1] for name, grid, _ in r["launches"] if k in name]
             assert not wgs or max(wgs) >= n, (p, fn, k, wgs)
+
+
+# kernel -> class of the timing record (bgpo_timing); k_gemm4w by its epilogue
+# and the layout of its A operand (the dW GEMM's is the transposed one)
+CLASS_OF = {"k_transpose_w": 0, "k_masks_and_w": 0, "k_mask_compact": 1, "k_timesteps": 1, "k_mask_bits": 1,
+            "k_mask_scan": 1, "k_mask_scatter": 1, "k_row_rms": 2, "k_gather": 2, "k_combine_rows": 4,
+            "k_seq_terms": 4, "k_mean_ratio": 4, "k_row_termsILb0E": 4, "k_row_termsILb1E": 5,
+            "k_gemm4w_dx_dw": 6, "k_dx_reduce": 7, "k_dgamma": 7}
+
+
+def _class_of(name):
+    m = re.search(r"k_gemm4wILi(\d)ELi(\d)E", name)
+    if m:
+        epi, layout = int(m[1]), int(m[2])
+        return 3 if epi < 2 else 9 if epi == 4 else 8 if layout == 1 else 6
+    return next(c for k, c in CLASS_OF.items() if k in name)
+
+
+@pytest.mark.parametrize("fn", CALLS)
+@pytest.mark.parametrize("kw", [
+    dict(B=2, L=64, d=128, V=1024, n_t=10),                          # masks beside W, dW beside dX
+    dict(B=2, L=64, d=128, V=1024, n_t=10, vocab_chunk=256),         # recompute
+    dict(B=2, L=64, d=128, V=1024, n_t=10, sample_stride=64 * 128),  # overlapping samples: a reduction each
+    dict(B=2, L=64, d=128, V=1024, n_t=10, sample_stride=2 * 64 * 128),
+    dict(B=2, L=64, d=128, V=1024, n_t=10, bound=3),
+    dict(B=2, L=64, d=128, V=1024, n_t=10, bound=3, retain_samples=1),
+    dict(B=8, L=512, d=256, V=4096, n_t=9),                          # masks of a launch of their own
+    dict(B=1, L=65537, d=64, V=128, n_t=3),                          # multi-block masks
+    dict(B=2, L=500, d=1024, V=65600, n_t=10, ws_budget=400 << 20),  # dW batches that end themselves
+    dict(B=8, L=512, d=4096, V=126464, n_t=64),
+], ids=lambda kw: " ".join(f"{k}={v}" for k, v in kw.items()))
+def test_timing_record_counts_the_launches_made(recorder, fn, kw):
+    """Per class, the record's count is the number of its kernels launched, and
+    every launch lies inside an interval of its class (the recorder's events
+    measure launches)."""
+    from paper_2510_11683_amd import bgpo as b
+    r, = record(recorder, [_call(fn, b.Problem(**kw), "timing", "ptr" if kw.get("bound") else None)])
+    assert r["status"] == 0
+    want = [0] * len(b.KERNEL_CLASSES)
+    for name, _, _ in r["launches"]:
+        want[_class_of(name)] += 1
+    assert dict(zip(b.KERNEL_CLASSES, r["counts"])) == dict(zip(b.KERNEL_CLASSES, want))
+    assert r["ms"] == want
