@@ -47,6 +47,26 @@ int bgpo_test_gemm_split(const uint16_t* A, const uint16_t* B, float* C, int32_t
 int bgpo_test_gemm_tn(const uint16_t* A, const uint16_t* B, float* C, int32_t M, int32_t N,
                       int32_t K, void* stream);
 
+/* Every form of the GEMM core that the library launches:
+ *   C[s][n][m] (+)= sum over K slice s of A[m][k] * B[n][k]
+ * with the slices of bgpo_test_gemm_split, added to C if `accumulate`, on block
+ * tiles of edge `tile` (128 or 256).  a_layout: 0 A [M, K] row-major, 1 A
+ * [M/64][K][64] as in bgpo_test_gemm_tn (accumulate only), 2 A [K/64][M][64];
+ * B [K/64][N][64]; C float [n_split, N, M].  Requires M a multiple of 4 (of 64
+ * in layout 1), N >= 1, K a positive multiple of 64.  Return codes as above. */
+int bgpo_test_gemm(const uint16_t* A, int32_t a_layout, const uint16_t* B, float* C, int32_t M,
+                   int32_t N, int32_t K, int32_t n_split, int32_t accumulate, int32_t tile,
+                   void* stream);
+
+/* Two such GEMMs in one launch on tiles of edge 128, as the dX and dW GEMMs of
+ * small problems run: the first (layout 0 or 2, stored) by the first n_first
+ * workgroups (a multiple of 8 from 8 to 8 below the compute units), the second
+ * (layout 1, one slice, added to C2) by the others. */
+int bgpo_test_gemm_pair(const uint16_t* A, int32_t a_layout, const uint16_t* B, float* C, int32_t M,
+                        int32_t N, int32_t K, int32_t n_split, const uint16_t* A2,
+                        const uint16_t* B2, float* C2, int32_t M2, int32_t N2, int32_t K2,
+                        int32_t n_first, void* stream);
+
 /* The multi-block form of the mask and compaction step (the three passes the
  * library uses above 65536 positions: mask words with per-block counts, a
  * one-block scan of the counts, a scatter), run at any size, with the same

@@ -91,6 +91,8 @@ def _load():
     lib.bgpo_test_gemm_nt.argtypes = [vp, vp, vp, i32, i32, i32, vp]
     lib.bgpo_test_gemm_split.argtypes = [vp, vp, vp, i32, i32, i32, i32, vp]
     lib.bgpo_test_gemm_tn.argtypes = [vp, vp, vp, i32, i32, i32, vp]
+    lib.bgpo_test_gemm.argtypes = [vp, i32, vp, vp, i32, i32, i32, i32, i32, i32, vp]
+    lib.bgpo_test_gemm_pair.argtypes = [vp, i32, vp, vp, i32, i32, i32, i32, vp, vp, vp, i32, i32, i32, i32, vp]
     lib.bgpo_test_mask_scratch_bytes.restype = sz
     lib.bgpo_test_mask_scratch_bytes.argtypes = [P(_Problem)]
     lib.bgpo_test_mask_multiblock.argtypes = [P(_Problem), vp, i32, vp, vp, vp, vp, sz, vp]
@@ -98,6 +100,7 @@ def _load():
               "bgpo_elbo_bwd_accumulate", "bgpo_elbo_bwd_accumulate_noalloc", "bgpo_elbo_fwd_rmsnorm",
               "bgpo_elbo_bwd_accumulate_rmsnorm", "bgpo_moments_update", "bgpo_moments_summary",
               "bgpo_test_gemm_nt", "bgpo_test_gemm_split", "bgpo_test_gemm_tn",
+              "bgpo_test_gemm", "bgpo_test_gemm_pair",
               "bgpo_test_mask_multiblock"):
         getattr(lib, f).restype = ctypes.c_int
     return lib
@@ -406,6 +409,35 @@ def bgpo_test_gemm_tn(A, B, C, stream=None):
     _check(_lib.bgpo_test_gemm_tn(_ptr(A, "A", _BF16, (MS, K, 64)), _ptr(B, "B", _BF16, (K // 64, N, 64)),
                                   _ptr(C, "C", (torch.float32,), (N, M)), M, N, K, _stream(stream)),
            "bgpo_test_gemm_tn")
+
+
+# layouts of the first operand of bgpo_test_gemm: [M, K], [M/64, K, 64], [K/64, M, 64]
+GEMM_A_ROW, GEMM_A_MSLAB, GEMM_A_KSLAB = 0, 1, 2
+
+
+def _gemm_operands(A, layout, B, C):
+    """Checked pointers and sizes (A, layout, B, C, M, N, K, n_split) of a hooked GEMM."""
+    K, N = B.shape[0] * 64, B.shape[1]
+    M, n_split = C.shape[2], C.shape[0]
+    shape = {GEMM_A_ROW: (M, K), GEMM_A_MSLAB: (M // 64, K, 64), GEMM_A_KSLAB: (K // 64, M, 64)}[layout]
+    return (_ptr(A, "A", _BF16, shape), layout, _ptr(B, "B", _BF16, (K // 64, N, 64)),
+            _ptr(C, "C", (torch.float32,), (n_split, N, M)), M, N, K, n_split)
+
+
+def bgpo_test_gemm(A, layout: int, B, C, accumulate: bool, tile: int, stream=None):
+    """Test hook: C[s, n, m] (+)= sum over K slice s of A[m, k] B[n, k] on block
+    tiles of edge `tile`; A in the given layout, B [K/64, N, 64], C float32
+    [n_split, N, M]."""
+    _check(_lib.bgpo_test_gemm(*_gemm_operands(A, layout, B, C), int(accumulate), int(tile),
+                               _stream(stream)), "bgpo_test_gemm")
+
+
+def bgpo_test_gemm_pair(A, layout: int, B, C, A2, B2, C2, n_first: int, stream=None):
+    """Test hook: the stored GEMM of (A, B, C) by n_first workgroups beside the
+    accumulated one of (A2 [M/64, K, 64], B2, C2 [1, N, M]) in one launch."""
+    a2, _, b2, c2, M2, N2, K2, _ = _gemm_operands(A2, GEMM_A_MSLAB, B2, C2)
+    _check(_lib.bgpo_test_gemm_pair(*_gemm_operands(A, layout, B, C), a2, b2, c2, M2, N2, K2,
+                                    int(n_first), _stream(stream)), "bgpo_test_gemm_pair")
 
 
 def device_inputs(x: dict, device="cuda") -> dict:

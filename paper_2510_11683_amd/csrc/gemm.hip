@@ -981,3 +981,74 @@ extern "C" int bgpo_test_gemm_tn(const uint16_t* A, const uint16_t* B, float* C,
   k_gemm4w<EPI_F32_ACCUM, A_MSLAB, BGPO_TILE4><<<gemm_grid(dev), kGemmThreads4, 0, (hipStream_t)stream>>>(p);
   return hipGetLastError() == hipSuccess ? 0 : -3;
 }
+
+// ---- test hooks: the GEMM core in each form that the library launches, on
+// either tile, and two GEMMs sharing a launch ----
+namespace bgpo {
+
+// C[s][n][m] (+)= the product of K slice s; false: operands the form cannot hold
+static bool test_params(const uint16_t* A, int a_layout, const uint16_t* B, float* C, int32_t M, int32_t N,
+                        int32_t K, int32_t n_split, GemmParams* out) {
+  if (!A || !B || !C || M <= 0 || N <= 0 || K <= 0 || K % 64 || M % (a_layout == A_MSLAB ? 64 : 4) ||
+      n_split < 1 || n_split > 255 || a_layout < A_ROW || a_layout > A_KSLAB ||
+      (int64_t)((M + 127) / 128) * ((N + 127) / 128) * n_split >= (int64_t(1) << 30))
+    return false;
+  GemmParams p = base_params();
+  p.A = A; p.lda = a_layout == A_KSLAB ? M : K;
+  p.B = B; p.ldb = N;
+  p.M = M; p.N = N; p.K = K;
+  p.n_split = n_split;
+  p.k_split = ((K + n_split - 1) / n_split + 63) / 64 * 64;
+  p.group_m = kGroupMdX;
+  p.out = C; p.ldo = M; p.split_stride = (int64_t)M * N;
+  *out = p;
+  return true;
+}
+
+}  // namespace bgpo
+
+extern "C" int bgpo_test_gemm(const uint16_t* A, int32_t a_layout, const uint16_t* B, float* C, int32_t M,
+                              int32_t N, int32_t K, int32_t n_split, int32_t accumulate, int32_t tile,
+                              void* stream) {
+  using namespace bgpo;
+  GemmParams p;
+  if (!test_params(A, a_layout, B, C, M, N, K, n_split, &p) || (tile != 128 && tile != 256) ||
+      (a_layout == A_MSLAB && !accumulate))
+    return -1;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return -3;
+  const bool small = tile == 128;
+  const int grid = gemm_grid(dev);
+  hipStream_t s = (hipStream_t)stream;
+  hipError_t e;
+  if (a_layout == A_MSLAB)
+    e = launch_tiled<EPI_F32_ACCUM, A_MSLAB>(small, grid, p, s);
+  else if (a_layout == A_KSLAB)
+    e = accumulate ? launch_tiled<EPI_F32_ACCUM, A_KSLAB>(small, grid, p, s)
+                   : launch_tiled<EPI_F32_STORE, A_KSLAB>(small, grid, p, s);
+  else
+    e = accumulate ? launch_tiled<EPI_F32_ACCUM, A_ROW>(small, grid, p, s)
+                   : launch_tiled<EPI_F32_STORE, A_ROW>(small, grid, p, s);
+  return e == hipSuccess ? 0 : -3;
+}
+
+extern "C" int bgpo_test_gemm_pair(const uint16_t* A, int32_t a_layout, const uint16_t* B, float* C, int32_t M,
+                                   int32_t N, int32_t K, int32_t n_split, const uint16_t* A2,
+                                   const uint16_t* B2, float* C2, int32_t M2, int32_t N2, int32_t K2,
+                                   int32_t n_first, void* stream) {
+  using namespace bgpo;
+  GemmParams p, q;
+  if (!test_params(A, a_layout, B, C, M, N, K, n_split, &p) || a_layout == A_MSLAB ||
+      !test_params(A2, A_MSLAB, B2, C2, M2, N2, K2, 1, &q))
+    return -1;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return -3;
+  const int grid = gemm_grid(dev);
+  if (n_first < 8 || n_first % 8 || n_first > grid - 8) return -1;
+  hipStream_t s = (hipStream_t)stream;
+  if (a_layout == A_KSLAB)
+    k_gemm4w_dx_dw<A_KSLAB, BGPO_TILE4S><<<grid, kGemmThreads4, 0, s>>>(p, q, (uint32_t)n_first);
+  else
+    k_gemm4w_dx_dw<A_ROW, BGPO_TILE4S><<<grid, kGemmThreads4, 0, s>>>(p, q, (uint32_t)n_first);
+  return hipGetLastError() == hipSuccess ? 0 : -3;
+}

@@ -131,6 +131,14 @@ def test_gemm_hooks_check_shapes_before_hip(b):
     assert lib.bgpo_test_gemm_tn(fake, fake, fake, 96, 64, 64, None) == -1
     assert lib.bgpo_test_gemm_tn(None, fake, fake, 64, 64, 64, None) == -1
     assert lib.bgpo_test_gemm_split(fake, fake, fake, 64, 64, 64, 0, None) == -1
+    # the forms of either tile, and two of them in one launch
+    ok = (fake, 0, fake, fake, 64, 64, 64, 1)
+    for M, N, K, s, layout, acc, tile in ((64, 64, 96, 1, 0, 0, 128), (66, 64, 64, 1, 0, 0, 128), (96, 64, 64, 1, 1, 1, 128),
+                                          (64, 64, 64, 1, 1, 0, 128), (64, 64, 64, 1, 3, 0, 128),
+                                          (64, 64, 64, 0, 0, 0, 128), (64, 64, 64, 1, 0, 0, 192)):
+        assert lib.bgpo_test_gemm(fake, layout, fake, fake, M, N, K, s, acc, tile, None) == -1
+    assert lib.bgpo_test_gemm_pair(fake, 1, fake, fake, 64, 64, 64, 1, fake, fake, fake, 64, 64, 64, 8, None) == -1
+    assert lib.bgpo_test_gemm_pair(*ok, fake, fake, fake, 96, 64, 64, 8, None) == -1
 
 
 def test_problem_struct_layout(b):
