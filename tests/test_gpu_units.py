@@ -246,3 +246,43 @@ def test_dw_batches_end_where_rows_no_longer_fit(budget_mib):
     for k in ("ell", "g", "nm", "dX"):
         assert np.array_equal(one[k], many[k]), k
     assert rel_maxnorm(one["dW"], many["dW"]) <= 1e-5
+
+
+@pytest.mark.parametrize("B,L,d,V,n_t,budget_mib,plan", [
+    (2, 500, 1024, 65600, 22, 640, (3, 1)),      # units of three samples, the last of one
+    (2, 500, 1024, 65600, 22, 1040, (3, 2)),
+    (1, 65600, 2048, 33024, 6, 12500, (2, 1)),   # of two, masks in several passes over the GPU
+], ids=["units of 3", "units of 3, two at least", "multi-block masks"])
+def test_dw_batches_of_units_of_several_samples(B, L, d, V, n_t, budget_mib, plan):
+    """As above with several samples per unit: some units join the batch of the
+    one before them and some do not, as their rows decide.  The whole range in
+    one call against one call per unit: dX bit for bit, dW up to the order of
+    fp32 sums (1e-5)."""
+    b = lib()
+    budget = budget_mib << 20
+    w = workloads.Workload("flush", B=B, L=L, d=d, V=V, n_t=n_t, adv="normal", group=B, targets="uniform",
+                           data_seed=2600, philox_seed=0xB6B80001)
+    p = b.bgpo_workspace_plan(b.Problem(B, L, d, V, n_t, ws_budget=budget))
+    G = p["samples_per_unit"]
+    assert (p["mode"], G, p["dw_batch"]) == ("stored", *plan)
+    x = workloads.generate(w)
+    outs = []
+    for ranges in ([(0, n_t)], [(j, min(G, n_t - j)) for j in range(0, n_t, G)]):
+        r = Runner(w, x, ws_budget=budget)
+        for j0, n in ranges:
+            r.bwd(j_begin=j0, j_count=n)
+        outs.append(r.out())
+        del r
+    one, many = outs
+    per_sample = one["nm"].sum(0)
+    rows = [int(per_sample[j:j + G].sum()) for j in range(0, n_t, G)]
+    cap = plan[1] * G * ((B * L + 255) // 256 * 256)
+    end, joined = 0, []
+    for n in rows:                       # the column after the batch's last unit
+        joined.append(end > 0 and end + (n + 255) // 256 * 256 <= cap)
+        end = (end if joined[-1] else 0) + (n + 63) // 64 * 64
+    assert any(joined) and not all(joined[1:])
+    for k in ("ell", "g", "nm", "dX"):
+        assert np.array_equal(one[k], many[k]), k
+    assert rel_maxnorm(one["dW"], many["dW"]) <= 1e-5
+    assert np.abs(one["dW"]).max() > 0 and one["flags"] == 0
