@@ -21,7 +21,6 @@
 // samples (except in the retained-state contrast mode of the exact
 // objective).
 #include <math.h>
-#include <stdlib.h>
 #include <string.h>
 
 #include <algorithm>
@@ -716,12 +715,19 @@ constexpr int64_t kFlushBytes = int64_t(256) << 20;
 // faster when it has few.  Steps without and with the copy: 2048-4096 positions
 // 7.49 and 7.62 ms, 8192 (as 4 samples of 2048) 10.19 and 10.30, 16384 20.73 and
 // 20.77, 32768 38.49 and 38.36; d 2048 V 32000, 4096 positions 0.931 and 0.947;
-// V 65600, 2048 positions 1.51 and 1.56.  Some row pitches of W are slow in
-// place: V 66048 (129 KB) dX 677 us against 418, V 65024 (127 KB) 470 and 387, up
-// to 6 % at other pitches of 127-137 KB, and V 65536 15 %; of 60 others between 9
-// and 255 KB, 0.89 to 1.03 of the time with the copy.
+// V 65600, 2048 positions 1.51 and 1.56.
+//
+// Some row pitches of W are slow in place, those at which the rows of a tile meet
+// in few memory channels: many multiples of 2 KB, and the multiples of 127 and 129
+// times 512 bytes.  The copies of W and the dX GEMM together, in place against
+// copied: V 66048 (129 KB) 1.16-1.35, 65024 1.08-1.28, 99072 1.00-1.07, 130048
+// 1.16-1.27, 88064 1.43, 520192 1.56.  Elsewhere in place was no slower, mostly 5
+// to 25 % faster: every V of 4096 to 139840 (512 positions, d 4096) and of 8192 to
+// 131008 (d 512, within its noise below V 30000), every multiple of 256 from there
+// to 2^20 (d 512), every V around 32768, 65536 and 131072 (d 1024; 65536 at 4096
+// positions of d 2048 too).  V 130560 and 131584 at d 512 are 4 % slower.
 static bool copy_pays(int64_t positions, int V) {
-  return positions > 8192 || V % 1024 == 0 || std::abs(V - 65536) <= 5120;
+  return positions > 8192 || V % 1024 == 0 || V % (127 * 256) == 0 || V % (129 * 256) == 0;
 }
 
 // dX (and dgamma with the norm) are per sample at dX + (j - j_begin) * stride.

@@ -198,6 +198,7 @@ def test_moments_around_the_streaming_line(n, offset):
     (32, 128, 576),     # the largest call that reads W in place
     (32, 129, 576),     # the smallest that makes the slab-major copy
     (4, 33, 1024),      # rows a multiple of 2 KB apart: the copy at any size
+    (1, 33, 33024),     # of 129 times 512 bytes: the same
 ])
 def test_w_in_place_or_copied(B, L, V):
     """The dX GEMM on the caller's row-major bf16 W and on its slab-major copy,
