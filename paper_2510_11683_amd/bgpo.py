@@ -180,10 +180,17 @@ def _in_types(prob: "Problem"):
     return (torch.float32,) if prob.in_dtype == BGPO_F32 else _BF16
 
 
+# the handle of a device's current stream without a Stream object (2 us less per
+# call); not a public name, so a torch without it takes the public way
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream):
-    if stream is None:   # the current device's current stream, without a Stream object
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
-    return stream.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def bgpo_version() -> int:

@@ -287,3 +287,17 @@ def test_dw_batches_of_units_of_several_samples(B, L, d, V, n_t, budget_mib, pla
         assert np.array_equal(one[k], many[k]), k
     assert rel_maxnorm(one["dW"], many["dW"]) <= 1e-5
     assert np.abs(one["dW"]).max() > 0 and one["flags"] == 0
+
+
+def test_binding_passes_the_current_stream(monkeypatch):
+    """The handle that the binding passes is the current stream's, on the default
+    stream and inside a stream context, with and without torch's unlisted
+    accessor; a stream that is named goes as it is."""
+    b = lib()
+    side = torch.cuda.Stream()
+    for raw in (b._raw_stream, None):
+        monkeypatch.setattr(b, "_raw_stream", raw)
+        assert b._stream(None) == torch.cuda.current_stream().cuda_stream
+        with torch.cuda.stream(side):
+            assert b._stream(None) == side.cuda_stream != 0
+        assert b._stream(side) == side.cuda_stream
