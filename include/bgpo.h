@@ -166,8 +166,8 @@ typedef struct bgpo_problem {
  *                         log2 units, so that dZ = s (softmax - onehot) is
  *                         one factor per row times them, except at the
  *                         target: three GEMM passes per sample, a workspace
- *                         of about rows x V x 4 bytes per unit (the two units
- *                         of a dW batch; 24 GB at B=8, L=512, d=4096,
+ *                         of about rows x V x 4 bytes per unit (two fully
+ *                         masked units share a dW GEMM; 24 GB at B=8, L=512, d=4096,
  *                         V=126464 with units of 8 samples).  The dX GEMM
  *                         reads a slab-major bf16 copy of W_head (2 d V
  *                         bytes, re-staged every call; calls over few
@@ -184,7 +184,7 @@ typedef struct bgpo_problem {
  *                         sample, nothing of size rows x V is ever stored
  * ws_budget = 0 and vocab_chunk = 0 give the stored mode with units of up to
  * 8 samples within about 32 GB.  A nonzero ws_budget takes that layout if
- * it fits, with the dW batch raised to up to 4 units while the budget allows
+ * it fits, with room for a dW batch of up to 4 units while the budget allows
  * (fewer read-modify-writes of dW); below it, the stored-mode layout (unit,
  * dW batch, dX split capacity) of least estimated time that fits; if none
  * does, the recompute mode with the unit and chunk width of least estimated

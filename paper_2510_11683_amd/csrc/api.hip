@@ -35,10 +35,10 @@ namespace bgpo {
 static size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 constexpr int64_t kMaxUnit = 8;
-constexpr int64_t kDwUnits = 2;   // units per dW GEMM in the constant-memory mode
-// units per dW GEMM that a workspace budget above the default layout may buy
-// (each halving of the dW read-modify-writes saves about 1 % of the step at
-// the LLaDA head shape)
+constexpr int64_t kDwUnits = 2;   // fully masked units that the dW buffers hold
+// the same, that a workspace budget above the default layout may buy (each
+// halving of the dW read-modify-writes saves about 1 % of the step at the LLaDA
+// head shape)
 constexpr int64_t kDwUnitsMax = 4;
 constexpr int64_t kGiB = int64_t(1) << 30;
 
@@ -109,8 +109,9 @@ size_t workspace_layout(const Dims& dm, const Plan& pl, void* base, Workspace* w
   const size_t unit_bytes = off;   // the same for every unit (all pieces 256-byte aligned)
   off = unit_bytes * n_units;
   w.dbar = static_cast<double*>(take(dm.B * 8));
-  take((NP / 256) * dm.d * 4);   // not used: a problem's layouts keep their sizes, so that a
-                                 // budget or the static scratch holds what it always held
+  // not used: without it a budget could hold a plan that it did not hold before, and
+  // the plan decides the order in which dX and dW are summed
+  take((NP / 256) * dm.d * 4);
   w.HcT = static_cast<uint16_t*>(take(KT * dm.d * 2));
   w.WT = static_cast<uint16_t*>(take((size_t)dm.V * dm.d * 2));
   // the slab-major bf16 W of the dX GEMM (without it the GEMM reads the
@@ -148,8 +149,8 @@ static size_t plan_bytes(const Dims& dm, const Plan& pl) {
 }
 
 // The stored-exponential plan used without a budget: units of up to 8
-// samples while the unit's H_c and the dZ rows and H_c^T columns of a dW
-// batch of two units stay within about 32 GB; dX split capacity up to 16
+// samples while the unit's H_c and the dZ rows and H_c^T columns of two fully
+// masked units stay within about 32 GB; dX split capacity up to 16
 // within about 4 GB.  With every sample retained, the same units (at most n_t
 // samples each) each keep their own state and all of them form the one dW
 // batch, so both modes run the same unit compositions.
@@ -169,8 +170,10 @@ static Plan default_plan(const Dims& dm, int retain) {
 // about half of the positions masked, as E[t] = 1/2), plus the fp32
 // read-modify-write traffic that the chunking adds (dX partials once per
 // chunk and split, dW once per unit).  Used only to rank plans.
-// The grid fill of a GEMM of `tiles` tiles on 256 workgroups, averaged over
-// masked fractions 0.4 .. 0.6 of the positions (rows_t row tiles at 0.5)
+// The grid fill of a GEMM of 256-wide tiles on 256 workgroups, averaged over
+// masked fractions 0.4 .. 0.6 of the positions (rows_t row tiles at 0.5).  (The
+// GEMMs take 128-wide tiles where these leave much of the grid idle; the fill of
+// such a plan is better than ranked here.)
 static double mean_fill(double rows_cap, double other_tiles, double split) {
   double f = 0.0;
   for (double q : {0.4, 0.45, 0.5, 0.55, 0.6}) {
@@ -201,7 +204,9 @@ static double recompute_cost(const Dims& dm, const Plan& pl) {
 // The same estimate for the stored-exponential backward: three GEMM passes
 // (the dX GEMM at the best split the capacity allows, about 2 % faster on
 // the slab-major copy of W), the forward's stores of the kept exponentials
-// (2 bytes per entry) and the dW read-modify-write once per batch of units.
+// (2 bytes per entry) and the dW read-modify-write once per dw_batch units.  (The
+// batches of a large dW take as many units as their masked rows fit, about twice as
+// many: such a plan reads and writes dW less often than ranked here.)
 // fwd_fill, dx_fill: the forward's and the dX GEMM's grid fills.
 static double stored_cost(const Dims& dm, const Plan& pl, double fwd_fill, double dx_fill) {
   const double NP = (double)padded_positions(dm);

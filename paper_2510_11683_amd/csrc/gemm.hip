@@ -277,9 +277,10 @@ __device__ __forceinline__ void gemm4w(const GemmParams& p, uint4* smem, uint32_
     k_split = (int64_t)p.meta->dx_kslab * 64;   // whole 64-deep slabs
   }
   if (EPI == EPI_F32_ACCUM && K == 0) return;   // nothing to add
-  // The tile walk in 32-bit wave-uniform (scalar) arithmetic: tile counts
-  // stay below 2^30 for every launch (tiles of M and N below 2^12 and 2^14,
-  // at most 16 splits; the test hook checks its own).
+  // The tile walk in 32-bit wave-uniform (scalar) arithmetic: tile counts stay
+  // below 2^30 for every launch (128-wide tiles: at most 2^13 of the vocabulary,
+  // 2^15 of the rows and 2^9 of d, and 16 splits of dX, so 2^28 of the forward and
+  // of dX; the test hooks check their own).
   const uint32_t tilesM = __builtin_amdgcn_readfirstlane((M + BM - 1) / BM);
   const uint32_t tilesN = __builtin_amdgcn_readfirstlane((N + BN - 1) / BN);
   const uint32_t per_split = tilesM * tilesN;

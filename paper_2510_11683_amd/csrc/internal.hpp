@@ -122,7 +122,8 @@ struct Workspace {
   int64_t G;           // samples per unit
   int64_t RP;          // G * NP: row capacity of a unit
   int64_t n_split;     // capacity of dx_part in splits (the unit's count is in its meta)
-  int64_t dw_batch;    // units whose dW contributions share one GEMM
+  int64_t dw_batch;    // fully masked units that the dW buffers hold: so many share a dW GEMM, or,
+                       // with max_cols, as many as their masked rows fit
   int64_t KT;          // dw_batch * RP: columns of H_c^T, rows of the stored dZ
   int64_t ldz;         // rows per slab of dZ: KT + kDzPadRows (stored), RP (recompute)
   int64_t chunk;       // 0: stored exponentials; > 0: recompute backward, vocabulary chunk width
@@ -141,7 +142,7 @@ struct Dims {
 // the budget (never from n_t, except the unit count of the retained mode).
 struct Plan {
   int64_t G;          // samples per unit
-  int64_t dw_batch;   // units per dW GEMM (stored mode)
+  int64_t dw_batch;   // fully masked units that the dW buffers hold (stored mode)
   int64_t n_split;    // capacity of the dX split partials, in splits
   int64_t chunk;      // 0: stored exponentials; > 0: recompute in vocabulary chunks of this width
   int retain;         // every unit keeps its own state (memory grows with n_t)
@@ -152,8 +153,8 @@ struct Plan {
 
 // Views into the caller's workspace for plan `pl` (base may be NULL: sizes
 // only).
-// retain = 0: the state of one unit of G samples at a time, dw_batch units
-//             per dW GEMM; the size does not depend on n_t.
+// retain = 0: the state of one unit of G samples at a time, the rows and columns
+//             of dw_batch units for the dW GEMM; the size does not depend on n_t.
 // retain = 1: the same units (G capped at n_t), each keeping its own state
 //             (units[0 .. ceil(n_t / G)): meta, rows, partials, H_c; H_c^T
 //             and dZ hold all units' columns and rows; one dW batch), so
