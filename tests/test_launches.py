@@ -105,3 +105,19 @@ def test_timing_record_counts_the_launches_made(recorder, fn, kw):
         want[_class_of(name)] += 1
     assert dict(zip(b.KERNEL_CLASSES, r["counts"])) == dict(zip(b.KERNEL_CLASSES, want))
     assert r["ms"] == want
+
+
+@pytest.mark.parametrize("V,copied", [
+    (32768, True), (65536, True), (88064, True),                         # rows a multiple of 2 KB apart
+    (32512, True), (33024, True), (65024, True), (66048, True), (99072, True),   # of 127 or 129 x 512 bytes
+    (32000, False), (60928, False), (65600, False), (70656 - 64, False), (126464, False), (151936, False),
+])
+def test_short_calls_copy_w_at_slow_row_pitches_only(recorder, V, copied):
+    """Which W the dX GEMM of a call over 512 positions reads: its slab-major copy
+    (layout 2) or the caller's rows (0); over 16384 positions always the copy."""
+    from paper_2510_11683_amd import bgpo as b
+    probs = [b.Problem(B, L, 1024, V, 1) for B, L in ((2, 256), (16, 1024))]
+    res = record(recorder, [_call("bgpo_elbo_bwd_accumulate", p) for p in probs])
+    layouts = [{m[1] for n, _, _ in r["launches"] for m in [re.search(r"k_gemm4wILi2ELi(\d)E", n)] if m}
+               for r in res]
+    assert layouts == [{"2" if copied else "0"}, {"2"}]
